@@ -591,9 +591,12 @@ rt_status rt_graph_set_frames(rt_graph* g, const void* const* frames, void* cons
 /* Synchronize the device and report RT_EDEVICE if a HIP error is pending. */
 rt_status rt_ctx_check(rt_ctx* ctx);
 
-/* Performance knobs that never change results.  grid == 0 (the default):
- * each vertical block of each camera is cut into tiles of equal height of at
- * most tile_rows rows (1..4096), one apply workgroup per tile.  grid > 0
+/* Performance knobs that never change results.  The default (tile_rows 32, grid
+ * 0): about two apply workgroups per compute unit, shared among the cameras
+ * by their bytes, each on an even share of its camera's rows.  grid == 0 with
+ * another tile_rows (1..4096): each vertical block of each camera is cut into
+ * tiles of equal height of at most tile_rows rows, one apply workgroup per
+ * tile.  grid > 0
  * (up to 65536): that many workgroups, each on a contiguous share of rows,
  * cut into segments at block boundaries and at most tile_rows rows; with at
  * least one workgroup per camera every camera gets a whole number of shares

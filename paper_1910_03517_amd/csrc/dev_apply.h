@@ -1,21 +1,35 @@
-// Apply pass of section 3.1 as device functions over segments of rows: every
-// sample is blended between the identity and its side's affine map with the
-// Q8 weight of its column, y = ((256 - w) x + w f(x) + 128) >> 8, in exact
+// Apply pass of section 3.1 as device functions over rows of one camera:
+// every sample is blended between the identity and its side's affine map with
+// the Q8 weight of its column, y = ((256 - w) x + w f(x) + 128) >> 8, in exact
 // integers; optionally fused with the whole-frame histogram and sums of the
 // input samples.
 //
-// A thread owns groups of 4 consecutive pixels of a row (12 bytes for RGB8, 4
-// for gray8, 8 for gray16) and walks down its segments' rows, kUnroll rows at
-// a time so that several loads are in flight; its pixels' weights and map
-// constants stay in registers.  The histogram is kept in LDS in kRep replicas
+// A workgroup of kApplyThreads threads takes a run of rows.  Its threads lie
+// over the image as ap_lanes rows of ap_cols groups of 4 consecutive pixels
+// (12 bytes for RGB8, 4 for gray8, 8 for gray16); a thread keeps its columns
+// and walks down the run ap_lanes rows at a time, kUnroll rows in flight, so
+// its pixels' weights and its side's map constants stay in registers.  Images
+// whose groups do not fit the workgroup in one row, or fill it badly, are
+// taken in ap_chunks column chunks (chosen per camera on the host).  The maps
+// of the run's blocks (or, blended between blocks, of its rows) are staged in
+// LDS, kMapBytes at a time.  The histogram is kept in LDS in kRep replicas
 // interleaved bin by bin, lane l updating replica l % kRep, so that lanes of
-// one wave that see the same value mostly hit different LDS words (packed
-// variants, two 16-bit bins per word, are compile-time options; the segment
-// tables then bound the rows between flushes so that no half can reach
-// 2^16).  After a workgroup's last segment of a camera the replicas are summed
-// and added to the camera's whole-frame statistics with global atomics (the
-// whole-frame buffers must be zero before the first segment).
+// one wave that see the same value mostly hit different LDS words; after the
+// run the replicas are summed and added to the camera's whole-frame
+// statistics with global atomics (the whole-frame buffers must be zero before
+// the first run).
+//
+// What bounds it: memory requests in flight and, next to them, the vector ALU
+// and the LDS atomics, each busy about half of the time.  Long runs pay the
+// set-up and the flush of the histogram once per half compute unit, and rows
+// side by side keep narrow images' workgroups full.  Measured on MI355X
+// against one 256-thread workgroup per 22-row tile (us, statistics fused):
+// 14x1920x1080 RGB8 50.6 -> 44.7 (174 MB: 3.4 -> 3.9 TB/s), 1x640x480 18.0 ->
+// 10.6, 5x1031x517 RGB8 + 3x333x251 u16 + 2x719x405 gray8 57 -> 17, which was
+// the ragged row ends, read byte by byte and row by row.
 #pragma once
+
+#include <type_traits>
 
 #include "dev_estimate.h"
 #include "dev_stats.h"
@@ -24,12 +38,11 @@ namespace rc {
 
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x3 __attribute__((ext_vector_type(3)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 #ifndef RC_APPLY_UNROLL
-#define RC_APPLY_UNROLL 6     // measured on MI355X: best when applies of consecutive frame-sets overlap
-#endif
-#ifndef RC_APPLY_DIRECT
-#define RC_APPLY_DIRECT 1     // evaluate 8-bit maps from their Q16 pairs instead of the LDS tables
+#define RC_APPLY_UNROLL 6
 #endif
 #ifndef RC_LOAD_POLICY
 #define RC_LOAD_POLICY 2      // non-temporal: every frame byte is touched exactly once
@@ -37,33 +50,19 @@ typedef unsigned int u32x3 __attribute__((ext_vector_type(3)));
 #ifndef RC_STORE_POLICY
 #define RC_STORE_POLICY 2
 #endif
-constexpr bool kPack = RC_APPLY_PACK != 0;  // two 16-bit bins per histogram word
-constexpr int kRep = RC_APPLY_REP;        // histogram replicas
-constexpr int kHistWords = kCS * (kPack ? kNB / 2 : kNB) * kRep;
-constexpr int kUnroll = RC_APPLY_UNROLL;  // rows in flight per thread
+constexpr int kRep = 8;                        // histogram replicas
+constexpr int kUnroll = RC_APPLY_UNROLL;       // rows in flight per thread
 constexpr int kLoadPolicy = RC_LOAD_POLICY;    // cache-policy bits of frame loads
 constexpr int kStorePolicy = RC_STORE_POLICY;  // cache-policy bits of frame stores
 
-// Word (before the replica index) and bit offset of (channel c, bin) in the
-// LDS histogram.  Unpacked: a word per bin.  RC_APPLY_PACK 1: bins 2i and
-// 2i + 1 share word i; RC_APPLY_PACK 2: bins i and i + 128 share word i, so
-// that neighbouring values, frequent within a region, fall in different words.
-__device__ inline int hist_word(int c, uint32_t bin) {
-  if (RC_APPLY_PACK == 1) return c * (kNB / 2) + (int)(bin >> 1);
-  if (RC_APPLY_PACK == 2) return c * (kNB / 2) + (int)(bin & (kNB / 2 - 1));
-  return c * kNB + (int)bin;
-}
-__device__ inline uint32_t hist_shift(uint32_t bin) {
-  if (RC_APPLY_PACK == 1) return (bin & 1u) << 4;
-  if (RC_APPLY_PACK == 2) return (bin >> 7) << 4;
-  return 0u;
-}
+constexpr int kMapBytes = 3072;                // staged maps
+constexpr int kMapEntries = 64;                // most blocks (or rows) staged at a time
 
 struct ApplyLds {
-  uint8_t lut[2 * kCS * kNB];          // [side][channel][x]
-  int64_t q[4];                        // [side][A, Bq]
-  uint32_t hist[kHistWords];           // [channel][bin (pair when packed)][replica]
-  unsigned long long red[9 * 16];
+  alignas(16) uint8_t map[kMapBytes];          // [block or row][side][channel] maps, see stage_maps
+  alignas(16) uint32_t hist[kCS * kNB * kRep]; // [channel][bin][replica]
+  int32_t end[kMapEntries];                    // first row after each staged block
+  unsigned long long sums[9];                  // [channel] (n, S1, S2) of the run
 };
 
 template <int NW, int POL = kLoadPolicy>
@@ -92,240 +91,61 @@ __device__ inline void store_group(__amdgpu_buffer_rsrc_t r, int off, const uint
   }
 }
 
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+// The first nb (1 .. 4 NW) bytes of a group at the ragged end of a row, whole
+// dwords first, then the rest: no byte beyond the row is touched.
+template <int NW>
+__device__ inline void load_part(__amdgpu_buffer_rsrc_t r, int off, int nb, uint32_t (&d)[NW]) {
+#pragma unroll
+  for (int q = 0; q < NW; ++q) {
+    const int rem = nb - 4 * q;
+    d[q] = 0;
+    if (rem >= 4) d[q] = __builtin_amdgcn_raw_buffer_load_b32(r, off + 4 * q, 0, 0);
+    else if (rem >= 2) {
+      d[q] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, off + 4 * q, 0, 0);
+      if (rem == 3) d[q] |= (uint32_t)(uint8_t)__builtin_amdgcn_raw_buffer_load_b8(r, off + 4 * q + 2, 0, 0) << 16;
+    } else if (rem == 1) d[q] = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(r, off + 4 * q, 0, 0);
+  }
+}
 
-// Per-pixel constants of a thread's group.
-struct PixConst {
-  uint32_t wp[4];         // Q8 weight pair: (256 - w) in the low half, w in the high half
-  int lb[4];              // table base of the pixel's side
-  int64_t qa[4], qb[4];   // 16-bit map of the pixel's side
-  int32_t da[4][3];       // direct 8-bit map of the pixel's side: A and Bq + 2^15 per channel
-  int32_t dc[4][3];
+template <int NW>
+__device__ inline void store_part(__amdgpu_buffer_rsrc_t r, int off, int nb, const uint32_t (&d)[NW]) {
+#pragma unroll
+  for (int q = 0; q < NW; ++q) {
+    const int rem = nb - 4 * q;
+    if (rem >= 4) __builtin_amdgcn_raw_buffer_store_b32(d[q], r, off + 4 * q, 0, 0);
+    else if (rem >= 2) {
+      __builtin_amdgcn_raw_buffer_store_b16((uint16_t)d[q], r, off + 4 * q, 0, 0);
+      if (rem == 3) __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(d[q] >> 16), r, off + 4 * q + 2, 0, 0);
+    } else if (rem == 1) __builtin_amdgcn_raw_buffer_store_b8((uint8_t)d[q], r, off + 4 * q, 0, 0);
+  }
+}
+
+// How a run's maps are staged and evaluated, f(x) = clamp((A x + Bq + 2^15) >> 16):
+//   kMapDirect  32-bit integers: (A, Bq + 2^15) as int32, for 8-bit samples whose
+//               maps pass small_map;
+//   kMapWide    64-bit integers: (A, Bq) as int64;
+//   kMapTable   the caller's 256-entry tables (8-bit samples);
+//   kMapCross / kMapCrossWide  3x3 maps across the channels, f_r(x) =
+//               clamp((A_r . x + B_r + 2^15) >> 16, 0, 255), in 32-bit integers
+//               (B_r + 2^15 staged) or 64-bit ones.
+enum { kMapDirect, kMapWide, kMapTable, kMapCross, kMapCrossWide };
+
+constexpr int kX3 = 12;   // parameters of one 3x3 map
+
+template <int KIND, int C>
+struct MapEntry {   // bytes of one block's (or row's) staged maps, both sides
+  static constexpr int kBytes = KIND == kMapDirect ? 2 * C * 8 : KIND == kMapWide ? 2 * C * 16
+                                : KIND == kMapTable ? 2 * C * kNB : KIND == kMapCross ? 2 * kX3 * 4 : 2 * kX3 * 8;
+  static constexpr int kCap = kMapBytes / kBytes < kMapEntries ? kMapBytes / kBytes : kMapEntries;
 };
 
-// The 8-bit table entry f(x) = clamp((A x + Bq + 2^15) >> 16, 0, 255) can be
-// evaluated directly in 32-bit integers, bit for bit equal to the table, when
-// |A| < 2^23 (a 24-bit multiply) and A x + Bq + 2^15 stays inside int32 for
-// x in [0, 255].  The check is made once per segment on its six (A, Bq) pairs.
-__device__ inline bool direct_ok(int64_t A, int64_t Bq) {
-  if (A >= (1 << 23) || A < -(1 << 23)) return false;
-  const int64_t c = Bq + 32768, e = 255 * A + c;
-  const int64_t lo = c < e ? c : e, hi = c < e ? e : c;
-  return lo >= INT32_MIN && hi <= INT32_MAX;
-}
-
-// Returns the blended sample, or with RAW the dot product itself: the sample
-// is then its byte 1 and bytes 2-3 are zero (the sum stays below 2^16).
-template <int BPS, bool WRITE, bool STATS, bool DIRECT = false, bool RAW = false>
-__device__ inline uint32_t one_sample(uint32_t x, int c, int p, const PixConst& pc, ApplyLds& L, int hrep,
-                                      int shift, uint32_t maxv, unsigned long long& a1, unsigned long long& a2) {
-  if (STATS) {
-    uint32_t bin = x;
-    if (BPS == 2) { bin = x >> shift; bin = bin > 255u ? 255u : bin; }
-    __hip_atomic_fetch_add(&L.hist[hist_word(c, bin) * kRep + hrep], 1u << hist_shift(bin), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_WORKGROUP);
-    if (BPS == 2) { a1 += x; a2 += (unsigned long long)x * x; }
-  }
-  if (!WRITE) return 0;
-  uint32_t f, xf;
-  if (BPS == 1 && DIRECT) {
-    // da holds a sign-extended 24-bit value (see direct_ok), so this is a 24-bit multiply.
-    // clamp(v >> 16, 0, 255) << 16 == clamp(v, 0, 2^24 - 1) & 0xffff0000 for the
-    // arithmetic shift, so f lands in the high half of (x, f) directly.
-    const int32_t a24 = (int32_t)((uint32_t)pc.da[p][c] << 8) >> 8;
-    int32_t v = a24 * (int32_t)x + pc.dc[p][c];
-    v = v < 0 ? 0 : (v > 0xffffff ? 0xffffff : v);
-    xf = ((uint32_t)v & 0xffff0000u) | x;
-  } else if (BPS == 1) {
-    f = L.lut[pc.lb[p] + c * kNB + x];
-  } else {
-    int64_t y = (pc.qa[p] * (int64_t)x + pc.qb[p] + 32768) >> 16;
-    y = y < 0 ? 0 : (y > (int64_t)maxv ? (int64_t)maxv : y);
-    f = (uint32_t)y;
-  }
-  // ((256 - w) x + w f + 128) >> 8 as one dot product of (x, f) with (256 - w, w).
-  if (!(BPS == 1 && DIRECT)) xf = x | (f << 16);
-  const uint32_t dot =
-      __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, xf), __builtin_bit_cast(u16x2, pc.wp[p]), 128u, false);
-  return RAW ? dot : dot >> 8;
-}
-
-// Four raw dot products (see one_sample) to one dword of samples: byte 1 of
-// each, in order, by two byte permutes (selector byte 0x0c gives zero).
-__device__ inline uint32_t pack_raw4(uint32_t r0, uint32_t r1, uint32_t r2, uint32_t r3) {
-  return __builtin_amdgcn_perm(r1, r0, 0x0c0c0501u) | __builtin_amdgcn_perm(r3, r2, 0x05010c0cu);
-}
-
-// Adds the workgroup's LDS histogram of camera `cam` (replicas summed) and
-// its share of (n, S1, S2) - linear in the histogram for 8-bit samples, from
-// the sample sums a1, a2 for 16-bit ones - to the camera's whole-frame
-// statistics.
-template <int C, int BPS>
-__device__ inline void flush_whole(const Geo& g, const Bufs& b, int cam, ApplyLds& L, unsigned long long a1,
-                                   unsigned long long a2) {
-  const int tid = threadIdx.x;
-  __syncthreads();
-  uint32_t* gh = b.whole_hist + (int64_t)cam * kCS * kNB;
-  uint32_t h[kCS];
-#pragma unroll
-  for (int c = 0; c < kCS; ++c) {
-    uint32_t sum = 0;
-    if (c < C) {
-      if (kPack) {
-        // Thread tid owns bin tid; the replica order is rotated per word so
-        // that the lanes of a wave read distinct banks.
-        const int wd = hist_word(c, (uint32_t)tid);
-        const uint32_t sh = hist_shift((uint32_t)tid);
-#pragma unroll 8
-        for (int i = 0; i < kRep; ++i) sum += (L.hist[wd * kRep + ((i + wd) & (kRep - 1))] >> sh) & 0xffffu;
-      } else {
-#pragma unroll
-        for (int r = 0; r < kRep; ++r) sum += L.hist[(c * kNB + tid) * kRep + r];
-      }
-    }
-    h[c] = sum;
-    if (sum) atomicAdd(&gh[c * kNB + tid], sum);
-  }
-  const unsigned long long x = (unsigned long long)tid;
-  const unsigned long long h0 = h[0], h1 = h[1], h2 = h[2];
-  block_sums(
-      (BPS == 2) ? 3 : 3 * C,
-      [=](int i) -> unsigned long long {
-        const int c = i / 3, m = i - 3 * (i / 3);
-        const unsigned long long hc = c == 0 ? h0 : (c == 1 ? h1 : h2);
-        if (m == 0) return hc;
-        if (BPS == 2) return m == 1 ? a1 : a2;
-        return m == 1 ? hc * x : hc * x * x;
-      },
-      [&](int i, unsigned long long tot) {
-        if (tot) atomicAdd((unsigned long long*)&b.whole_sums[(int64_t)cam * 9 + i], tot);
-      },
-      L.red);
-}
-
-// Segment ti of the context through the block's tables (8-bit samples:
-// staged in LDS; 16-bit: the Q16 pairs).  WTAB: weights from the caller's
-// table (true) or from their closed form (false); both give the same
-// integers.  With statistics, `first` clears the LDS histogram (the first
-// segment of its camera in this workgroup's run) and `last` adds it to the
-// whole-frame statistics (the camera's last segment in the run); 16-bit
-// samples, whose sums are kept in registers, and the packed histogram, whose
-// counters are bounded per segment, do both on every segment.
-template <int C, int BPS, bool WRITE, bool STATS, bool WTAB, class FP>
-__device__ void apply_tile(const Geo& g, const FP& fp, const Bufs& b, int ti, ApplyLds& L, bool first,
-                           bool last) {
-  const bool clear = first || BPS == 2 || kPack;
-  const bool flush = last || BPS == 2 || kPack;
-  constexpr int NW = C * BPS;    // dwords per 4-pixel group
-  constexpr int SPG = 4 * C;     // samples per group
-  const int tid = threadIdx.x;
-  const Tile t = uniform_tile(g.tiles[ti]);
-  const DevCam cam = uniform_cam(g.cams[t.cam]);
-  const int W = cam.width;
-  const int half = cam.half;
-  const int shift = cam.bit_depth - 8;
-  const uint32_t maxv = (1u << cam.bit_depth) - 1u;
-  const int pitch = (int)cam.pitch;
-
-  // Stage the tables of both sides of the segment's block; clear the histogram.
-  const int64_t u_left = unit_index(t.cam, 0, t.block, 0, g.n_blocks);
-  const int64_t u_right = unit_index(t.cam, 1, t.block, 0, g.n_blocks);
-  if (WRITE) {
-    if (BPS == 1) {
-      constexpr int DW = C * kNB / 4;   // dwords of one side's tables
-      for (int i = tid; i < 2 * DW; i += kThreads) {
-        const int s = i / DW;
-        const int rem = i - s * DW;
-        const uint32_t* src = reinterpret_cast<const uint32_t*>(b.lut8 + (s ? u_right : u_left) * kNB);
-        reinterpret_cast<uint32_t*>(L.lut + s * kCS * kNB)[rem] = src[rem];
-      }
-    } else if (tid < 4) {
-      L.q[tid] = b.q16[((tid >> 1) ? u_right : u_left) * 2 + (tid & 1)];
-    }
-  }
-  if (STATS && clear) {
-    for (int i = tid; i < kHistWords / kCS * C; i += kThreads) L.hist[i] = 0;
-  }
-  __syncthreads();
-
-  const __amdgpu_buffer_rsrc_t rin = frame_rsrc(fp.in[t.cam], cam);
-  __amdgpu_buffer_rsrc_t rout = rin;
-  if (WRITE) rout = frame_rsrc(fp.out[t.cam], cam);
-  const uint16_t* wrow = b.weights + (int64_t)t.cam * g.w_max;
-  const int ngroups = (W + 3) >> 2;
-  const int hrep = tid & (kRep - 1);
-  unsigned long long a1 = 0, a2 = 0;
-
-  for (int grp = tid; grp < ngroups; grp += kThreads) {
-    const int col0 = grp * 4;
-    const int npx = min(4, W - col0);
-    PixConst pc;
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      const int col = col0 + p;
-      const int side = col < half ? 0 : 1;
-      uint32_t w = 0;
-      if (WRITE && p < npx) w = WTAB ? (uint32_t)wrow[col] : blend_weight(W, col);
-      pc.wp[p] = (256u - w) | (w << 16);
-      pc.lb[p] = side * kCS * kNB;
-      if (BPS == 2 && WRITE) { pc.qa[p] = L.q[side * 2]; pc.qb[p] = L.q[side * 2 + 1]; }
-    }
-    const int cbyte = col0 * C * BPS;
-    const Tile& ts = t;
-
-    if (npx == 4) {
-      for (int row = ts.r0; row < ts.r1; row += kUnroll) {
-        uint32_t d[kUnroll][NW];
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u)
-          if (row + u < ts.r1) load_group<NW>(rin, (row + u) * pitch + cbyte, d[u]);
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-          if (row + u < ts.r1) {
-            uint32_t o[NW];
-#pragma unroll
-            for (int q = 0; q < NW; ++q) o[q] = 0;
-#pragma unroll
-            for (int i = 0; i < SPG; ++i) {
-              const int p = i / C;
-              const int c = i - p * C;
-              uint32_t x;
-              if (BPS == 1) x = (d[u][i >> 2] >> (8 * (i & 3))) & 0xffu;
-              else x = (d[u][i >> 1] >> (16 * (i & 1))) & 0xffffu;
-              const uint32_t y = one_sample<BPS, WRITE, STATS, false>(x, c, p, pc, L, hrep, shift, maxv, a1, a2);
-              if (WRITE) {
-                if (BPS == 1) o[i >> 2] |= y << (8 * (i & 3));
-                else o[i >> 1] |= y << (16 * (i & 1));
-              }
-            }
-            if (WRITE) store_group<NW>(rout, (row + u) * pitch + cbyte, o);
-          }
-        }
-      }
-    } else {
-      // Ragged end of the row: sample by sample, touching only the row's bytes.
-      for (int row = ts.r0; row < ts.r1; ++row) {
-        const int off = row * pitch + cbyte;
-#pragma unroll
-        for (int i = 0; i < SPG; ++i) {
-          const int p = i / C;
-          const int c = i - p * C;
-          if (p < npx) {
-            uint32_t x;
-            if (BPS == 1) x = __builtin_amdgcn_raw_buffer_load_b8(rin, off + i, 0, 0);
-            else x = __builtin_amdgcn_raw_buffer_load_b16(rin, off + 2 * i, 0, 0);
-            const uint32_t y = one_sample<BPS, WRITE, STATS, false>(x, c, p, pc, L, hrep, shift, maxv, a1, a2);
-            if (WRITE) {
-              if (BPS == 1) __builtin_amdgcn_raw_buffer_store_b8((uint8_t)y, rout, off + i, 0, 0);
-              else __builtin_amdgcn_raw_buffer_store_b16((uint16_t)y, rout, off + 2 * i, 0, 0);
-            }
-          }
-        }
-      }
-    }
-  }
-
-  if (STATS && flush) flush_whole<C, BPS>(g, b, t.cam, L, a1, a2);
+// An 8-bit map may be evaluated directly, bit for bit equal to its table, when
+// A fits a 24-bit multiply and A x + Bq + 2^15 stays inside int32 for x in [0,
+// 255].  |A| <= 2^22 (a gain of 64) and |Bq + 2^15| <= 2^30 give that, and hold
+// for every convex combination of maps that pass.
+__device__ inline bool small_map(int64_t A, int64_t Bq) {
+  const int64_t c = Bq + 32768;
+  return A <= (1 << 22) && A >= -(1 << 22) && c <= (1 << 30) && c >= -(1 << 30);
 }
 
 // Row-wise blend of adjacent blocks' maps (section 5's convex combinations of
@@ -335,12 +155,16 @@ __device__ void apply_tile(const Geo& g, const FP& fp, const Bufs& b, int ti, Ap
 // the last centre on), weight v of the second block = round_half_up(256
 // (2r - C_a) / (C_b - C_a)); each Q16 parameter of the row is
 // floor(((256 - v) P_a + v P_b + 128) / 256).
-__device__ inline int block_centre2(int j, int H, int nb) {
-  return (int)((int64_t)j * H / nb) + (int)((int64_t)(j + 1) * H / nb) - 1;
+// First row of block j, and the block that holds row r (products stay below
+// 2^26: at most 32768 rows and 1024 blocks).
+__device__ inline int block_row(int j, int H, int nb) { return (int)((uint32_t)j * (uint32_t)H / (uint32_t)nb); }
+__device__ inline int row_block(int r, int H, int nb) {
+  return (int)(((uint32_t)(r + 1) * (uint32_t)nb - 1u) / (uint32_t)H);
 }
+__device__ inline int block_centre2(int j, int H, int nb) { return block_row(j, H, nb) + block_row(j + 1, H, nb) - 1; }
 
 __device__ inline void vblend_row(int H, int nb, int r, int& a, int& b, int& v) {
-  const int j = (int)(((int64_t)(r + 1) * nb - 1) / H);
+  const int j = row_block(r, H, nb);
   const int lo = 2 * r < block_centre2(j, H, nb) ? j - 1 : j;
   if (lo < 0 || lo + 1 >= nb) {
     a = b = j;
@@ -357,438 +181,407 @@ __device__ inline int64_t blend_q16(int64_t pa, int64_t pb, int v) {
   return ((256 - v) * pa + v * pb + 128) >> 8;
 }
 
-// Apply (and statistics) of segment ti with the maps blended row by row.
-// Each row's blended Q16 pairs of both sides are computed once per row
-// (uniform over the workgroup) and every sample is evaluated from its side's
-// pair in 64-bit integers, 8-bit and 16-bit samples alike.  Same histogram
-// and flush as apply_tile.
-template <int C, int BPS, bool WRITE, bool STATS, bool WTAB, class FP>
-__device__ void apply_tile_vblend(const Geo& g, const FP& fp, const Bufs& b, int ti, ApplyLds& L,
-                                  bool first, bool last) {
-  const bool clear = first || BPS == 2 || kPack;
-  const bool flush = last || BPS == 2 || kPack;
-  constexpr int SPG = 4 * C;     // samples per group
-  const int tid = threadIdx.x;
-  const Tile t = uniform_tile(g.tiles[ti]);
-  const DevCam cam = uniform_cam(g.cams[t.cam]);
-  const int W = cam.width, H = cam.height, half = cam.half, nb = g.n_blocks;
-  const int shift = cam.bit_depth - 8;
-  const uint32_t maxv = (1u << cam.bit_depth) - 1u;
-  const int pitch = (int)cam.pitch;
-  if (STATS && clear) {
-    for (int i = tid; i < kHistWords / kCS * C; i += kThreads) L.hist[i] = 0;
+// Whether the maps of blocks [ja, jb] of camera k pass small_map.  Each wave
+// looks at all of them, so that every wave has the answer without a barrier.
+template <int C>
+__device__ inline bool maps_small(const Geo& g, const Bufs& b, int k, int ja, int jb) {
+  const int n = (jb - ja + 1) * 2 * C;
+  bool ok = true;
+  for (int i = threadIdx.x % kWave; i < n; i += kWave) {
+    const int c = i % C, s = (i / C) & 1, j = ja + i / (2 * C);
+    const int64_t u = unit_index(k, s, j, c, g.n_blocks);
+    ok = ok && small_map(b.q16[u * 2], b.q16[u * 2 + 1]);
   }
-  __syncthreads();
-  const __amdgpu_buffer_rsrc_t rin = frame_rsrc(fp.in[t.cam], cam);
-  __amdgpu_buffer_rsrc_t rout = rin;
-  if (WRITE) rout = frame_rsrc(fp.out[t.cam], cam);
-  const uint16_t* wrow = b.weights + (int64_t)t.cam * g.w_max;
-  const int hrep = tid & (kRep - 1);
-  unsigned long long a1 = 0, a2 = 0;
-  const int ngroups = (W + 3) >> 2;
-  for (int grp = tid; grp < ngroups; grp += kThreads) {
-    const int col0 = grp * 4, npx = min(4, W - col0);
-    uint32_t wp[4];
-    bool right[4];
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      const int col = col0 + p;
-      uint32_t w = 0;
-      if (WRITE && p < npx) w = WTAB ? (uint32_t)wrow[col] : blend_weight(W, col);
-      wp[p] = (256u - w) | (w << 16);
-      right[p] = col >= half;
-    }
-    for (int row = t.r0; row < t.r1; ++row) {
-      int ja, jb, v;
-      vblend_row(H, nb, row, ja, jb, v);
-      int64_t A[2][kCS], Bq[2][kCS];
-      if (WRITE) {
-#pragma unroll
-        for (int sd = 0; sd < 2; ++sd)
-#pragma unroll
-          for (int c = 0; c < C; ++c) {
-            const int64_t ua = unit_index(t.cam, sd, ja, c, nb), ub = unit_index(t.cam, sd, jb, c, nb);
-            A[sd][c] = blend_q16(uniform(b.q16[ua * 2]), uniform(b.q16[ub * 2]), v);
-            Bq[sd][c] = blend_q16(uniform(b.q16[ua * 2 + 1]), uniform(b.q16[ub * 2 + 1]), v);
-          }
-      }
-      const int off = row * pitch + col0 * C * BPS;
-#pragma unroll
-      for (int i = 0; i < SPG; ++i) {
-        const int p = i / C, c = i - p * C;
-        if (p < npx) {
-          const uint32_t x = BPS == 1 ? __builtin_amdgcn_raw_buffer_load_b8(rin, off + i, 0, 0)
-                                      : __builtin_amdgcn_raw_buffer_load_b16(rin, off + 2 * i, 0, 0);
-          if (STATS) {
-            uint32_t bin = x;
-            if (BPS == 2) { bin = x >> shift; bin = bin > 255u ? 255u : bin; }
-            __hip_atomic_fetch_add(&L.hist[hist_word(c, bin) * kRep + hrep], 1u << hist_shift(bin),
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (BPS == 2) { a1 += x; a2 += (unsigned long long)x * x; }
-          }
-          if (WRITE) {
-            const int sd = right[p] ? 1 : 0;
-            int64_t y = (A[sd][c] * (int64_t)x + Bq[sd][c] + 32768) >> 16;
-            y = y < 0 ? 0 : (y > (int64_t)maxv ? (int64_t)maxv : y);
-            const uint32_t xf = x | ((uint32_t)y << 16);
-            const uint32_t o = __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, xf),
-                                                      __builtin_bit_cast(u16x2, wp[p]), 128u, false) >> 8;
-            if (BPS == 1) __builtin_amdgcn_raw_buffer_store_b8((uint8_t)o, rout, off + i, 0, 0);
-            else __builtin_amdgcn_raw_buffer_store_b16((uint16_t)o, rout, off + 2 * i, 0, 0);
-          }
-        }
-      }
-    }
-  }
-  if (STATS && flush) flush_whole<C, BPS>(g, b, t.cam, L, a1, a2);
+  return __builtin_amdgcn_ballot_w64(!ok) == 0;
 }
 
-// Direct-map constants of this many blocks fit in the LDS table area.
-constexpr int kRunBlocks = (int)(sizeof(ApplyLds::lut) / (2 * kCS * 2 * sizeof(int32_t)));
-
-// Apply with statistics over segments [ti, te) of one 8-bit camera: their
-// rows are consecutive and every block among them has direct maps (at most
-// kRunBlocks blocks).  One row loop covers all the segments: the blocks'
-// constants are staged in LDS, and at a block's first row each thread
-// re-selects its pixels' constants (by side) from them, so a block boundary
-// costs no memory latency and no partly filled unroll step.  Same results as
-// apply_tile.
-template <int C, bool WTAB, class FP>
-__device__ void apply_run_direct(const Geo& g, const FP& fp, const Bufs& b, int ti, int te, ApplyLds& L,
-                                 bool first, bool last) {
-  constexpr int NW = C;          // dwords per 4-pixel group
-  const int tid = threadIdx.x;
-  const Tile t0 = uniform_tile(g.tiles[ti]);
-  const int R0 = t0.r0, R1 = uniform(g.tiles[te - 1].r1);
-  const int j0 = t0.block, j1 = uniform(g.tiles[te - 1].block);
-  const DevCam cam = uniform_cam(g.cams[t0.cam]);
-  const int W = cam.width, half = cam.half, H = cam.height, nb = g.n_blocks;
-  const int pitch = (int)cam.pitch;
-
-  // [block - j0][side][channel][a, c]
-  int32_t* cst = reinterpret_cast<int32_t*>(L.lut);
-  for (int i = tid; i < (j1 - j0 + 1) * 2 * kCS; i += kThreads) {
-    const int jj = i / (2 * kCS), sd = (i / kCS) & 1, c = i % kCS;
-    const int64_t u = unit_index(t0.cam, sd, j0 + jj, c, nb);
-    cst[i * 2] = (int32_t)b.q16[u * 2];
-    cst[i * 2 + 1] = (int32_t)(b.q16[u * 2 + 1] + 32768);
+// 3x3 maps: |A| <= 2^20 (a coefficient of 16) and |B + 2^15| <= 2^30 keep
+// A_r . x + B_r + 2^15 inside int32 for every x in [0, 255]^3.
+__device__ inline bool cross_small(const Geo& g, const int64_t* q3, int k, int ja, int jb) {
+  const int n = (jb - ja + 1) * 2 * kX3;
+  bool ok = true;
+  for (int i = threadIdx.x % kWave; i < n; i += kWave) {
+    const int e = i % kX3, s = (i / kX3) & 1, j = ja + i / (2 * kX3);
+    const int64_t v = q3[(((int64_t)k * 2 + s) * g.n_blocks + j) * kX3 + e];
+    ok = ok && (e < 9 ? v <= (1 << 20) && v >= -(1 << 20) : v + 32768 <= (1 << 30) && v + 32768 >= -(1 << 30));
   }
-  if (first || kPack)
-    for (int i = tid; i < kHistWords / kCS * C; i += kThreads) L.hist[i] = 0;
-  __syncthreads();
+  return __builtin_amdgcn_ballot_w64(!ok) == 0;
+}
 
-  const __amdgpu_buffer_rsrc_t rin = frame_rsrc(fp.in[t0.cam], cam);
-  const __amdgpu_buffer_rsrc_t rout = frame_rsrc(fp.out[t0.cam], cam);
-  const uint16_t* wrow = b.weights + (int64_t)t0.cam * g.w_max;
-  const int hrep = tid & (kRep - 1);
+// Stages the maps of a piece of the run: entry e is block j0 + e, or with VB
+// row p0 + e (its two blocks' maps blended).
+template <int C, int BPS, int KIND, bool VB>
+__device__ inline void stage_maps(const Geo& g, const Bufs& b, const int64_t* q3, const DevCam& cam, int k, int p0,
+                                  int j0, int n, ApplyLds& L) {
+  const int nb = g.n_blocks, H = cam.height, tid = threadIdx.x;
+  constexpr int kPer = KIND == kMapTable ? 2 * C * kNB / 4 : KIND >= kMapCross ? 2 * kX3 : 2 * C;
+  if (!VB && tid < n) L.end[tid] = block_row(j0 + tid + 1, H, nb);
+  for (int i = tid; i < n * kPer; i += kApplyThreads) {
+    const int e = i / kPer, rem = i - e * kPer;
+    if constexpr (KIND == kMapTable) {
+      constexpr int kSide = C * kNB / 4;
+      const int s = rem / kSide;
+      const uint32_t* src =
+          reinterpret_cast<const uint32_t*>(b.lut8 + unit_index(k, s, j0 + e, 0, nb) * kNB);
+      reinterpret_cast<uint32_t*>(L.map)[i] = src[rem - s * kSide];
+    } else if constexpr (KIND >= kMapCross) {
+      const int s = rem / kX3, q = rem - s * kX3;
+      const int64_t v = q3[(((int64_t)k * 2 + s) * nb + j0 + e) * kX3 + q];
+      if (KIND == kMapCross) reinterpret_cast<int32_t*>(L.map)[i] = (int32_t)(q < 9 ? v : v + 32768);
+      else reinterpret_cast<int64_t*>(L.map)[i] = v;
+    } else {
+      const int s = rem / C, c = rem - s * C;
+      int64_t A, B;
+      if (VB) {
+        int ja, jb, v;
+        vblend_row(H, nb, p0 + e, ja, jb, v);
+        const int64_t ua = unit_index(k, s, ja, c, nb), ub = unit_index(k, s, jb, c, nb);
+        A = blend_q16(b.q16[ua * 2], b.q16[ub * 2], v);
+        B = blend_q16(b.q16[ua * 2 + 1], b.q16[ub * 2 + 1], v);
+      } else {
+        const int64_t u = unit_index(k, s, j0 + e, c, nb);
+        A = b.q16[u * 2];
+        B = b.q16[u * 2 + 1];
+      }
+      if (KIND == kMapDirect) {
+        reinterpret_cast<int32_t*>(L.map)[2 * i] = (int32_t)A;
+        reinterpret_cast<int32_t*>(L.map)[2 * i + 1] = (int32_t)(B + 32768);
+      } else {
+        reinterpret_cast<int64_t*>(L.map)[2 * i] = A;
+        reinterpret_cast<int64_t*>(L.map)[2 * i + 1] = B;
+      }
+    }
+  }
+}
+
+// The maps of one side of one entry, in registers (the tables stay in LDS).
+template <int C, int KIND>
+struct SideMap {
+  static constexpr int kN = KIND >= kMapCross ? kX3 : 2 * C;
+  int32_t v[KIND == kMapDirect || KIND == kMapCross ? kN : 1];
+  int64_t w[KIND == kMapWide || KIND == kMapCrossWide ? kN : 1];
+  const uint8_t* t;
+
+  __device__ inline void read(const ApplyLds& L, int entry, int side) {
+    const int at = (entry * 2 + side) * (MapEntry<KIND, C>::kBytes / 2);
+    if constexpr (KIND == kMapDirect || KIND == kMapCross) {
+#pragma unroll
+      for (int i = 0; i < kN; ++i) v[i] = reinterpret_cast<const int32_t*>(L.map + at)[i];
+    } else if constexpr (KIND == kMapTable) {
+      t = L.map + at;
+    } else {
+#pragma unroll
+      for (int i = 0; i < kN; ++i) w[i] = reinterpret_cast<const int64_t*>(L.map + at)[i];
+    }
+  }
+
+  // x | f_c(x) << 16 for channel c of the pixel's samples xs.
+  __device__ inline uint32_t pair(const uint32_t (&xs)[C], int c, uint32_t maxv) const {
+    const uint32_t x = xs[c];
+    if constexpr (KIND == kMapDirect || KIND == kMapCross) {
+      // Staged coefficients fit 24 bits (small_map), so these are 24-bit
+      // multiplies.  clamp(v >> 16, 0, 255) << 16 == clamp(v, 0, 2^24 - 1) &
+      // 0xffff0000 for the arithmetic shift, so f lands in the high half.
+      auto m24 = [](int32_t a, uint32_t s) { return ((int32_t)((uint32_t)a << 8) >> 8) * (int32_t)s; };
+      int32_t y;
+      if constexpr (KIND == kMapDirect) {
+        y = m24(v[2 * c], x) + v[2 * c + 1];
+      } else {
+        y = m24(v[c * 3], xs[0]) + m24(v[c * 3 + 1], xs[C > 1 ? 1 : 0]) + m24(v[c * 3 + 2], xs[C > 2 ? 2 : 0]) + v[9 + c];
+      }
+      y = y < 0 ? 0 : (y > 0xffffff ? 0xffffff : y);
+      return ((uint32_t)y & 0xffff0000u) | x;
+    } else if constexpr (KIND == kMapTable) {
+      return x | ((uint32_t)t[c * kNB + x] << 16);
+    } else {
+      int64_t y;
+      if constexpr (KIND == kMapWide) {
+        y = (w[2 * c] * (int64_t)x + w[2 * c + 1] + 32768) >> 16;
+      } else {
+        y = (w[c * 3] * (int64_t)xs[0] + w[c * 3 + 1] * (int64_t)xs[C > 1 ? 1 : 0] +
+             w[c * 3 + 2] * (int64_t)xs[C > 2 ? 2 : 0] + w[9 + c] + 32768) >> 16;
+      }
+      y = y < 0 ? 0 : (y > (int64_t)maxv ? (int64_t)maxv : y);
+      return x | ((uint32_t)y << 16);
+    }
+  }
+};
+
+// Four raw dot products (see one_group) to one dword of 8-bit samples: byte 1
+// of each, in order, by two byte permutes (selector byte 0x0c gives zero).
+__device__ inline uint32_t pack_raw4(uint32_t r0, uint32_t r1, uint32_t r2, uint32_t r3) {
+  return __builtin_amdgcn_perm(r1, r0, 0x0c0c0501u) | __builtin_amdgcn_perm(r3, r2, 0x05010c0cu);
+}
+
+// 16-bit sample sums of a thread (S1, S2; 8-bit sums follow from the histogram).
+struct Sums16 {
+  unsigned long long s1, s2;
+};
+
+// One row of a 4-pixel group: histogram of its first npx pixels' samples
+// (STATS) and their corrected values (WRITE) with the maps m; wp[p] is pixel
+// p's weight pair (256 - w, w).
+template <int C, int BPS, bool WRITE, bool STATS, class Map>
+__device__ inline void one_group(const uint32_t (&d)[C * BPS], uint32_t (&o)[C * BPS], int npx, const Map& m,
+                                 const uint32_t (&wp)[4], ApplyLds& L, int hrep, int shift, uint32_t maxv,
+                                 Sums16& sums) {
+  uint32_t r[4 * C];
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    uint32_t xs[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const int i = p * C + c;
+      if (BPS == 1) xs[c] = (d[i >> 2] >> (8 * (i & 3))) & 0xffu;
+      else xs[c] = (d[i >> 1] >> (16 * (i & 1))) & 0xffffu;
+      if (STATS && p < npx) {
+        uint32_t bin = xs[c];
+        if (BPS == 2) {
+          bin >>= shift;
+          bin = bin > 255u ? 255u : bin;
+          sums.s1 += xs[c];
+          sums.s2 += (unsigned long long)xs[c] * xs[c];
+        }
+        __hip_atomic_fetch_add(&L.hist[(c * kNB + bin) * kRep + hrep], 1u, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    }
+    if (WRITE) {
+#pragma unroll
+      for (int c = 0; c < C; ++c)
+        // ((256 - w) x + w f + 128) >> 8 as one dot product of (x, f) with
+        // (256 - w, w): the sum stays below 2^16 for 8-bit samples, byte 1 is y.
+        r[p * C + c] = __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, m.pair(xs, c, maxv)),
+                                              __builtin_bit_cast(u16x2, wp[p]), 128u, false);
+    }
+  }
+  if (WRITE) {
+#pragma unroll
+    for (int q = 0; q < C * BPS; ++q) {
+      if (BPS == 1) o[q] = pack_raw4(r[4 * q], r[4 * q + 1], r[4 * q + 2], r[4 * q + 3]);
+      else o[q] = ((r[2 * q] >> 8) & 0xffffu) | ((r[2 * q + 1] >> 8) << 16);
+    }
+  }
+}
+
+// Rows [p0, p1) of the run, whose maps are staged.
+template <int C, int BPS, int KIND, bool WRITE, bool STATS, bool VB>
+__device__ inline void piece_rows(const Geo& g, const Bufs& b, const DevCam& cam, int k, __amdgpu_buffer_rsrc_t rin,
+                                  __amdgpu_buffer_rsrc_t rout, int p0, int p1, ApplyLds& L, Sums16& sums) {
+  constexpr int NW = C * BPS;
+  const int tid = threadIdx.x;
+  const int cols = cam.ap_cols, step = cam.ap_lanes;
+  const int ln = tid / cols, gc = tid - ln * cols;
+  if (ln >= step || p0 + ln >= p1) return;      // rows below are in [p0, p1), so inside a staged entry
+  const int W = cam.width, half = cam.half, pitch = (int)cam.pitch;
   const int ngroups = (W + 3) >> 2;
-  unsigned long long a1 = 0, a2 = 0;
-
-  for (int grp = tid; grp < ngroups; grp += kThreads) {
-    const int col0 = grp * 4;
-    const int npx = min(4, W - col0);
-    PixConst pc;
+  const int hrep = tid & (kRep - 1);
+  const int shift = cam.bit_depth - 8;
+  const uint32_t maxv = (1u << cam.bit_depth) - 1u;
+  const uint16_t* wrow = b.weights + (int64_t)k * g.w_max;
+  for (int grp = gc; grp < ngroups; grp += cols) {
+    const int col0 = grp * 4, npx = min(4, W - col0);
+    const int cbyte = col0 * NW;
+    uint32_t wp[4];
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
-      const uint32_t w = p < npx ? (WTAB ? (uint32_t)wrow[col0 + p] : blend_weight(W, col0 + p)) : 0u;
-      pc.wp[p] = (256u - w) | (w << 16);
+      const uint32_t w = WRITE && p < npx ? (uint32_t)wrow[col0 + p] : 0u;
+      wp[p] = (256u - w) | (w << 16);
     }
-    int jb = j0;
-    int rb = min(R1, (int)((int64_t)(jb + 1) * H / nb));   // first row of the next block
-    auto select = [&]() {
-      int32_t A[2][kCS], Cc[2][kCS];
-#pragma unroll
-      for (int sd = 0; sd < 2; ++sd)
-#pragma unroll
-        for (int c = 0; c < kCS; ++c) {
-          const int i = (((jb - j0) * 2 + sd) * kCS + c) * 2;
-          A[sd][c] = uniform(cst[i]);
-          Cc[sd][c] = uniform(cst[i + 1]);
-        }
-#pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        const bool right = col0 + p >= half;
-#pragma unroll
-        for (int c = 0; c < kCS; ++c) {
-          pc.da[p][c] = right ? A[1][c] : A[0][c];
-          pc.dc[p][c] = right ? Cc[1][c] : Cc[0][c];
-        }
+    int e = 0;     // staged entry of the row
+    auto entry_of = [&](int row) {
+      if (VB) {
+        e = row - p0;
+        return true;
       }
+      if (row < L.end[e]) return false;
+      do ++e; while (row >= L.end[e]);     // blocks without rows are stepped over
+      return true;
     };
-    select();
-    // Row r starts block jb + 1 when r == rb.  Blocks hold no rows when
-    // H < NB, so several block starts can fall on one row: step over every
-    // empty block to the one that holds r (uniform over the wave).
-    auto next_block = [&](int r) {
-      if (r != rb) return;
-      while (r == rb && jb < j1) {
-        ++jb;
-        rb = min(R1, (int)((int64_t)(jb + 1) * H / nb));
+    const int side = col0 >= half ? 1 : 0;
+    if (npx == 4 && side == (col0 + 3 >= half ? 1 : 0)) {
+      SideMap<C, KIND> m;
+      if (WRITE && !VB) {
+        (void)entry_of(p0 + ln);
+        m.read(L, e, side);
       }
-      select();
-    };
-    const int cbyte = col0 * C;
-
-    if (npx == 4) {
-      for (int row = R0; row < R1; row += kUnroll) {
+      for (int row = p0 + ln; row < p1; row += kUnroll * step) {
         uint32_t d[kUnroll][NW];
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u)
-          if (row + u < R1) load_group<NW>(rin, (row + u) * pitch + cbyte, d[u]);
+          if (row + u * step < p1) load_group<NW>(rin, (row + u * step) * pitch + cbyte, d[u]);
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
-          if (row + u < R1) {
-            next_block(row + u);
-            uint32_t r[4 * C], o[NW];
-#pragma unroll
-            for (int i = 0; i < 4 * C; ++i) {
-              const int p = i / C, c = i - (i / C) * C;
-              const uint32_t x = (d[u][i >> 2] >> (8 * (i & 3))) & 0xffu;
-              r[i] = one_sample<1, true, true, true, true>(x, c, p, pc, L, hrep, 0, 255u, a1, a2);
-            }
-#pragma unroll
-            for (int q = 0; q < NW; ++q) o[q] = pack_raw4(r[4 * q], r[4 * q + 1], r[4 * q + 2], r[4 * q + 3]);
-            store_group<NW>(rout, (row + u) * pitch + cbyte, o);
+          if (row + u * step < p1) {
+            if (WRITE && entry_of(row + u * step)) m.read(L, e, side);
+            uint32_t o[NW];
+            one_group<C, BPS, WRITE, STATS>(d[u], o, 4, m, wp, L, hrep, shift, maxv, sums);
+            if (WRITE) store_group<NW>(rout, (row + u * step) * pitch + cbyte, o);
           }
         }
       }
     } else {
-      // Ragged end of the row: sample by sample, touching only the row's bytes.
-      for (int row = R0; row < R1; ++row) {
-        next_block(row);
-        const int off = row * pitch + cbyte;
+      // The group across the image centre or at the ragged end of the row:
+      // its pixels' maps are read per row and side.
+      constexpr int kU = 4;
+      for (int row = p0 + ln; row < p1; row += kU * step) {
+        uint32_t d[kU][NW];
 #pragma unroll
-        for (int i = 0; i < 4 * C; ++i) {
-          const int p = i / C, c = i - (i / C) * C;
-          if (p < npx) {
-            const uint32_t x = __builtin_amdgcn_raw_buffer_load_b8(rin, off + i, 0, 0);
-            const uint32_t y = one_sample<1, true, true, true>(x, c, p, pc, L, hrep, 0, 255u, a1, a2);
-            __builtin_amdgcn_raw_buffer_store_b8((uint8_t)y, rout, off + i, 0, 0);
-          }
-        }
-      }
-    }
-  }
-  if (last || kPack) flush_whole<C, 1>(g, b, t0.cam, L, 0ull, 0ull);
-}
-
-// Whether every row map blended from blocks [js, je] of camera k can be
-// evaluated directly (uniform): a blended pair lies between its two blocks'
-// pairs (floor of a convex combination plus one half), so |A| < 2^23 and
-// 255 max|A| + max|Bq + 2^15| < 2^31 over the blocks bound every row's
-// A x + Bq + 2^15 inside int32.
-__device__ inline bool vblend_direct_ok(const Geo& g, const Bufs& b, int k, int js, int je) {
-  int64_t ma = 0, mc = 0;
-  for (int j = js; j <= je; ++j)
+        for (int u = 0; u < kU; ++u)
+          if (row + u * step < p1) load_part<NW>(rin, (row + u * step) * pitch + cbyte, npx * NW, d[u]);
+#pragma unroll 1
+        for (int u = 0; u < kU; ++u) {
+          if (row + u * step < p1) {
+            uint32_t du[NW], o[NW];
 #pragma unroll
-    for (int sd = 0; sd < 2; ++sd)
-#pragma unroll
-      for (int c = 0; c < kCS; ++c) {
-        const int64_t u = unit_index(k, sd, j, c, g.n_blocks);
-        const int64_t A = uniform(b.q16[u * 2]), C = uniform(b.q16[u * 2 + 1]) + 32768;
-        ma = max(ma, A < 0 ? -A : A);
-        mc = max(mc, C < 0 ? -C : C);
-      }
-  return ma < (1 << 23) && 255 * ma + mc <= (int64_t)INT32_MAX;
-}
-
-// Rows whose blended direct constants fit the LDS table area.
-constexpr int kVblendRows = (int)(sizeof(ApplyLds::lut) / (2 * kCS * 2 * sizeof(int32_t)));
-
-// Apply of segments [ti, te) of one 8-bit camera with the maps blended row
-// by row (apply_tile_vblend's results), kVblendRows rows at a time: one
-// thread per row blends the row's two blocks' Q16 pairs of both sides into
-// direct constants in LDS, then every thread takes its pixels' constants of
-// each row from there and the samples follow the direct path of
-// apply_run_direct.
-template <int C, bool STATS, bool WTAB, class FP>
-__device__ void apply_run_vblend(const Geo& g, const FP& fp, const Bufs& b, int ti, int te, ApplyLds& L,
-                                 bool first, bool last) {
-  constexpr int NW = C;
-  const int tid = threadIdx.x;
-  const Tile t0 = uniform_tile(g.tiles[ti]);
-  const int R0 = t0.r0, R1 = uniform(g.tiles[te - 1].r1);
-  const DevCam cam = uniform_cam(g.cams[t0.cam]);
-  const int W = cam.width, half = cam.half, H = cam.height, nb = g.n_blocks;
-  const int pitch = (int)cam.pitch;
-  int32_t* rc = reinterpret_cast<int32_t*>(L.lut);   // [row - chunk start][side][channel][A, Bq + 2^15]
-  if (STATS && (first || kPack))
-    for (int i = tid; i < kHistWords / kCS * C; i += kThreads) L.hist[i] = 0;
-  const __amdgpu_buffer_rsrc_t rin = frame_rsrc(fp.in[t0.cam], cam);
-  const __amdgpu_buffer_rsrc_t rout = frame_rsrc(fp.out[t0.cam], cam);
-  const uint16_t* wrow = b.weights + (int64_t)t0.cam * g.w_max;
-  const int hrep = tid & (kRep - 1);
-  const int ngroups = (W + 3) >> 2;
-  unsigned long long a1 = 0, a2 = 0;
-
-  for (int c0 = R0; c0 < R1; c0 += kVblendRows) {
-    const int c1 = min(c0 + kVblendRows, R1);
-    __syncthreads();   // the previous chunk's rows are done with the table
-    if (tid < c1 - c0) {
-      int ja, jb, v;
-      vblend_row(H, nb, c0 + tid, ja, jb, v);
-#pragma unroll
-      for (int sd = 0; sd < 2; ++sd)
-#pragma unroll
-        for (int c = 0; c < kCS; ++c) {
-          const int64_t ua = unit_index(t0.cam, sd, ja, c, nb), ub = unit_index(t0.cam, sd, jb, c, nb);
-          const int i = ((tid * 2 + sd) * kCS + c) * 2;
-          rc[i] = (int32_t)blend_q16(b.q16[ua * 2], b.q16[ub * 2], v);
-          rc[i + 1] = (int32_t)(blend_q16(b.q16[ua * 2 + 1], b.q16[ub * 2 + 1], v) + 32768);
-        }
-    }
-    __syncthreads();
-    for (int grp = tid; grp < ngroups; grp += kThreads) {
-      const int col0 = grp * 4;
-      const int npx = min(4, W - col0);
-      PixConst pc;
-#pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        const uint32_t w = p < npx ? (WTAB ? (uint32_t)wrow[col0 + p] : blend_weight(W, col0 + p)) : 0u;
-        pc.wp[p] = (256u - w) | (w << 16);
-      }
-      // A group on one side of the centre takes one side's constants (three
-      // 8-byte LDS reads per row); only the group across the centre, if
-      // any, selects per pixel.
-      const bool one_side = (col0 >= half) == (col0 + 3 >= half);
-      const int side0 = col0 >= half ? kCS * 2 : 0;
-      auto select_row = [&](int r) {
-        const int base = (r - c0) * 2 * kCS * 2;
-        if (one_side) {
-          const int2* q = reinterpret_cast<const int2*>(rc + base + side0);
-#pragma unroll
-          for (int c = 0; c < kCS; ++c) {
-            const int2 v = q[c];
-#pragma unroll
-            for (int p = 0; p < 4; ++p) {
-              pc.da[p][c] = v.x;
-              pc.dc[p][c] = v.y;
+            for (int q = 0; q < NW; ++q) du[q] = u == 0 ? d[0][q] : u == 1 ? d[1][q] : u == 2 ? d[2][q] : d[3][q];
+            SideMap<C, KIND> m;
+            if (WRITE) {
+              (void)entry_of(row + u * step);
+              m.read(L, e, side);
             }
-          }
-          return;
-        }
+            one_group<C, BPS, WRITE, STATS>(du, o, npx, m, wp, L, hrep, shift, maxv, sums);
+            if (WRITE && col0 < half && col0 + 3 >= half) {
+              // The pixels from half on, again with the right side's maps.
+              uint32_t q[NW];
+              m.read(L, e, 1);
+              one_group<C, BPS, WRITE, false>(du, q, npx, m, wp, L, hrep, shift, maxv, sums);
+              const int keep = (half - col0) * NW;      // bytes of the left side's pixels
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-          const int sb = base + (col0 + p >= half ? kCS * 2 : 0);
-#pragma unroll
-          for (int c = 0; c < kCS; ++c) {
-            pc.da[p][c] = rc[sb + c * 2];
-            pc.dc[p][c] = rc[sb + c * 2 + 1];
-          }
-        }
-      };
-      const int cbyte = col0 * C;
-      if (npx == 4) {
-        for (int row = c0; row < c1; row += kUnroll) {
-          uint32_t d[kUnroll][NW];
-#pragma unroll
-          for (int u = 0; u < kUnroll; ++u)
-            if (row + u < c1) load_group<NW>(rin, (row + u) * pitch + cbyte, d[u]);
-#pragma unroll
-          for (int u = 0; u < kUnroll; ++u) {
-            if (row + u < c1) {
-              select_row(row + u);
-              uint32_t r[4 * C], o[NW];
-#pragma unroll
-              for (int i = 0; i < 4 * C; ++i) {
-                const int p = i / C, c = i - (i / C) * C;
-                const uint32_t x = (d[u][i >> 2] >> (8 * (i & 3))) & 0xffu;
-                r[i] = one_sample<1, true, STATS, true, true>(x, c, p, pc, L, hrep, 0, 255u, a1, a2);
+              for (int i = 0; i < NW; ++i) {
+                const int n = min(max(keep - 4 * i, 0), 4);
+                const uint32_t mask = n == 4 ? ~0u : (1u << (8 * n)) - 1u;
+                o[i] = (o[i] & mask) | (q[i] & ~mask);
               }
-#pragma unroll
-              for (int q = 0; q < NW; ++q) o[q] = pack_raw4(r[4 * q], r[4 * q + 1], r[4 * q + 2], r[4 * q + 3]);
-              store_group<NW>(rout, (row + u) * pitch + cbyte, o);
             }
+            if (WRITE) store_part<NW>(rout, (row + u * step) * pitch + cbyte, npx * NW, o);
           }
         }
+      }
+    }
+  }
+}
+
+// Adds the run's LDS histogram of camera k (replicas summed) and its (n, S1,
+// S2) - linear in the histogram for 8-bit samples, the threads' sums for
+// 16-bit ones - to the camera's whole-frame statistics.
+template <int C, int BPS>
+__device__ inline void flush_whole(const Bufs& b, int k, ApplyLds& L, const Sums16& sums) {
+  const int tid = threadIdx.x, lane = tid % kWave;
+  auto add = [&](int i, unsigned long long s) {
+    if (lane == 0)
+      __hip_atomic_fetch_add(&L.sums[i], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  };
+  __syncthreads();
+  uint32_t* gh = b.whole_hist + (int64_t)k * kCS * kNB;
+  for (int i = tid; i < C * kNB; i += kApplyThreads) {    // whole waves, one channel each
+    const u32x4* h4 = reinterpret_cast<const u32x4*>(&L.hist[i * kRep]);
+    uint32_t h = 0;
+#pragma unroll
+    for (int q = 0; q < kRep / 4; ++q) {
+      const u32x4 v = h4[q];
+      h += v.x + v.y + v.z + v.w;
+    }
+    if (h) atomicAdd(&gh[i], h);
+    const int c = i / kNB;
+    const unsigned long long x = (unsigned long long)(i % kNB);
+    add(c * 3, wave_sum_u64(h));
+    if (BPS == 1) {
+      add(c * 3 + 1, wave_sum_u64(h * x));
+      add(c * 3 + 2, wave_sum_u64(h * x * x));
+    }
+  }
+  if (BPS == 2) {
+    add(1, wave_sum_u64(sums.s1));
+    add(2, wave_sum_u64(sums.s2));
+  }
+  __syncthreads();
+  if (tid < 3 * C && L.sums[tid]) atomicAdd((unsigned long long*)&b.whole_sums[(int64_t)k * 9 + tid], L.sums[tid]);
+}
+
+// Rows [R0, R1) of camera k, of C channels of BPS bytes.  CROSS: the 3x3 maps
+// q3 in place of the affine ones.
+template <int C, int BPS, bool WRITE, bool STATS, bool VB, bool CROSS, class FP>
+__device__ __attribute__((always_inline)) inline void apply_rows(const Geo& g, const FP& fp, const Bufs& b,
+                                                                 const int64_t* q3, const DevCam& cam, int k, int R0,
+                                                                 int R1, ApplyLds& L) {
+  const int tid = threadIdx.x, H = cam.height, nb = g.n_blocks;
+  if (STATS) {
+    const u32x4 zero = {0, 0, 0, 0};
+    for (int i = tid; i < C * kNB * kRep / 4; i += kApplyThreads) reinterpret_cast<u32x4*>(L.hist)[i] = zero;
+    if (tid < 9) L.sums[tid] = 0;
+  }
+  const __amdgpu_buffer_rsrc_t rin = frame_rsrc(fp.in[k], cam);
+  __amdgpu_buffer_rsrc_t rout = rin;
+  if (WRITE) rout = frame_rsrc(fp.out[k], cam);
+  Sums16 sums = {0, 0};
+  // The run in pieces whose maps fit the staging area.
+  auto pieces = [&](auto kind, int p0, int pe) {
+    constexpr int KIND = decltype(kind)::value;
+    constexpr int kCap = MapEntry<KIND, C>::kCap;
+    while (p0 < pe) {
+      const int j0 = row_block(p0, H, nb);
+      int p1 = pe, n;
+      if (VB) {
+        p1 = min(pe, p0 + kCap);
+        n = p1 - p0;
       } else {
-        // Ragged end of the row: sample by sample, touching only the row's bytes.
-        for (int row = c0; row < c1; ++row) {
-          select_row(row);
-          const int off = row * pitch + cbyte;
-#pragma unroll
-          for (int i = 0; i < 4 * C; ++i) {
-            const int p = i / C, c = i - (i / C) * C;
-            if (p < npx) {
-              const uint32_t x = __builtin_amdgcn_raw_buffer_load_b8(rin, off + i, 0, 0);
-              const uint32_t y = one_sample<1, true, STATS, true>(x, c, p, pc, L, hrep, 0, 255u, a1, a2);
-              __builtin_amdgcn_raw_buffer_store_b8((uint8_t)y, rout, off + i, 0, 0);
-            }
-          }
-        }
+        n = min(kCap, row_block(pe - 1, H, nb) - j0 + 1);
+        p1 = min(pe, block_row(j0 + n, H, nb));
       }
+      if (p0 != R0) __syncthreads();    // the previous piece's rows are done with the maps
+      if (WRITE) stage_maps<C, BPS, KIND, VB>(g, b, q3, cam, k, p0, j0, n, L);
+      __syncthreads();
+      piece_rows<C, BPS, KIND, WRITE, STATS, VB>(g, b, cam, k, rin, rout, p0, p1, L, sums);
+      p0 = p1;
     }
+  };
+  if constexpr (!WRITE) {
+    pieces(std::integral_constant<int, kMapDirect>{}, R0, R1);
+  } else if constexpr (CROSS) {
+    if (cross_small(g, q3, k, row_block(R0, H, nb), row_block(R1 - 1, H, nb)))
+      pieces(std::integral_constant<int, kMapCross>{}, R0, R1);
+    else
+      pieces(std::integral_constant<int, kMapCrossWide>{}, R0, R1);
+  } else if constexpr (BPS == 2) {
+    pieces(std::integral_constant<int, kMapWide>{}, R0, R1);
+  } else if constexpr (VB) {
+    if (maps_small<C>(g, b, k, max(0, row_block(R0, H, nb) - 1), min(nb - 1, row_block(R1 - 1, H, nb) + 1)))
+      pieces(std::integral_constant<int, kMapDirect>{}, R0, R1);
+    else
+      pieces(std::integral_constant<int, kMapWide>{}, R0, R1);
+  } else if constexpr (STATS) {
+    if (maps_small<C>(g, b, k, row_block(R0, H, nb), row_block(R1 - 1, H, nb)))
+      pieces(std::integral_constant<int, kMapDirect>{}, R0, R1);
+    else
+      pieces(std::integral_constant<int, kMapTable>{}, R0, R1);
+  } else {
+    pieces(std::integral_constant<int, kMapTable>{}, R0, R1);
   }
-  if (STATS && (last || kPack)) flush_whole<C, 1>(g, b, t0.cam, L, 0ull, 0ull);
+  if (STATS) flush_whole<C, BPS>(b, k, L, sums);
 }
 
-// Whether the six 8-bit maps of segment ti can be evaluated directly (uniform).
-__device__ inline bool tile_direct(const Geo& g, const Bufs& b, int ti) {
-  const Tile t = uniform_tile(g.tiles[ti]);
-  bool ok = true;
-#pragma unroll
-  for (int sd = 0; sd < 2; ++sd)
-#pragma unroll
-    for (int c = 0; c < kCS; ++c) {
-      const int64_t u = unit_index(t.cam, sd, t.block, c, g.n_blocks);
-      ok = ok && direct_ok(uniform(b.q16[u * 2]), uniform(b.q16[u * 2 + 1]));
+// Workgroup w's run: its rows of every camera it takes.
+template <bool WRITE, bool STATS, bool VB, bool CROSS, class FP>
+__device__ __attribute__((always_inline)) inline void apply_run(const Geo& g, const FP& fp, const Bufs& b,
+                                                                const int64_t* q3, int w, ApplyLds& L) {
+  const WgRun run = uniform_run(g, w);
+  for (int k = run.cam0; k <= run.cam1; ++k) {
+    if (!cam_active(g, k)) continue;              // uniform over the workgroup
+    const DevCam cam = uniform_cam(g, k);
+    const int r0 = k == run.cam0 ? run.row0 : 0, r1 = k == run.cam1 ? run.row1 : cam.height;
+    if (r0 >= r1) continue;
+    if constexpr (CROSS) {
+      apply_rows<3, 1, WRITE, STATS, VB, true>(g, fp, b, q3, cam, k, r0, r1, L);
+    } else if (cam.bps == 2) {
+      apply_rows<1, 2, WRITE, STATS, VB, false>(g, fp, b, q3, cam, k, r0, r1, L);
+    } else if (cam.channels == 3) {
+      apply_rows<3, 1, WRITE, STATS, VB, false>(g, fp, b, q3, cam, k, r0, r1, L);
+    } else {
+      apply_rows<1, 1, WRITE, STATS, VB, false>(g, fp, b, q3, cam, k, r0, r1, L);
     }
-  return ok;
-}
-
-// The segments from ti on, up to se, that one call takes: with the direct
-// maps (8-bit samples, apply with statistics, every segment's maps direct),
-// the camera's consecutive segments (apply_run_direct); otherwise one
-// (apply_tile).  Returns the end of the segments taken; `last` is set when
-// they end the camera's run in this workgroup.
-template <bool WRITE, bool STATS, bool WTAB, bool VBLEND = false, class FP = FramePtrs>
-__device__ inline int apply_tile_dispatch(const Geo& g, const FP& fp, const Bufs& b, int ti, int se,
-                                          ApplyLds& L, bool first) {
-  const int k = uniform(g.tiles[ti].cam);
-  const DevCam cam = uniform_cam(g.cams[k]);
-  int te = ti + 1;
-  if constexpr (VBLEND) {
-    const int j0 = uniform(g.tiles[ti].block);
-    if (cam.bps == 1 && WRITE && RC_APPLY_DIRECT &&
-        vblend_direct_ok(g, b, k, j0 > 0 ? j0 - 1 : 0, min(j0 + 1, g.n_blocks - 1))) {
-      // A camera's consecutive segments whose blocks and neighbours fit the
-      // staging area and evaluate directly.
-      const int cap = max_tile_rows(cam.width), r0 = uniform(g.tiles[ti].r0);
-      while (te < se && uniform(g.tiles[te].cam) == k && uniform(g.tiles[te].r1) - r0 <= cap) {
-        const int jt = uniform(g.tiles[te].block);
-        if (!vblend_direct_ok(g, b, k, jt, min(jt + 1, g.n_blocks - 1))) break;
-        ++te;
-      }
-      const bool lastr = te == se || uniform(g.tiles[te].cam) != k;
-      if (cam.channels == 3) apply_run_vblend<3, STATS, WTAB>(g, fp, b, ti, te, L, first, lastr);
-      else apply_run_vblend<1, STATS, WTAB>(g, fp, b, ti, te, L, first, lastr);
-      return te;
-    }
-    const bool lastv = te == se || uniform(g.tiles[te].cam) != k;
-    if (cam.bps == 2) apply_tile_vblend<1, 2, WRITE, STATS, WTAB>(g, fp, b, ti, L, first, lastv);
-    else if (cam.channels == 3) apply_tile_vblend<3, 1, WRITE, STATS, WTAB>(g, fp, b, ti, L, first, lastv);
-    else apply_tile_vblend<1, 1, WRITE, STATS, WTAB>(g, fp, b, ti, L, first, lastv);
-    return te;
+    if (k < run.cam1) __syncthreads();
   }
-  const bool direct = cam.bps == 1 && WRITE && STATS && RC_APPLY_DIRECT && tile_direct(g, b, ti);
-  const int j0 = uniform(g.tiles[ti].block);
-  // Packed counters bound the rows between flushes.
-  const int cap = max_tile_rows(cam.width), r0 = uniform(g.tiles[ti].r0);
-  if (direct)
-    while (te < se && uniform(g.tiles[te].cam) == k && uniform(g.tiles[te].block) - j0 < kRunBlocks &&
-           uniform(g.tiles[te].r1) - r0 <= cap && tile_direct(g, b, te))
-      ++te;
-  const bool last = te == se || uniform(g.tiles[te].cam) != k;
-  if (cam.bps == 2) apply_tile<1, 2, WRITE, STATS, WTAB>(g, fp, b, ti, L, first, last);
-  else if (direct) {
-    // Measured on MI355X: faster than the LDS tables when the pass also
-    // builds the histogram (the LDS is then busy with its atomics), slower
-    // for the apply alone.
-    if (cam.channels == 3) apply_run_direct<3, WTAB>(g, fp, b, ti, te, L, first, last);
-    else apply_run_direct<1, WTAB>(g, fp, b, ti, te, L, first, last);
-  } else if (cam.channels == 3) apply_tile<3, 1, WRITE, STATS, WTAB>(g, fp, b, ti, L, first, last);
-  else apply_tile<1, 1, WRITE, STATS, WTAB>(g, fp, b, ti, L, first, last);
-  return te;
 }
 
 }  // namespace rc

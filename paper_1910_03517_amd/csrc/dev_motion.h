@@ -72,7 +72,7 @@ __device__ __attribute__((always_inline)) void band_unit_motion(const Geo& g, co
                                                                 MotionLds& L, uint64_t* sums_out,
                                                                 uint64_t* kept_out, int tid) {
   constexpr int ND = C * BPS;                 // dwords of a 4-pixel group
-  const DevCam cam = uniform_cam(g.cams[k]);
+  const DevCam cam = uniform_cam(g, k);
   for (int i = tid; i < kCS * kNB; i += kThreads) L.hist[i] = 0;
   __syncthreads();
 

@@ -24,7 +24,7 @@ constexpr int kBandBarriers = 4;
 template <int C, int BPS>
 __device__ __attribute__((always_inline)) void band_unit(const Geo& g, const FramePtrs& fp, const Bufs& b, int k,
                                                          int s, int j, StatsLds& L, uint64_t* sums_out, int tid) {
-  const DevCam cam = uniform_cam(g.cams[k]);
+  const DevCam cam = uniform_cam(g, k);
   auto clear = [&]() {
     for (int i = tid; i < kCS * kNB; i += kThreads) L.hist[i] = 0;
     __syncthreads();

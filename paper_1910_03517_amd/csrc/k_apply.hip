@@ -7,38 +7,24 @@
 
 namespace rc {
 
-// Workgroup w takes its run of segments (one tile, or a contiguous share of
-// all rows balanced by bytes); the histogram of a camera stays in LDS across
-// the run's segments of that camera and is added to the whole-frame
-// statistics once, after its last one.  No workgroup waits for another.
 #ifndef RC_APPLY_WAVES
-#define RC_APPLY_WAVES 1
+#define RC_APPLY_WAVES 4
 #endif
-// VBLEND: the maps of adjacent blocks blended row by row (a kernel of its own,
-// so that its registers do not weigh on the plain pass).
+// Workgroup w takes its run of rows (apply_run); no workgroup waits for
+// another.  VBLEND: the maps of adjacent blocks blended row by row (a kernel
+// of its own, so that its registers do not weigh on the plain pass).
 template <bool WRITE, bool STATS, bool VBLEND>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(RC_APPLY_WAVES)))
+__global__ __launch_bounds__(kApplyThreads) __attribute__((amdgpu_waves_per_eu(RC_APPLY_WAVES)))
 void k_apply(Geo g, FramePtrs fp, Bufs b) {
   __shared__ ApplyLds L;
-  const int s0 = uniform(g.wg_seg[blockIdx.x]), s1 = uniform(g.wg_seg[blockIdx.x + 1]);
-  int prev = -1;
-  for (int s = s0; s < s1;) {
-    const int cam = uniform(g.tiles[s].cam);
-    if (!cam_active(g, cam)) {   // uniform over the workgroup
-      ++s;
-      continue;
-    }
-    s = apply_tile_dispatch<WRITE, STATS, true, VBLEND>(g, fp, b, s, s1, L, cam != prev);
-    __syncthreads();
-    prev = cam;
-  }
+  apply_run<WRITE, STATS, VBLEND, false>(g, fp, b, nullptr, (int)blockIdx.x, L);
 }
 
 // Apply with statistics of several frame-sets of the rig (see SetPtrs): the
-// same runs of segments as k_apply, once per set, set-major, so that one
-// launch has no drain between the frame-sets it holds.
+// same runs as k_apply, once per set, set-major, so that one launch has no
+// drain between the frame-sets it holds.
 template <bool VBLEND>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(RC_APPLY_WAVES)))
+__global__ __launch_bounds__(kApplyThreads) __attribute__((amdgpu_waves_per_eu(RC_APPLY_WAVES)))
 void k_apply_sets(Geo g, SetPtrs sp) {
   __shared__ ApplyLds L;
   const int f = (int)blockIdx.x / g.n_wg, w = (int)blockIdx.x - f * g.n_wg;
@@ -48,26 +34,14 @@ void k_apply_sets(Geo g, SetPtrs sp) {
   b.lut8 = sp.b[f].lut8;
   b.q16 = sp.b[f].q16;
   b.weights = sp.b[f].weights;
-  const SetFrames& fp = sp.f[f];
-  const int s0 = uniform(g.wg_seg[w]), s1 = uniform(g.wg_seg[w + 1]);
-  int prev = -1;
-  for (int s = s0; s < s1;) {
-    const int cam = uniform(g.tiles[s].cam);
-    if (!cam_active(g, cam)) {
-      ++s;
-      continue;
-    }
-    s = apply_tile_dispatch<true, true, true, VBLEND>(g, fp, b, s, s1, L, cam != prev);
-    __syncthreads();
-    prev = cam;
-  }
+  apply_run<true, true, VBLEND, false>(g, sp.f[f], b, nullptr, w, L);
 }
 
 // start / stop (may be NULL): events that take the dispatch's own start and
 // end times (no marker packets around it).
 hipError_t launch_apply(const Geo& g, const FramePtrs& fp, const Bufs& b, bool write, bool stats, hipStream_t st,
                         hipEvent_t start, hipEvent_t stop) {
-  const dim3 grid(g.n_wg), block(kThreads);
+  const dim3 grid(g.n_wg), block(kApplyThreads);
   if (g.vblend && write && stats)
     hipExtLaunchKernelGGL((k_apply<true, true, true>), grid, block, 0, st, start, stop, 0u, g, fp, b);
   else if (g.vblend && write)
@@ -93,7 +67,7 @@ const void* apply_kernel(const Geo& g, bool write, bool stats) {
 
 hipError_t launch_apply_sets(const Geo& g, const SetPtrs& sp, hipStream_t st, hipEvent_t start, hipEvent_t stop) {
   if (sp.n_sets < 1 || sp.n_sets > kSetsMax || g.n_cams > kSetCams) return hipErrorInvalidValue;
-  const dim3 grid(g.n_wg * sp.n_sets), block(kThreads);
+  const dim3 grid(g.n_wg * sp.n_sets), block(kApplyThreads);
   if (g.vblend) hipExtLaunchKernelGGL((k_apply_sets<true>), grid, block, 0, st, start, stop, 0u, g, sp);
   else hipExtLaunchKernelGGL((k_apply_sets<false>), grid, block, 0, st, start, stop, 0u, g, sp);
   return hipGetLastError();

@@ -102,7 +102,7 @@ __global__ __launch_bounds__(kThreads) void k_diff_cells(Geo g, FramePtrs fp, At
   __shared__ AttnLds L;
   const int k = blockIdx.y, ci = blockIdx.x;
   if (!cam_active(g, k)) return;
-  const DevCam cam = uniform_cam(g.cams[k]);
+  const DevCam cam = uniform_cam(g, k);
   if (ci * a.cell >= cam.height) {   // below the camera's cell grid: zeros
     uint32_t* out = a.cells + ((int64_t)k * a.hc + ci) * a.wc;
     for (int i = threadIdx.x; i < a.wc; i += kThreads) out[i] = 0u;

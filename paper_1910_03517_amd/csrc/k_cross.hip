@@ -18,9 +18,6 @@
 
 namespace rc {
 
-constexpr int kX3 = 12;   // parameters of one map
-constexpr int kXU = 4;    // rows in flight per thread in the apply
-
 // ----------------------------------------------------------------- statistics
 
 // Cross sums of the band of unit (k, s, j) = blockIdx.x, one workgroup each.
@@ -29,7 +26,7 @@ __global__ __launch_bounds__(kThreads) void k_cross_stats(Geo g, FramePtrs fp, C
   const int nb = g.n_blocks, unit = blockIdx.x;
   const int k = unit / (2 * nb), s = (unit / nb) & 1, j = unit % nb;
   if (!cam_active(g, k)) return;
-  const DevCam cam = uniform_cam(g.cams[k]);
+  const DevCam cam = uniform_cam(g, k);
   const int r0 = (int)((int64_t)j * cam.height / nb), r1 = (int)((int64_t)(j + 1) * cam.height / nb);
   const int band = cam.band, c0 = s == 0 ? 0 : cam.width - band;
   const __amdgpu_buffer_rsrc_t rin = frame_rsrc(fp.in[k], cam);
@@ -184,218 +181,11 @@ __global__ __launch_bounds__(kThreads) void k_build_cross(Geo g, CrossBufs x) {
 
 // ----------------------------------------------------------------- apply
 
-// Whether every row r of both sides' maps can be evaluated in 32-bit
-// integers: |A| < 2^23 (24-bit multiplies) and A_r . x + B_r + 2^15 inside
-// int32 for every x in [0, 255]^3.
-__device__ inline bool cross_small(const int64_t (&q)[2][kX3]) {
-  bool ok = true;
-#pragma unroll
-  for (int sd = 0; sd < 2; ++sd)
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-      int64_t lo = q[sd][9 + r] + 32768, hi = lo;
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        const int64_t a = q[sd][r * 3 + c];
-        ok = ok && a < (1 << 23) && a > -(1 << 23);
-        lo += a < 0 ? 255 * a : 0;
-        hi += a > 0 ? 255 * a : 0;
-      }
-      ok = ok && lo >= INT32_MIN && hi <= INT32_MAX;
-    }
-  return ok;
-}
-
-// The blended sample of channel r: f = clamp((A_r . x + B_r + 2^15) >> 16,
-// 0, 255), y = ((256 - w) x_r + w f + 128) >> 8.
-// y = ((256 - w) x + w f + 128) >> 8 as one dot product of (x, f) with (256 - w, w).
-__device__ inline uint32_t cross_blend(uint32_t x, uint32_t f, uint32_t wp) {
-  return __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, x | (f << 16)), __builtin_bit_cast(u16x2, wp), 128u,
-                                false) >> 8;
-}
-
-// One row of a 4-pixel group with a 32-bit map a (B + 2^15 last) shared by
-// its four pixels: the histogram of its samples (STATS), then per sample the
-// map clamped in place, clamp(v, 0, 2^24 - 1) & 0xffff0000 = f << 16 for the
-// arithmetic v >> 16 (so f lands in the high half next to x), the blend as
-// one dot product, and the four results of a dword gathered by byte permutes.
 template <bool STATS>
-__device__ inline void cross_group_fast(const uint32_t (&d)[3], uint32_t (&o)[3], int npx, const uint32_t (&wp)[4],
-                                        ApplyLds& L, int hrep, const int32_t (&a)[kX3]) {
-  uint32_t raw[12];
-#pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    uint32_t xs[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      const int i = p * 3 + c;
-      xs[c] = (d[i >> 2] >> (8 * (i & 3))) & 0xffu;
-      if (STATS && p < npx)
-        __hip_atomic_fetch_add(&L.hist[hist_word(c, xs[c]) * kRep + hrep], 1u << hist_shift(xs[c]), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-      int32_t v = a[r * 3] * (int32_t)xs[0] + a[r * 3 + 1] * (int32_t)xs[1] + a[r * 3 + 2] * (int32_t)xs[2] + a[9 + r];
-      v = v < 0 ? 0 : (v > 0xffffff ? 0xffffff : v);
-      const uint32_t xf = ((uint32_t)v & 0xffff0000u) | xs[r];
-      raw[p * 3 + r] = p < npx ? __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, xf),
-                                                        __builtin_bit_cast(u16x2, wp[p]), 128u, false)
-                               : 0u;
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < 3; ++q) o[q] = pack_raw4(raw[4 * q], raw[4 * q + 1], raw[4 * q + 2], raw[4 * q + 3]);
-}
-
-// Segment ti with the cross-channel maps of its block; optional whole-frame
-// statistics as in the plain apply (first clears, last flushes).  SMALL (the
-// maps fit 32-bit arithmetic, cross_small): the groups of four pixels that
-// lie on one side take that side's map, the same for every lane (so it stays
-// in scalar registers), with kXU rows of loads in flight.  The group holding
-// the image centre, and every group when the maps need 64-bit arithmetic, go
-// sample by sample with the map read from LDS.
-template <bool STATS, bool SMALL>
-__device__ __attribute__((always_inline)) void cross_tile(const Geo& g, const FramePtrs& fp, const Bufs& b,
-                                                          const CrossBufs& x, int ti, ApplyLds& L, bool first,
-                                                          bool last, const int64_t (&q)[2][kX3]) {
-  const int tid = threadIdx.x;
-  const Tile t = uniform_tile(g.tiles[ti]);
-  const DevCam cam = uniform_cam(g.cams[t.cam]);
-  const int W = cam.width, half = cam.half, pitch = (int)cam.pitch;
-  int64_t* qs = reinterpret_cast<int64_t*>(L.lut);   // [side][12]
-  if (tid < 2 * kX3) qs[tid] = x.q3[(((int64_t)t.cam * 2 + tid / kX3) * g.n_blocks + t.block) * kX3 + tid % kX3];
-  if (STATS && first)
-    for (int i = tid; i < kHistWords; i += kThreads) L.hist[i] = 0;
-  __syncthreads();
-  const __amdgpu_buffer_rsrc_t rin = frame_rsrc(fp.in[t.cam], cam);
-  const __amdgpu_buffer_rsrc_t rout = frame_rsrc(fp.out[t.cam], cam);
-  const uint16_t* wrow = x.weights + (int64_t)t.cam * g.w_max;
-  const int hrep = tid & (kRep - 1);
-  const int ngroups = (W + 3) >> 2;
-  // Both sides' maps in 32-bit form (uniform).
-  int32_t aL[kX3], aR[kX3];
-#pragma unroll
-  for (int i = 0; i < kX3; ++i) {
-    aL[i] = i >= 9 ? (int32_t)(q[0][i] + 32768) : (int32_t)((uint32_t)q[0][i] << 8) >> 8;
-    aR[i] = i >= 9 ? (int32_t)(q[1][i] + 32768) : (int32_t)((uint32_t)q[1][i] << 8) >> 8;
-  }
-  // Group grp (four pixels) of every row of the segment: mode 0 / 1 all on
-  // the left / right side with that side's map, 2 sample by sample.
-  auto do_group = [&](int grp, int mode) {
-    const int col0 = grp * 4, npx = min(4, W - col0);
-    uint32_t wp[4];
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      const uint32_t w = p < npx ? (uint32_t)wrow[col0 + p] : 0u;
-      wp[p] = (256u - w) | (w << 16);
-    }
-    auto rows_one_side = [&](const int32_t (&a)[kX3]) {
-      for (int row = t.r0; row < t.r1; row += kXU) {
-        uint32_t d[kXU][3];
-#pragma unroll
-        for (int u = 0; u < kXU; ++u) {
-          const int off = (row + u) * pitch + col0 * 3;
-          if (row + u < t.r1) {
-            if (npx == 4) {
-              load_group<3>(rin, off, d[u]);
-            } else {
-              d[u][0] = d[u][1] = d[u][2] = 0u;
-#pragma unroll
-              for (int i = 0; i < 12; ++i)
-                if (i < 3 * npx)
-                  d[u][i >> 2] |= (uint32_t)__builtin_amdgcn_raw_buffer_load_b8(rin, off + i, 0, 0) << (8 * (i & 3));
-            }
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < kXU; ++u) {
-          if (row + u < t.r1) {
-            const int off = (row + u) * pitch + col0 * 3;
-            uint32_t o[3];
-            cross_group_fast<STATS>(d[u], o, npx, wp, L, hrep, a);
-            if (npx == 4) {
-              store_group<3>(rout, off, o);
-            } else {
-#pragma unroll
-              for (int i = 0; i < 12; ++i)
-                if (i < 3 * npx)
-                  __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(o[i >> 2] >> (8 * (i & 3))), rout, off + i, 0, 0);
-            }
-          }
-        }
-      }
-    };
-    if (SMALL && mode == 0) {
-      rows_one_side(aL);
-    } else if (SMALL && mode == 1) {
-      rows_one_side(aR);
-    } else {
-      // Sample by sample in 64-bit integers (exact for every map).
-      for (int row = t.r0; row < t.r1; ++row) {
-        const int off = row * pitch + col0 * 3;
-#pragma unroll 1
-        for (int p = 0; p < npx; ++p) {
-          const uint32_t x0 = __builtin_amdgcn_raw_buffer_load_b8(rin, off + 3 * p, 0, 0);
-          const uint32_t x1 = __builtin_amdgcn_raw_buffer_load_b8(rin, off + 3 * p + 1, 0, 0);
-          const uint32_t x2 = __builtin_amdgcn_raw_buffer_load_b8(rin, off + 3 * p + 2, 0, 0);
-          if (STATS) {
-            __hip_atomic_fetch_add(&L.hist[hist_word(0, x0) * kRep + hrep], 1u << hist_shift(x0), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_WORKGROUP);
-            __hip_atomic_fetch_add(&L.hist[hist_word(1, x1) * kRep + hrep], 1u << hist_shift(x1), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_WORKGROUP);
-            __hip_atomic_fetch_add(&L.hist[hist_word(2, x2) * kRep + hrep], 1u << hist_shift(x2), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_WORKGROUP);
-          }
-          const int base = col0 + p >= half ? kX3 : 0;
-          const uint32_t w = (uint32_t)wrow[col0 + p], wpp = (256u - w) | (w << 16);
-#pragma unroll 1
-          for (int c = 0; c < 3; ++c) {
-            int64_t v = qs[base + c * 3] * (int64_t)x0 + qs[base + c * 3 + 1] * (int64_t)x1 +
-                        qs[base + c * 3 + 2] * (int64_t)x2 + qs[base + 9 + c] + 32768;
-            v >>= 16;
-            const uint32_t f = (uint32_t)(v < 0 ? 0 : (v > 255 ? 255 : v));
-            const uint32_t xc = c == 0 ? x0 : (c == 1 ? x1 : x2);
-            __builtin_amdgcn_raw_buffer_store_b8((uint8_t)cross_blend(xc, f, wpp), rout, off + 3 * p + c, 0, 0);
-          }
-        }
-      }
-    }
-  };
-  if (SMALL) {
-    // Threads take the all-left groups, then the all-right ones, so that
-    // every wave but the last of each run follows one side's path; the group
-    // holding the image centre (when half % 4 != 0) goes sample by sample.
-    const int gL = half >> 2, gR = (half + 3) >> 2;
-    for (int i = tid; i < gL; i += kThreads) do_group(i, 0);
-    for (int i = tid; i < ngroups - gR; i += kThreads) do_group(gR + i, 1);
-    if (gR > gL && tid == 0) do_group(gL, 2);
-  } else {
-    for (int grp = tid; grp < ngroups; grp += kThreads) do_group(grp, 2);
-  }
-  if (STATS && (last || kPack)) flush_whole<3, 1>(g, b, t.cam, L, 0ull, 0ull);
-}
-
-template <bool STATS>
-__global__ __launch_bounds__(kThreads) void k_apply_cross(Geo g, FramePtrs fp, Bufs b, CrossBufs x) {
+__global__ __launch_bounds__(kApplyThreads) void k_apply_cross(Geo g, FramePtrs fp, Bufs b, CrossBufs x) {
   __shared__ ApplyLds L;
-  const int s0 = uniform(g.wg_seg[blockIdx.x]), s1 = uniform(g.wg_seg[blockIdx.x + 1]);
-  int prev = -1;
-  for (int s = s0; s < s1; ++s) {
-    const int cam = uniform(g.tiles[s].cam);
-    if (!cam_active(g, cam)) continue;
-    const bool last = s + 1 == s1 || uniform(g.tiles[s + 1].cam) != cam;
-    const int blk = uniform(g.tiles[s].block);
-    int64_t q[2][kX3];
-#pragma unroll
-    for (int sd = 0; sd < 2; ++sd)
-#pragma unroll
-      for (int i = 0; i < kX3; ++i) q[sd][i] = uniform(x.q3[(((int64_t)cam * 2 + sd) * g.n_blocks + blk) * kX3 + i]);
-    if (cross_small(q)) cross_tile<STATS, true>(g, fp, b, x, s, L, cam != prev, last, q);
-    else cross_tile<STATS, false>(g, fp, b, x, s, L, cam != prev, last, q);
-    __syncthreads();
-    prev = cam;
-  }
+  b.weights = x.weights;
+  apply_run<true, STATS, false, true>(g, fp, b, x.q3, (int)blockIdx.x, L);
 }
 
 // ----------------------------------------------------------------- launchers
@@ -423,8 +213,8 @@ hipError_t launch_build_cross(const Geo& g, const CrossBufs& x, hipStream_t st) 
 
 hipError_t launch_apply_cross(const Geo& g, const FramePtrs& fp, const Bufs& b, const CrossBufs& x, bool stats,
                               hipStream_t st) {
-  if (stats) hipLaunchKernelGGL(k_apply_cross<true>, dim3(g.n_wg), dim3(kThreads), 0, st, g, fp, b, x);
-  else hipLaunchKernelGGL(k_apply_cross<false>, dim3(g.n_wg), dim3(kThreads), 0, st, g, fp, b, x);
+  if (stats) hipLaunchKernelGGL(k_apply_cross<true>, dim3(g.n_wg), dim3(kApplyThreads), 0, st, g, fp, b, x);
+  else hipLaunchKernelGGL(k_apply_cross<false>, dim3(g.n_wg), dim3(kApplyThreads), 0, st, g, fp, b, x);
   return hipGetLastError();
 }
 

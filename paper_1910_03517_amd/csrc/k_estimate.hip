@@ -28,7 +28,7 @@ __global__ __launch_bounds__(kThreads) void k_estimate_quantile(Geo g, Bufs b) {
   if (u >= g.n_cams * 2 * nb * kCS) return;    // the whole wave
   const int c = u % kCS, j = (u / kCS) % nb, s = (u / (kCS * nb)) & 1, k = u / (kCS * nb * 2);
   if (!cam_active(g, k)) return;
-  const DevCam cam = uniform_cam(g.cams[k]);
+  const DevCam cam = uniform_cam(g, k);
   const int fc = cam.face_cam[s];
   const int64_t uf = fc < 0 ? -1 : unit_index(fc, cam.face_side[s], j, c, nb);
   const uint64_t n_own = b.band_sums[(int64_t)u * 3];
@@ -252,32 +252,21 @@ __global__ __launch_bounds__(kThreads) void k_estimate_removal(Geo g, Bufs b, Re
 // chain the estimates in order.
 union AheadLds {
   ApplyLds a;
-  StatsLds s;
+  StatsLds s[2];
 };
+static_assert(kApplyThreads == 2 * kThreads, "the seam part takes the wide form");
 template <bool VBLEND, bool QFIT>
-__global__ __launch_bounds__(kThreads) void k_frameset_ahead(Geo g, FramePtrs fa, Bufs ba, FramePtrs fe, Bufs be,
+__global__ __launch_bounds__(kApplyThreads) void k_frameset_ahead(Geo g, FramePtrs fa, Bufs ba, FramePtrs fe, Bufs be,
                                                              int n_est) {
   __shared__ AheadLds U;
   const int bid = (int)blockIdx.x;
   if (bid < n_est) {
     PrevPtrs pp;
     Removal rm;
-    band_estimate_body<false, false, QFIT>(g, fe, pp, be, rm, &U.s, bid, n_est);
+    band_estimate_body<true, false, QFIT>(g, fe, pp, be, rm, U.s, bid, n_est);
     return;
   }
-  const int w = bid - n_est;
-  const int s0 = uniform(g.wg_seg[w]), s1 = uniform(g.wg_seg[w + 1]);
-  int prev = -1;
-  for (int s = s0; s < s1;) {
-    const int cam = uniform(g.tiles[s].cam);
-    if (!cam_active(g, cam)) {
-      ++s;
-      continue;
-    }
-    s = apply_tile_dispatch<true, true, true, VBLEND>(g, fa, ba, s, s1, U.a, cam != prev);
-    __syncthreads();
-    prev = cam;
-  }
+  apply_run<true, true, VBLEND, false>(g, fa, ba, nullptr, bid - n_est, U.a);
 }
 
 hipError_t launch_frameset_ahead(const Geo& g, const FramePtrs* fa, const Bufs& ba, const FramePtrs* fe,
@@ -287,7 +276,7 @@ hipError_t launch_frameset_ahead(const Geo& g, const FramePtrs* fa, const Bufs& 
   const FramePtrs none = {};
   const FramePtrs& a = fa ? *fa : none;
   const FramePtrs& e = fe ? *fe : none;
-  const dim3 grid(n_est + n_app), block(kThreads);
+  const dim3 grid(n_est + n_app), block(kApplyThreads);
   const bool q = g.fit == RT_FIT_QUANTILE;
   if (g.vblend && q) hipLaunchKernelGGL((k_frameset_ahead<true, true>), grid, block, 0, st, g, a, ba, e, be, n_est);
   else if (g.vblend) hipLaunchKernelGGL((k_frameset_ahead<true, false>), grid, block, 0, st, g, a, ba, e, be, n_est);

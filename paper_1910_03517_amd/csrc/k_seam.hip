@@ -87,8 +87,8 @@ __device__ void seam_rows_chunk(const Geo& g, const FramePtrs& fp, const SeamArg
   const int R = kSeamChunk / f;                 // box rows per chunk
   const int j0 = chunk * R;                     // first box row of the chunk
   if (it.n == 0 || j0 >= it.n) return;          // uniform over the workgroup
-  const DevCam cl = uniform_cam(g.cams[k]);
-  const DevCam cr = uniform_cam(g.cams[it.kr]);
+  const DevCam cl = uniform_cam(g, k);
+  const DevCam cr = uniform_cam(g, it.kr);
   const int i = tid >> 2, b = tid & 3;          // image row in the chunk; box 0 = I-_{-1}, 1 = I-_0, 2 = I+_0, 3 = I+_1
   const int nrow = min(R, it.n - j0) * f;
   if (i < nrow) {
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(kThreads) void k_seam_rows(Geo g, FramePtrs fp, Sea
   __shared__ SeamLds L;
   const int k = blockIdx.x >> 1, kind = blockIdx.x & 1;
   if (!cam_active(g, k)) return;
-  const DevCam c = uniform_cam(g.cams[k]);
+  const DevCam c = uniform_cam(g, k);
   if (c.bps == 2) seam_rows_chunk<1, 2>(g, fp, a, k, kind, blockIdx.y, L);
   else if (c.channels == 3) seam_rows_chunk<3, 1>(g, fp, a, k, kind, blockIdx.y, L);
   else seam_rows_chunk<1, 1>(g, fp, a, k, kind, blockIdx.y, L);

@@ -4,8 +4,6 @@
 
 namespace rc {
 
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
 // Two vectors in flight per thread and the apply pass's non-temporal cache
 // policy: the fastest copy shape measured on MI355X for 87 MB buffers.
 template <int VB>

@@ -25,13 +25,11 @@ struct rt_ctx {
   rt_opts opts{};
   std::vector<rt_camera_desc> cams;
   std::vector<DevCam> hcams;
-  std::vector<Tile> htiles;
   int w_max = 0;
   int tile_rows = 0;
-  int grid = 0;             // apply workgroups (0 = one per tile)
+  int grid = 0;             // apply workgroups (0: see build_tables)
   DevCam* dcams = nullptr;
-  Tile* dtiles = nullptr;
-  int32_t* dwg = nullptr;   // [n_wg + 1] first segment of each apply workgroup
+  WgRun* druns = nullptr;   // [n_wg] rows of each apply workgroup
   double* seam_rows = nullptr;   // row values of rt_seam_cost when the caller passes none
   size_t seam_rows_n = 0;
 
@@ -87,6 +85,14 @@ rt_status hip_fail(hipError_t e, const char* what) {
 constexpr int kMaxDim = 32768;
 constexpr int kDefaultTileRows = 32;
 constexpr int kMaxApplyGrid = 1 << 16;
+// Apply workgroups of the default split, two per compute unit.  Measured on
+// the 14x1920x1080 rig (us per frame-set, both kernels): 512 of 512 threads
+// 60.6, 768 69.9, 256 of 1024 threads 75.2, 1024 of 256 threads 59.7 (but 45.1
+// against 42.4 on a rig of small ragged cameras).
+#ifndef RC_APPLY_RUNS
+#define RC_APPLY_RUNS 512
+#endif
+constexpr int kAutoRuns = RC_APPLY_RUNS;
 
 bool aligned(const void* p, uintptr_t a) { return ((uintptr_t)p % a) == 0; }
 
@@ -146,50 +152,67 @@ rt_status check_active(const rt_ctx* ctx, uint64_t active) {
 
 }  // namespace
 
-// Tile table and device tables.  Every block is split into
-// ceil(rows / cap) tiles of equal height (+-1 row), cap = tile_rows or less
-// where the apply pass's packed histogram needs it; tiles are camera-major.
-// Apply work.  grid == 0: every vertical block of every camera is cut into
-// ceil(rows / cap) tiles of equal height (+-1 row), one workgroup per tile.
-// grid > 0: `grid` workgroups, each on a contiguous share of rows, the
-// shares as even in bytes as whole cameras allow, cut into segments at block
-// boundaries and at most cap rows.  cap = tile_rows, or less where the packed
-// histogram needs it.
+// How an apply workgroup lies over the rows of camera d: ap_cols groups of 4
+// pixels by ap_lanes rows, the split of the row into equal column chunks (at
+// most 8) that keeps most of its threads busy.
+static void lay_apply(DevCam& d) {
+  const int groups = (d.width + 3) / 4;
+  int64_t best = -1;
+  for (int chunks = 1; chunks <= 8 || best < 0; ++chunks) {
+    const int cols = (groups + chunks - 1) / chunks;
+    if (cols > kApplyThreads) continue;
+    const int lanes = kApplyThreads / cols;
+    // Groups taken per pass of the workgroup over a chunk, of equal worth at
+    // equal use: the fewest chunks win.
+    const int64_t use = (int64_t)groups * lanes * 1024 / chunks;
+    if (use > best + best / 32) {
+      best = use;
+      d.ap_cols = cols;
+      d.ap_lanes = lanes;
+    }
+  }
+}
+
+// Device tables: the rows that each apply workgroup takes.  By default
+// (tile_rows kDefaultTileRows, grid 0) every camera gets a whole number of
+// workgroups, about kAutoRuns of them over the rig in proportion to its bytes,
+// and its rows are split evenly among them, in steps of the rows a workgroup
+// takes at a time.  Any other tile_rows with grid 0: one workgroup per tile,
+// every vertical block cut into ceil(rows / tile_rows) tiles of equal height
+// (+-1 row).  grid > 0: `grid` workgroups, each on a contiguous share of rows,
+// the shares as even in bytes as whole cameras allow.
 static rt_status build_tables(rt_ctx* ctx, int tile_rows, int grid) {
   const int n_cams = ctx->n_cams;
   const int nb = ctx->opts.n_blocks;
   ctx->tile_rows = tile_rows;
   ctx->grid = grid;
   ++ctx->generation;
-  ctx->htiles.clear();
-  // Rows [a, e) of camera k, cut at block boundaries and at most cap rows.
-  auto emit = [&](int k, int a, int e) {
+  std::vector<WgRun> runs;
+  // Segments (parts of runs inside one block, of at most tile_rows rows) of
+  // rows [a, e) of camera k: what rt_ctx_tuning reports.
+  int64_t segments = 0;
+  auto tiles = [&](int k, int a, int e, bool one_run_each) {
     const int H = ctx->cams[k].height;
-    const int cap = std::min(tile_rows, max_tile_rows(ctx->cams[k].width));
     for (int j = 0; j < nb; ++j) {
       const int b0 = std::max(a, (int)((int64_t)j * H / nb)), b1 = std::min(e, (int)((int64_t)(j + 1) * H / nb));
       const int rows = b1 - b0;
       if (rows <= 0) continue;
-      const int parts = (rows + cap - 1) / cap;
-      for (int p = 0; p < parts; ++p)
-        ctx->htiles.push_back(
-            Tile{k, j, b0 + (int)((int64_t)p * rows / parts), b0 + (int)((int64_t)(p + 1) * rows / parts)});
+      const int parts = (rows + tile_rows - 1) / tile_rows;
+      segments += parts;
+      for (int p = 0; one_run_each && p < parts; ++p)
+        runs.push_back(WgRun{k, b0 + (int)((int64_t)p * rows / parts), k, b0 + (int)((int64_t)(p + 1) * rows / parts)});
     }
   };
-  std::vector<int32_t> wg;
-  int G = 0;
-  if (grid == 0) {
-    for (int k = 0; k < n_cams; ++k) emit(k, 0, ctx->cams[k].height);
-    G = (int)ctx->htiles.size();
-    wg.resize(G + 1);
-    for (int w = 0; w <= G; ++w) wg[w] = w;
-  } else if (grid >= n_cams) {
+  int64_t total = 0;
+  for (int k = 0; k < n_cams; ++k) total += (int64_t)ctx->cams[k].height * ctx->hcams[k].row_bytes;
+  const bool own = grid == 0 && tile_rows == kDefaultTileRows;
+  const int G = own ? std::max(kAutoRuns, n_cams) : grid;
+  if (grid == 0 && !own) {
+    for (int k = 0; k < n_cams; ++k) tiles(k, 0, ctx->cams[k].height, true);
+  } else if (G >= n_cams) {
     // Every camera gets a whole number of shares, one plus its part of the
     // other G - K by bytes (largest remainders), and its rows are split
     // evenly among them: no share spans two cameras.
-    G = grid;
-    int64_t total = 0;
-    for (int k = 0; k < n_cams; ++k) total += (int64_t)ctx->cams[k].height * ctx->hcams[k].row_bytes;
     std::vector<int> n(n_cams, 1);
     std::vector<std::pair<int64_t, int>> rem(n_cams);
     int given = n_cams;
@@ -201,19 +224,21 @@ static rt_status build_tables(rt_ctx* ctx, int tile_rows, int grid) {
     }
     std::sort(rem.begin(), rem.end(), std::greater<std::pair<int64_t, int>>());
     for (int i = 0; given < G; ++i, ++given) ++n[-rem[i].second];
-    wg.resize(G + 1);
-    int w = 0;
     for (int k = 0; k < n_cams; ++k) {
       const int H = ctx->cams[k].height;
-      for (int i = 0; i < n[k]; ++i, ++w) {
-        wg[w] = (int32_t)ctx->htiles.size();
-        emit(k, (int)((int64_t)i * H / n[k]), (int)((int64_t)(i + 1) * H / n[k]));
+      const int step = own ? ctx->hcams[k].ap_lanes : 1;
+      const int steps = (H + step - 1) / step;
+      const int m = own ? std::min(n[k], steps) : n[k];
+      for (int i = 0; i < m; ++i) {
+        const int a = std::min(H, (int)((int64_t)i * steps / m) * step);
+        const int e = std::min(H, (int)((int64_t)(i + 1) * steps / m) * step);
+        runs.push_back(WgRun{k, a, k, e});
+        tiles(k, a, e, false);
       }
     }
   } else {
     // Fewer workgroups than cameras: share w starts at the first row whose
     // byte offset reaches w / G of the total, so shares span cameras.
-    G = grid;
     std::vector<int64_t> base(n_cams + 1, 0);
     for (int k = 0; k < n_cams; ++k)
       base[k + 1] = base[k] + (int64_t)ctx->cams[k].height * ctx->hcams[k].row_bytes;
@@ -226,48 +251,37 @@ static rt_status build_tables(rt_ctx* ctx, int tile_rows, int grid) {
       row = (int)((target - base[cam] + rb - 1) / rb);
       if (row >= ctx->cams[cam].height) { ++cam; row = 0; }
     };
-    wg.resize(G + 1);
     int c0, r0s;
     share_start(0, c0, r0s);
     for (int w = 0; w < G; ++w) {
       int c1, r1s;
       share_start(w + 1, c1, r1s);
-      wg[w] = (int32_t)ctx->htiles.size();
-      for (int k = c0; k <= c1 && k < n_cams; ++k) emit(k, k == c0 ? r0s : 0, k == c1 ? r1s : ctx->cams[k].height);
+      // A share that ends at a camera's first row ends with the camera before.
+      const bool back = r1s == 0 && c1 > c0;
+      runs.push_back(WgRun{c0, r0s, back ? c1 - 1 : std::min(c1, n_cams - 1), back ? ctx->cams[c1 - 1].height : r1s});
+      for (int k = c0; k <= c1 && k < n_cams; ++k)
+        tiles(k, k == c0 ? r0s : 0, k == c1 ? r1s : ctx->cams[k].height, false);
       c0 = c1;
       r0s = r1s;
     }
   }
-  wg[G] = (int32_t)ctx->htiles.size();
-  for (int k = 0; k < n_cams; ++k) ctx->hcams[k].tile_begin = ctx->hcams[k].tile_end = 0;
-  for (size_t i = ctx->htiles.size(); i-- > 0;) {
-    DevCam& d = ctx->hcams[ctx->htiles[i].cam];
-    if (d.tile_end == 0) d.tile_end = (int32_t)i + 1;
-    d.tile_begin = (int32_t)i;
-  }
-  const size_t nt = ctx->htiles.size();
-  if (ctx->dtiles) (void)hipFree(ctx->dtiles);
-  if (ctx->dwg) (void)hipFree(ctx->dwg);
-  ctx->dtiles = nullptr;
-  ctx->dwg = nullptr;
+  if (ctx->druns) (void)hipFree(ctx->druns);
+  ctx->druns = nullptr;
   hipError_t e = hipSuccess;
   if (!ctx->dcams) e = hipMalloc((void**)&ctx->dcams, sizeof(DevCam) * n_cams);
-  if (e == hipSuccess) e = hipMalloc((void**)&ctx->dtiles, sizeof(Tile) * std::max<size_t>(nt, 1));
-  if (e == hipSuccess) e = hipMalloc((void**)&ctx->dwg, sizeof(int32_t) * wg.size());
+  if (e == hipSuccess) e = hipMalloc((void**)&ctx->druns, sizeof(WgRun) * runs.size());
   if (e != hipSuccess) return fail(RT_ENOMEM, "device tables: %s", hipGetErrorString(e));
   e = hipMemcpy(ctx->dcams, ctx->hcams.data(), sizeof(DevCam) * n_cams, hipMemcpyHostToDevice);
-  if (e == hipSuccess && nt) e = hipMemcpy(ctx->dtiles, ctx->htiles.data(), sizeof(Tile) * nt, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(ctx->dwg, wg.data(), sizeof(int32_t) * wg.size(), hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = hipMemcpy(ctx->druns, runs.data(), sizeof(WgRun) * runs.size(), hipMemcpyHostToDevice);
   if (e != hipSuccess) return hip_fail(e, "uploading context tables");
   Geo& g = ctx->geo;
   g.cams = ctx->dcams;
-  g.tiles = ctx->dtiles;
-  g.wg_seg = ctx->dwg;
-  g.n_wg = G;
+  g.runs = ctx->druns;
+  g.n_wg = (int32_t)runs.size();
   g.n_cams = n_cams;
   g.n_blocks = nb;
   g.w_max = ctx->w_max;
-  g.n_tiles = (int32_t)nt;
+  g.n_tiles = (int32_t)segments;
   g.mode = ctx->opts.mode;
   g.vblend = ctx->opts.vblend;
   g.fit = ctx->opts.fit;
@@ -375,6 +389,7 @@ rt_status rt_ctx_create(const rt_camera_desc* cams, int32_t n_cams, const rt_opt
     d.band = std::min(o.band_width, d.half);
     d.row_bytes = c.width * c.channels * d.bps;
     d.pitch = c.pitch_bytes;
+    lay_apply(d);
     // Ring neighbours: right side of position p meets the left side of p + 1.
     int m = 0;
     for (int i = 0; i < n_cams; ++i) m += cams[i].ring == c.ring;
@@ -415,8 +430,7 @@ rt_status rt_ctx_destroy(rt_ctx* ctx) {
   (void)hipDeviceSynchronize();
   free_timing(ctx);
   if (ctx->dcams) (void)hipFree(ctx->dcams);
-  if (ctx->dtiles) (void)hipFree(ctx->dtiles);
-  if (ctx->dwg) (void)hipFree(ctx->dwg);
+  if (ctx->druns) (void)hipFree(ctx->druns);
   if (ctx->seam_rows) (void)hipFree(ctx->seam_rows);
   delete ctx;
   return RT_OK;
@@ -1800,7 +1814,7 @@ rt_status rt_ctx_tuning(const rt_ctx* ctx, int32_t* tile_rows, int32_t* grid, in
   if (!ctx) return fail(RT_EINVAL, "ctx is NULL");
   if (tile_rows) *tile_rows = ctx->tile_rows;
   if (grid) *grid = ctx->grid;
-  if (n_tiles) *n_tiles = (int32_t)ctx->htiles.size();
+  if (n_tiles) *n_tiles = ctx->geo.n_tiles;
   return RT_OK;
 }
 

@@ -13,26 +13,10 @@ constexpr int kNB = RT_NBINS;    // histogram bins
 constexpr int kThreads = 256;    // threads of every workgroup
 constexpr int kMlpIn = RT_MLP_IN, kMlpHid = RT_MLP_HID, kMlpOut = RT_MLP_OUT;
 
-// Whole-frame histogram of the apply pass: replicas, and whether two bins
-// share a word as 16-bit halves (1: bins 2i, 2i + 1; 2: bins i, i + 128).
-#ifndef RC_APPLY_PACK
-#define RC_APPLY_PACK 0
+#ifndef RC_APPLY_THREADS
+#define RC_APPLY_THREADS 512
 #endif
-#ifndef RC_APPLY_REP
-#define RC_APPLY_REP (RC_APPLY_PACK ? 16 : 8)
-#endif
-static_assert(kThreads % RC_APPLY_REP == 0 && (RC_APPLY_REP & (RC_APPLY_REP - 1)) == 0, "replicas");
-
-// Most rows one apply tile of a camera of this width may hold so that no
-// packed 16-bit counter overflows: replica r is updated by the threads with
-// tid % REP == r, which own the 4-pixel column groups g with g % REP == r, so
-// a tile adds at most 4 * ceil(groups / REP) * rows to one counter.
-__host__ __device__ inline int max_tile_rows(int width) {
-  if (!RC_APPLY_PACK) return 1 << 30;
-  const int groups = (width + 3) / 4;
-  const int per_rep = (groups + RC_APPLY_REP - 1) / RC_APPLY_REP;
-  return 65535 / (4 * per_rep);
-}
+constexpr int kApplyThreads = RC_APPLY_THREADS;   // threads of an apply workgroup
 
 // Per-camera geometry as the kernels see it (uploaded once per context).
 struct DevCam {
@@ -43,15 +27,15 @@ struct DevCam {
   int32_t row_bytes;     // width * channels * bps
   int32_t face_cam[2];   // camera facing side s, -1 if none (open chain end)
   int32_t face_side[2];
-  int32_t tile_begin;    // this camera's tiles are [tile_begin, tile_end)
-  int32_t tile_end;
+  int32_t ap_cols;       // 4-pixel groups of a row that an apply workgroup takes side by side
+  int32_t ap_lanes;      // rows it takes at a time (ap_cols * ap_lanes <= kApplyThreads)
   int64_t pitch;         // bytes between rows
 };
 
-// One segment of the apply pass: rows [r0, r1) of block `block` of camera
-// `cam`.  Each apply workgroup takes a contiguous run of segments.
-struct Tile {
-  int32_t cam, block, r0, r1;
+// The run of an apply workgroup: from row row0 of camera cam0 up to row row1
+// (exclusive) of camera cam1, whole cameras between them.
+struct WgRun {
+  int32_t cam0, row0, cam1, row1;
 };
 
 // Frame pointers of one launch, passed by value as a kernel argument.
@@ -108,8 +92,7 @@ struct CrossBufs {
 // Context-wide constants passed to every kernel.
 struct Geo {
   const DevCam* cams;    // device array [K]
-  const Tile* tiles;     // device array [n_tiles], camera-major
-  const int32_t* wg_seg; // device array [n_wg + 1]: workgroup w takes segments [wg_seg[w], wg_seg[w + 1])
+  const WgRun* runs;     // device array [n_wg]
   int32_t n_cams, n_blocks, w_max, n_tiles;
   int32_t mode;
   int32_t n_wg;          // apply workgroups
@@ -141,21 +124,22 @@ __device__ inline T* uniform_ptr(T* p) {
   return reinterpret_cast<T*>(uniform((int64_t)reinterpret_cast<uintptr_t>(p)));
 }
 
-__device__ inline DevCam uniform_cam(const DevCam& c) {
-  DevCam u;
-  u.width = uniform(c.width); u.height = uniform(c.height); u.channels = uniform(c.channels);
-  u.bit_depth = uniform(c.bit_depth); u.bps = uniform(c.bps); u.band = uniform(c.band); u.half = uniform(c.half);
-  u.row_bytes = uniform(c.row_bytes);
-  u.face_cam[0] = uniform(c.face_cam[0]); u.face_cam[1] = uniform(c.face_cam[1]);
-  u.face_side[0] = uniform(c.face_side[0]); u.face_side[1] = uniform(c.face_side[1]);
-  u.tile_begin = uniform(c.tile_begin); u.tile_end = uniform(c.tile_end);
-  u.pitch = uniform(c.pitch);
-  return u;
+// A copy of *p, p the same in every lane of the wave, through scalar loads:
+// context tables do not change while a kernel runs.
+template <typename T>
+__device__ inline T uniform_load(const T* p) {
+  static_assert(sizeof(T) % 4 == 0, "whole dwords");
+  const __attribute__((address_space(4))) int32_t* q =
+      (const __attribute__((address_space(4))) int32_t*)(uintptr_t)uniform((int64_t)(uintptr_t)p);
+  int32_t v[sizeof(T) / 4];
+#pragma unroll
+  for (int i = 0; i < (int)(sizeof(T) / 4); ++i) v[i] = q[i];
+  T t;
+  __builtin_memcpy(&t, v, sizeof t);
+  return t;
 }
-
-__device__ inline Tile uniform_tile(const Tile& t) {
-  return Tile{uniform(t.cam), uniform(t.block), uniform(t.r0), uniform(t.r1)};
-}
+__device__ inline DevCam uniform_cam(const Geo& g, int k) { return uniform_load(g.cams + k); }
+__device__ inline WgRun uniform_run(const Geo& g, int w) { return uniform_load(g.runs + w); }
 
 // p and cam must be uniform over the wave (see uniform_cam).
 __device__ inline __amdgpu_buffer_rsrc_t frame_rsrc(const void* p, const DevCam& cam) {
