@@ -248,39 +248,35 @@ __device__ inline void estimate_unit(const Geo& g, const Bufs& b, int u) {
   temporal_update(g, b.params, b.valid, u, st, a, bb);
 }
 
-// Entry x of the three channel tables of unit (k, s, j) = `unit3` (the
-// channel-0 unit index divided by 3) from the maps ab[c] = (a, b); thread
-// x == 0 also stores the q16 pairs.
-__device__ inline void lut_entry_ab(const Geo& g, const Bufs& b, int unit3, int x, const double (*ab)[2]) {
-  const int k = unit3 / (2 * g.n_blocks);
-  const DevCam& cam = g.cams[k];
+// A map parameter in Q16.
+__device__ inline int64_t q16_of(double p) { return (int64_t)__builtin_rint(p * 65536.0); }
+
+// Entries x .. x + 3 of the 8-bit table of the map (A, Bq), entry x in the low byte.
+__device__ inline uint32_t table_quad(int64_t A, int64_t Bq, int x) {
+  int64_t y = A * x + Bq + 32768;
+  uint32_t t = 0;
 #pragma unroll
-  for (int c = 0; c < kCS; ++c) {
-    const int64_t u = (int64_t)unit3 * kCS + c;
-    const int64_t A = (int64_t)__builtin_rint(ab[c][0] * 65536.0);
-    const int64_t Bq = (int64_t)__builtin_rint(ab[c][1] * 65536.0);
-    if (x == 0) {
-      b.q16[u * 2 + 0] = A;
-      b.q16[u * 2 + 1] = Bq;
-    }
-    if (cam.bps == 1) {
-      int64_t y = (A * x + Bq + 32768) >> 16;
-      y = y < 0 ? 0 : (y > 255 ? 255 : y);
-      b.lut8[u * kNB + x] = (uint8_t)y;
-    }
+  for (int i = 0; i < 4; ++i, y += A) {
+    const int64_t f = y >> 16;
+    t |= (uint32_t)(f < 0 ? 0 : (f > 255 ? 255 : f)) << (8 * i);
   }
+  return t;
 }
 
-// lut_entry_ab with the maps read from the caller's parameters.
-__device__ inline void lut_entry(const Geo& g, const Bufs& b, int unit3, int x) {
-  double ab[kCS][2];
-#pragma unroll
-  for (int c = 0; c < kCS; ++c) {
-    const int64_t u = (int64_t)unit3 * kCS + c;
-    ab[c][0] = b.params[u * 2 + 0];
-    ab[c][1] = b.params[u * 2 + 1];
+// The three channel tables of unit (k, s, j) = `unit3` (the channel-0 unit
+// index divided by 3) and its q16 pairs from the caller's parameters, by the
+// kThreads threads of a workgroup.
+__device__ inline void unit_tables(const Geo& g, const Bufs& b, int unit3, int tid) {
+  const int k = unit3 / (2 * g.n_blocks);
+  const int c = tid / (kNB / 4), x = 4 * (tid % (kNB / 4));
+  if (c >= kCS) return;
+  const int64_t u = (int64_t)unit3 * kCS + c;
+  const int64_t A = q16_of(b.params[u * 2]), Bq = q16_of(b.params[u * 2 + 1]);
+  if (x == 0) {
+    b.q16[u * 2 + 0] = A;
+    b.q16[u * 2 + 1] = Bq;
   }
-  lut_entry_ab(g, b, unit3, x, ab);
+  if (g.cams[k].bps == 1) reinterpret_cast<uint32_t*>(b.lut8 + u * kNB)[x / 4] = table_quad(A, Bq, x);
 }
 
 // Q8 blend weight of column col of a camera of width W: h = floor(W/2); the

@@ -1,179 +1,401 @@
-// Statistics of section 3.1 as device functions: the band statistics of one
-// (camera, side, block) unit, and the clearing of the whole-frame statistics
-// that the apply pass accumulates.
+// Band statistics of section 3.1 as device functions: the histogram and sums
+// of one (camera, side, block) unit, optionally with the sums of its pixels
+// that do not move against the previous frame (object removal) or with its
+// cross sums over the channels; and the clearing of the whole-frame
+// statistics that the apply pass accumulates.
 #pragma once
+
+#include <type_traits>
 
 #include "dev_common.h"
 
 namespace rc {
 
-struct StatsLds {
-  uint32_t hist[kCS * kNB];
-  unsigned long long red[9 * 16];
+// Previous frames of a launch (device pointers; all NULL: nothing moves).
+struct PrevPtrs {
+  const uint8_t* in[RT_MAX_CAMS];
 };
 
-// Band statistics of unit (k, s, j): histogram and exact (n, S1, S2) of the
-// band's samples.  Threads walk the band as (row, dword) pairs; a dword holds 4
-// consecutive 8-bit samples or 2 16-bit samples of the row, and only the bytes
-// inside the band count.  8-bit sums follow from the exact histogram.
+// Object-removal arguments of a launch.
+struct Removal {
+  uint64_t* kept_sums;   // [K][2][NB][3][3] (n, S1, S2) of the kept pixels
+  uint8_t* method;       // [K][2][NB] method taken by each unit (may be NULL)
+  int32_t tau;           // threshold in 8-bit units
+  int32_t has_prev;      // 0: no previous frames, every pixel is kept
+  double min_kept;       // least kept fraction of both bands for the removal fit
+};
+
+// What a band pass gathers beside the histogram and (n, S1, S2).
+enum { kBandPlain, kBandMotion, kBandCross };
+
+struct BandArgs {
+  const PrevPtrs* pp;        // kBandMotion
+  const Removal* rm;
+  uint64_t* cross;           // kBandCross: [unit][3]
+};
+
+constexpr int kPartMax = 7;    // sums a thread accumulates itself
+constexpr int kBandWaves = 4;  // most waves of a band pass
+
+struct BandLds {
+  alignas(16) uint32_t hist[kCS * kNB];
+  unsigned long long part[kBandWaves][kPartMax];
+};
+
 // Barriers (__syncthreads) that band_unit passes, on every path.
-constexpr int kBandBarriers = 4;
+constexpr int kBandBarriers = 3;
 
-// (Inlined: an outlined call would take the kernel's by-value arguments by
-// address, in scratch memory.)
-template <int C, int BPS>
-__device__ __attribute__((always_inline)) void band_unit(const Geo& g, const FramePtrs& fp, const Bufs& b, int k,
-                                                         int s, int j, StatsLds& L, uint64_t* sums_out, int tid) {
-  const DevCam cam = uniform_cam(g, k);
-  auto clear = [&]() {
-    for (int i = tid; i < kCS * kNB; i += kThreads) L.hist[i] = 0;
-    __syncthreads();
-  };
+// Four pixels of a band row as loaded: the dwords that hold them, the first
+// starting at the aligned byte at or before the group, and the third byte of
+// a last dword that is cut by the row's end after three bytes.
+template <int ND>
+struct BandGroup {
+  uint32_t d[ND + 1];
+  uint32_t x;
+};
 
-  const int r0 = (int)((int64_t)j * cam.height / g.n_blocks);
-  const int r1 = (int)((int64_t)(j + 1) * cam.height / g.n_blocks);
-  const int band = cam.band;
-  const int c0 = (s == 0) ? 0 : cam.width - band;
-  const int b0 = c0 * C * BPS;                 // band bytes [b0, b1) of each row
-  const int b1 = (c0 + band) * C * BPS;
-  const int q0 = b0 >> 2;
-  const int dw = ((b1 + 3) >> 2) - q0;         // dwords per band row
-  const int rows = r1 - r0;
-  const int shift = cam.bit_depth - 8;
-  const __amdgpu_buffer_rsrc_t rin = frame_rsrc(fp.in[k], cam);
-  unsigned long long a1 = 0, a2 = 0;           // 16-bit sums
-
-  // One sample (byte offset o of the row) into the histogram.
-  auto count = [&](uint32_t d, int boff) {
-    if (BPS == 1) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int o = boff + e;
-        if (o >= b0 && o < b1) {
-          const uint32_t v = (d >> (8 * e)) & 0xffu;
-          const int c = (C == 1) ? 0 : o % C;
-          __hip_atomic_fetch_add(&L.hist[c * kNB + v], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
-      }
+// Loads the nb bytes at byte offset o of the row at rowoff; SHIFTED: any o and
+// nb (no byte beyond the row's end is touched), else o is a multiple of 4 and
+// nb = 4 ND.
+template <int ND, bool SHIFTED>
+__device__ inline void load_band(__amdgpu_buffer_rsrc_t r, int rowoff, int o, int nb, int row_bytes,
+                                 BandGroup<ND>& v) {
+  if constexpr (!SHIFTED) {
+    if constexpr (ND == 3) {
+      typedef unsigned int u32x3 __attribute__((ext_vector_type(3)));
+      const u32x3 t = __builtin_amdgcn_raw_buffer_load_b96(r, rowoff + o, 0, 0);
+      v.d[0] = t.x; v.d[1] = t.y; v.d[2] = t.z;
+    } else if constexpr (ND == 2) {
+      typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+      const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(r, rowoff + o, 0, 0);
+      v.d[0] = t.x; v.d[1] = t.y;
     } else {
+      v.d[0] = __builtin_amdgcn_raw_buffer_load_b32(r, rowoff + o, 0, 0);
+    }
+    return;
+  }
+  const int base = o & ~3, end = o + nb;
+  v.x = 0;
 #pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        const int o = boff + 2 * e;
-        if (o >= b0 && o < b1) {
-          const uint32_t v = (d >> (16 * e)) & 0xffffu;
-          uint32_t bin = v >> shift;
-          bin = bin > 255u ? 255u : bin;
-          __hip_atomic_fetch_add(&L.hist[bin], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          a1 += v;
-          a2 += (unsigned long long)v * v;
-        }
+  for (int i = 0; i <= ND; ++i) {
+    const int at = base + 4 * i, have = row_bytes - at;
+    v.d[i] = 0;
+    if (at < end) {
+      if (have >= 4) v.d[i] = __builtin_amdgcn_raw_buffer_load_b32(r, rowoff + at, 0, 0);
+      else if (have >= 2) {
+        v.d[i] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, rowoff + at, 0, 0);
+        if (have == 3) v.x = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(r, rowoff + at + 2, 0, 0);
+      } else {
+        v.d[i] = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(r, rowoff + at, 0, 0);
       }
     }
-  };
-  // A dword of the band row at byte offset boff; the one crossing the row end
-  // is assembled from single bytes.
-  auto load = [&](int rowoff, int boff) -> uint32_t {
-    if (boff + 4 <= cam.row_bytes) return __builtin_amdgcn_raw_buffer_load_b32(rin, rowoff + boff, 0, 0);
-    uint32_t d = 0;
-    for (int e = 0; boff + e < cam.row_bytes; ++e)
-      d |= (uint32_t)__builtin_amdgcn_raw_buffer_load_b8(rin, rowoff + boff + e, 0, 0) << (8 * e);
-    return d;
-  };
+  }
+}
 
-  constexpr int kU = 4;                        // loads in flight per thread
-  if (band > 0 && rows > 0 && dw <= kThreads) {
-    // Thread tid keeps one dword column q of the band and walks the rows
-    // tid / dw, + rstep, ...: no division per load.
-    const int rstep = kThreads / dw;
-    const int q = tid % dw;
-    const int boff = (q0 + q) * 4;
-    constexpr int kR = 2 * kU;                 // a 67-row block of a 32-pixel RGB band in one round
-    const bool active = tid < rstep * dw;
-    uint32_t d[kR];
-    auto fetch = [&](int row) {
+// The group's ND dwords, its first byte in the lowest byte of w[0].
+template <int ND, bool SHIFTED>
+__device__ inline void band_dwords(const BandGroup<ND>& v, int o, int row_bytes, uint32_t (&w)[ND]) {
+  if constexpr (!SHIFTED) {
 #pragma unroll
-      for (int u = 0; u < kR; ++u) {
-        const int r = row + u * rstep;
-        d[u] = r < rows ? load((int)((int64_t)(r0 + r) * cam.pitch), boff) : 0u;
-      }
-    };
-    // The first round of loads is in flight while the histogram is cleared.
-    if (active) fetch(tid / dw);
-    clear();
-    if (active) {
-      for (int row = tid / dw; row < rows; row += kR * rstep) {
-        if (row != tid / dw) fetch(row);
-#pragma unroll
-        for (int u = 0; u < kR; ++u)
-          if (row + u * rstep < rows) count(d[u], boff);
-      }
-    }
-  } else if (band > 0 && rows > 0) {
-    clear();
-    const int total = rows * dw;
-    for (int base = tid; base < total; base += kU * kThreads) {
-      uint32_t d[kU];
-      int boffs[kU];
-#pragma unroll
-      for (int u = 0; u < kU; ++u) {
-        const int idx = base + u * kThreads;
-        d[u] = 0;
-        boffs[u] = -1;
-        if (idx < total) {
-          const int row = idx / dw;
-          const int q = idx - row * dw;
-          boffs[u] = (q0 + q) * 4;
-          d[u] = load((int)((int64_t)(r0 + row) * cam.pitch), boffs[u]);
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < kU; ++u)
-        if (boffs[u] >= 0) count(d[u], boffs[u]);
-    }
+    for (int i = 0; i < ND; ++i) w[i] = v.d[i];
   } else {
-    clear();
+    const int cut = row_bytes - (o & ~3);          // the third byte belongs to the dword that holds offset cut - 1
+    uint32_t d[ND + 1];
+#pragma unroll
+    for (int i = 0; i <= ND; ++i) d[i] = cut == 4 * i + 3 ? v.d[i] | (v.x << 16) : v.d[i];
+#pragma unroll
+    for (int i = 0; i < ND; ++i) w[i] = __builtin_amdgcn_alignbyte(d[i + 1], d[i], (uint32_t)(o & 3));
+  }
+}
+
+// Sample i (0 .. 4 C - 1 in pixel-major order) of a group of 4 pixels.
+template <int BPS>
+__device__ inline uint32_t group_sample(const uint32_t* w, int i) {
+  if (BPS == 1) return (w[i >> 2] >> (8 * (i & 3))) & 0xffu;
+  return (w[i >> 1] >> (16 * (i & 1))) & 0xffffu;
+}
+
+// Band statistics of unit (k, s, j) by HT threads (whole waves; tid: the
+// thread's index among them): histogram and exact (n, S1, S2) of the band's
+// samples into the caller's buffers.  The threads walk the band in groups of 4
+// pixels, kB groups per thread in flight; the first ones are loaded while the
+// histogram is cleared.  8-bit sums follow from the histogram, one wave per
+// channel; 16-bit ones, the kept sums (kBandMotion) and the cross sums
+// (kBandCross) are accumulated by the threads.  sums / extra (LDS, may be
+// NULL) also receive the nine sums and the nine kept or three cross sums.
+template <int C, int BPS, int HT, int WHAT, bool SHIFTED>
+__device__ __attribute__((always_inline)) inline void band_pass(const Geo& g, const FramePtrs& fp, const Bufs& b,
+                                                                const BandArgs& a, const DevCam& cam, int k, int s,
+                                                                int j, BandLds& L, uint64_t* sums, uint64_t* extra,
+                                                                int tid) {
+  constexpr int ND = C * BPS;                 // dwords of a 4-pixel group
+  constexpr bool kMotion = WHAT == kBandMotion, kCross = WHAT == kBandCross;
+  constexpr int kB = HT >= 256 ? 3 : kMotion ? 3 : 5;
+  constexpr int kParts = kMotion ? 1 + 2 * C : kCross ? 3 : 0;
+  constexpr int kPart16 = kParts;             // first of the two 16-bit sums
+  constexpr int kAll = kParts + (BPS == 2 ? 2 : 0);
+  static_assert(kAll <= kPartMax && HT / kWave <= kBandWaves, "partial sums");
+  const int nb = g.n_blocks;
+  const int r0 = (int)((uint32_t)j * (uint32_t)cam.height / (uint32_t)nb);
+  const int r1 = (int)((uint32_t)(j + 1) * (uint32_t)cam.height / (uint32_t)nb);
+  const int band = cam.band, rows = r1 - r0;
+  const int c0 = s == 0 ? 0 : cam.width - band;
+  const int ng = (band + 3) >> 2;             // groups per band row
+  const int shift = cam.bit_depth - 8;
+  const int pitch = (int)cam.pitch;
+  const __amdgpu_buffer_rsrc_t rin = frame_rsrc(fp.in[k], cam);
+  uint32_t thr = 0;
+  bool has_prev = false;
+  __amdgpu_buffer_rsrc_t rprev = rin;
+  if constexpr (kMotion) {
+    thr = (uint32_t)a.rm->tau << shift;
+    has_prev = a.rm->has_prev != 0;
+    if (has_prev) rprev = frame_rsrc(a.pp->in[k], cam);
+  }
+  // Walk over (row, group): HT groups on is drow rows and dq groups on.
+  const int total = rows * ng;
+  int row = ng ? tid / ng : 0, q = tid - row * ng;
+  const int drow = ng ? HT / ng : 0, dq = HT - drow * ng;
+  auto next = [&](int& rw, int& qq) {
+    rw += drow;
+    qq += dq;
+    if (qq >= ng) { qq -= ng; ++rw; }
+  };
+  BandGroup<ND> v[kB], pv[kMotion ? kB : 1];
+  auto fetch = [&](int rw, int qq) {
+#pragma unroll
+    for (int i = 0; i < kB; ++i) {
+      if (rw < rows) {
+        const int off = (r0 + rw) * pitch, o = (c0 + 4 * qq) * ND;
+        const int n = min(4, band - 4 * qq) * ND;
+        load_band<ND, SHIFTED>(rin, off, o, n, cam.row_bytes, v[i]);
+        if (kMotion && has_prev) load_band<ND, SHIFTED>(rprev, off, o, n, cam.row_bytes, pv[kMotion ? i : 0]);
+      }
+      next(rw, qq);
+    }
+  };
+  if (total > 0) fetch(row, q);
+  {
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    const u32x4 zero = {0, 0, 0, 0};
+    for (int i = tid; i < kCS * kNB / 4; i += HT) reinterpret_cast<u32x4*>(L.hist)[i] = zero;
   }
   __syncthreads();
 
-  const int64_t u0 = unit_index(k, s, j, 0, g.n_blocks);
-  uint32_t* oh = b.band_hist + u0 * kNB;
-  for (int i = tid; i < kCS * kNB; i += kThreads) oh[i] = L.hist[i];
-  // (n, S1, S2) per channel slot: quantity i is channel i / 3, moment i % 3.
-  const unsigned long long x = (unsigned long long)tid;
-  block_sums(
-      9,
-      [&](int i) -> unsigned long long {
-        const int c = i / 3, m = i - 3 * (i / 3);
-        if (c >= C) return 0ull;
-        const unsigned long long h = L.hist[c * kNB + tid];
-        if (m == 0) return h;
-        if (BPS == 2) return m == 1 ? a1 : a2;
-        return m == 1 ? h * x : h * x * x;
-      },
-      [&](int i, unsigned long long tot) {
-        b.band_sums[u0 * 3 + i] = tot;
-        if (sums_out) sums_out[i] = tot;
-      },
-      L.red, tid);
+  unsigned long long a1 = 0, a2 = 0;          // 16-bit sums
+  uint32_t kn = 0;
+  unsigned long long k1[C], k2[C];            // kept sums; cross: k2 the three products
+#pragma unroll
+  for (int c = 0; c < C; ++c) k1[c] = k2[c] = 0;
+  if (total > 0) {
+    for (int it = tid; it < total; it += kB * HT) {
+      if (it != tid) fetch(row, q);
+#pragma unroll
+      for (int i = 0; i < kB; ++i) {
+        if (row < rows) {
+          const int o = (c0 + 4 * q) * ND;
+          uint32_t w[ND], p[ND];
+          band_dwords<ND, SHIFTED>(v[i], o, cam.row_bytes, w);
+          if (kMotion && has_prev) band_dwords<ND, SHIFTED>(pv[kMotion ? i : 0], o, cam.row_bytes, p);
+          const int npx = SHIFTED ? min(4, band - 4 * q) : 4;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            if (e < npx) {
+              uint32_t x[C];
+              bool moving = false;
+#pragma unroll
+              for (int c = 0; c < C; ++c) {
+                x[c] = group_sample<BPS>(w, e * C + c);
+                if (kMotion && has_prev) {
+                  const uint32_t y = group_sample<BPS>(p, e * C + c);
+                  moving = moving || (x[c] > y ? x[c] - y : y - x[c]) > thr;
+                }
+                uint32_t bin = x[c];
+                if (BPS == 2) {
+                  bin >>= shift;
+                  bin = bin > 255u ? 255u : bin;
+                  a1 += x[c];
+                  a2 += (unsigned long long)x[c] * x[c];
+                }
+                __hip_atomic_fetch_add(&L.hist[c * kNB + bin], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+              }
+              if (kMotion && !moving) {
+                ++kn;
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                  k1[c] += x[c];
+                  k2[c] += (unsigned long long)x[c] * x[c];
+                }
+              }
+              if constexpr (kCross) {
+                k2[0] += x[0] * x[1];
+                k2[1] += x[0] * x[2];
+                k2[2] += x[1] * x[2];
+              }
+            }
+          }
+        }
+        next(row, q);
+      }
+    }
+  }
+  const int wave = tid / kWave, lane = tid % kWave;
+  if constexpr (kAll > 0) {
+    // Partial sums: kept n, S1 and S2 per channel (or the cross sums), then
+    // the 16-bit S1 and S2.
+    auto part = [&](int i, unsigned long long t) {
+      t = wave_sum_u64(t);
+      if (lane == 0) L.part[wave][i] = t;
+    };
+    if constexpr (kMotion) {
+      part(0, kn);
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        part(1 + c, k1[c]);
+        part(1 + C + c, k2[c]);
+      }
+    }
+    if constexpr (kCross) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) part(c, k2[c < C ? c : 0]);
+    }
+    if constexpr (BPS == 2) {
+      part(kPart16, a1);
+      part(kPart16 + 1, a2);
+    }
+  }
+  __syncthreads();
+
+  auto total_of = [&](int i) {
+    unsigned long long t = 0;
+#pragma unroll
+    for (int w = 0; w < HT / kWave; ++w) t += L.part[w][i];
+    return t;
+  };
+  const int64_t u0 = unit_index(k, s, j, 0, nb);
+  // One wave per channel: the histogram written out, lane l holding bins
+  // 4 l .. 4 l + 3, and its sums.
+  for (int c = wave; c < kCS; c += HT / kWave) {
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    const u32x4 h = reinterpret_cast<const u32x4*>(L.hist + c * kNB)[lane];
+    uint32_t* oh = b.band_hist + (u0 + c) * kNB + 4 * lane;
+    oh[0] = h.x; oh[1] = h.y; oh[2] = h.z; oh[3] = h.w;
+    unsigned long long s1 = 0, s2 = 0;
+    if (c < C) {
+      if (BPS == 2) {
+        s1 = total_of(kPart16);
+        s2 = total_of(kPart16 + 1);
+      } else {
+        const unsigned long long x = (unsigned long long)(4 * lane);
+        const unsigned long long t1 = h.x * x, t2 = h.y * (x + 1), t3 = h.z * (x + 2), t4 = h.w * (x + 3);
+        s1 = wave_sum_u64(t1 + t2 + t3 + t4);
+        s2 = wave_sum_u64(t1 * x + t2 * (x + 1) + t3 * (x + 2) + t4 * (x + 3));
+      }
+    }
+    if (lane < 3) {
+      const unsigned long long n = c < C ? (unsigned long long)rows * (unsigned long long)band : 0ull;
+      const unsigned long long t = lane == 0 ? n : (lane == 1 ? s1 : s2);
+      b.band_sums[(u0 + c) * 3 + lane] = t;
+      if (sums) sums[c * 3 + lane] = t;
+    }
+  }
+  if constexpr (kMotion) {
+    // Kept sums per channel slot, n repeated for every channel of the camera.
+    if (tid < 9) {
+      const int c = tid / 3, m = tid - 3 * (tid / 3);
+      const unsigned long long t = c >= C ? 0ull : total_of(m == 0 ? 0 : (m == 1 ? 1 + c : 1 + C + c));
+      a.rm->kept_sums[u0 * 3 + tid] = t;
+      if (extra) extra[tid] = t;
+    }
+  }
+  if constexpr (kCross) {
+    if (tid < 3) {
+      const unsigned long long t = total_of(tid);
+      a.cross[u0 + tid] = t;
+      if (extra) extra[tid] = t;
+    }
+  }
+  __syncthreads();
 }
 
-// Band statistics of unit (camera, side, block) = `unit` by kThreads threads
-// (tid: the thread's index among them; -1: the workgroup's threadIdx.x); with
-// sums_out (LDS) its nine sums are also left there for the workgroup.
-__device__ __attribute__((always_inline)) inline void band_unit_dispatch(const Geo& g, const FramePtrs& fp,
-                                                                         const Bufs& b, int unit, StatsLds& L,
-                                                                         uint64_t* sums_out = nullptr,
-                                                                         int tid = -1) {
-  if (tid < 0) tid = (int)threadIdx.x;
+// Band statistics of unit (camera, side, block) = `unit` by HT threads (see
+// band_pass); kBandCross takes RGB8 cameras only.
+template <int HT, int WHAT>
+__device__ __attribute__((always_inline)) inline void band_unit(const Geo& g, const FramePtrs& fp, const Bufs& b,
+                                                                const BandArgs& a, int unit, BandLds& L,
+                                                                uint64_t* sums, uint64_t* extra, int tid) {
   const int nb = g.n_blocks;
   const int k = unit / (2 * nb);
   const int s = (unit / nb) & 1;
   const int j = unit % nb;
-  const DevCam& cam = g.cams[k];
-  if (!cam_active(g, k)) return;
-  if (cam.bps == 2) band_unit<1, 2>(g, fp, b, k, s, j, L, sums_out, tid);
-  else if (cam.channels == 3) band_unit<3, 1>(g, fp, b, k, s, j, L, sums_out, tid);
-  else band_unit<1, 1>(g, fp, b, k, s, j, L, sums_out, tid);
+  const DevCam cam = uniform_cam(g, k);
+  // Whole groups of four pixels on dword boundaries.
+  const int start = (s == 0 ? 0 : cam.width - cam.band) * cam.channels * cam.bps;
+  const bool whole = (cam.band & 3) == 0 && (start & 3) == 0;
+  auto pass = [&](auto c, auto bps) {
+    if (whole) band_pass<decltype(c)::value, decltype(bps)::value, HT, WHAT, false>(g, fp, b, a, cam, k, s, j, L, sums, extra, tid);
+    else band_pass<decltype(c)::value, decltype(bps)::value, HT, WHAT, true>(g, fp, b, a, cam, k, s, j, L, sums, extra, tid);
+  };
+  using one = std::integral_constant<int, 1>;
+  using two = std::integral_constant<int, 2>;
+  using three = std::integral_constant<int, 3>;
+  if constexpr (WHAT == kBandCross) {
+    pass(three{}, one{});
+  } else {
+    if (cam.bps == 2) pass(one{}, two{});
+    else if (cam.channels == 3) pass(three{}, one{});
+    else pass(one{}, one{});
+  }
+}
+
+// The seam block (camera k, block j) = bid: its units are u[0], the right band
+// of camera k; the band that one faces, if any; and at the start of an open
+// ring camera k's left band, which faces nothing.  Over the rig every unit is
+// in exactly one seam block, and only units 0 and 1 of a seam with `faces` set
+// face each other.
+struct Seam {
+  int k, j, n;
+  int u[3];
+  bool faces;
+};
+
+__device__ inline Seam seam_of(const Geo& g, const DevCam& cam, int k, int j) {
+  const int nb = g.n_blocks;
+  Seam m;
+  m.k = k;
+  m.j = j;
+  m.faces = cam.face_cam[1] >= 0;
+  m.u[0] = (k * 2 + 1) * nb + j;
+  m.u[1] = m.u[2] = 0;
+  m.n = 1;
+  if (m.faces) m.u[m.n++] = (cam.face_cam[1] * 2 + cam.face_side[1]) * nb + j;
+  if (cam.face_cam[0] < 0) {
+    (m.n == 1 ? m.u[1] : m.u[2]) = k * 2 * nb + j;
+    ++m.n;
+  }
+  return m;
+}
+
+// Band statistics of a seam's units by a workgroup of NT threads, two units at
+// a time, each by one half of it; unit i's sums (and its kept or cross sums)
+// are left in sums[i] (extra[i]).
+template <int NT, int WHAT>
+__device__ __attribute__((always_inline)) inline void seam_bands(const Geo& g, const FramePtrs& fp, const Bufs& b,
+                                                                 const BandArgs& a, const Seam& m, BandLds (&L)[2],
+                                                                 uint64_t (&sums)[3][9], uint64_t (&extra)[3][9]) {
+  constexpr int HT = NT / 2;
+  static_assert(HT % kWave == 0, "whole waves");
+  const int tid = threadIdx.x;
+  const int half = uniform((int32_t)(tid / HT)), ltid = tid - half * HT;
+#pragma unroll 1
+  for (int p = 0; p < m.n; p += 2) {
+    const int i = p + half;
+    if (i < m.n) {
+      band_unit<HT, WHAT>(g, fp, b, a, i == 0 ? m.u[0] : (i == 1 ? m.u[1] : m.u[2]), L[half], sums[i], extra[i], ltid);
+    } else {
+      for (int w = 0; w < kBandBarriers; ++w) __syncthreads();
+    }
+  }
 }
 
 // Zero the whole-frame histogram and sums of every active camera (grid-stride).

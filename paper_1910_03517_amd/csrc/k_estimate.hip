@@ -5,7 +5,6 @@
 // as the seam estimate of the next).
 #include "dev_apply.h"
 #include "dev_estimate.h"
-#include "dev_motion.h"
 #include "dev_stats.h"
 #include "rt_ahead_internal.h"
 
@@ -46,7 +45,7 @@ __global__ __launch_bounds__(kThreads) void k_estimate_quantile(Geo g, Bufs b) {
 
 __global__ __launch_bounds__(kThreads) void k_build_lut(Geo g, Bufs b) {
   if (!cam_active(g, blockIdx.x / (2 * g.n_blocks))) return;
-  lut_entry(g, b, blockIdx.x, threadIdx.x);
+  unit_tables(g, b, blockIdx.x, threadIdx.x);
 }
 
 __global__ __launch_bounds__(kThreads) void k_weights(Geo g, Bufs b) {
@@ -58,70 +57,60 @@ __global__ __launch_bounds__(kThreads) void k_weights(Geo g, Bufs b) {
 }
 
 // Band statistics, estimate and tables of a frame-set in one launch, one
-// workgroup per (camera k, block j): it takes the right band of camera k, the
-// band that faces it (the left band of the next camera of the ring) and, at
-// the start of an open ring, camera k's left band, which faces nothing.
-// Every unit is taken exactly once, and a unit's estimate needs only its own
-// band and the one it faces, so after the statistics of its bands the
-// workgroup fits those units and builds their tables with no other
-// workgroup involved.  WIDE: 2 x kThreads threads whose halves gather two
-// bands at the same time (for rigs with few seam blocks, where the launch
-// is latency-bound; beside the apply kernels of a pipeline the 256-thread
-// form is faster, as its workgroups fit more easily on busy compute units).
-// Same results as k_band_stats, k_estimate, k_build_lut and k_weights in
-// sequence (the whole-frame statistics that the frame-set's apply pass
-// accumulates are cleared here too, when given).  REMOVAL: the band passes
-// also sum the pixels that do not move against the previous frames, and
-// each unit takes the object-removal fit or the smoothing fallback
-// (removal_step), as k_motion_stats and k_estimate_removal would.
-template <bool WIDE, bool REMOVAL, bool QFIT, typename Lds>
-__device__ __attribute__((always_inline)) void band_estimate_body(const Geo& g, const FramePtrs& fp,
-                                                                  const PrevPtrs& pp, const Bufs& b,
-                                                                  const Removal& rm, Lds* L, int bid, int nblk) {
-  static_assert(!(REMOVAL && QFIT), "object removal keeps only the moments of the kept pixels");
-  constexpr int NT = WIDE ? 2 * kThreads : kThreads;
+// workgroup of NT threads per seam block (see Seam).  A unit's estimate needs
+// only its own band and the one it faces, so after the statistics of its
+// bands the workgroup fits those units and builds their tables with no other
+// workgroup involved.  Same results as k_band_stats, k_estimate, k_build_lut
+// and k_weights in sequence (the whole-frame statistics that the frame-set's
+// apply pass accumulates are cleared here too, when given).  WHAT ==
+// kBandMotion: the band passes also sum the pixels that do not move against
+// the previous frames, and each unit takes the object-removal fit or the
+// smoothing fallback (removal_step), as k_motion_stats and k_estimate_removal
+// would.
+//
+// Bound by its chain of dependent steps, not by bytes (2.9 MB of bands per
+// 14x1920x1080 frame-set).  So both bands are gathered side by side, each by
+// half of the workgroup with all of its loads in flight at once, one wave per
+// channel sums a histogram, the fixed-point maps pass through LDS and the
+// tables are built four entries per thread.  Measured on MI355X against the
+// bands one after the other (us): 17.6 -> 13.6 on that rig, 10.5 -> 8.4 on
+// 1x640x480; with object removal, whose groups were loaded one at a time, 38.4
+// -> 15.5.
+struct SeamLds {
+  BandLds band[2];
+  uint64_t sums[3][9];     // (n, S1, S2) per channel of the units taken
+  uint64_t extra[3][9];    // the same over their kept pixels
+  int64_t q[3][kCS][2];    // their Q16 maps after the fit
+};
+
+template <int NT, int WHAT, bool QFIT>
+__device__ __attribute__((always_inline)) inline void band_estimate_body(const Geo& g, const FramePtrs& fp,
+                                                                         const BandArgs& a, const Bufs& b, SeamLds& L,
+                                                                         int bid, int nblk) {
+  constexpr bool kMotion = WHAT == kBandMotion;
+  static_assert(!(kMotion && QFIT), "object removal keeps only the moments of the kept pixels");
   // This kernel's chain of dependent steps is what the next apply waits
   // for; its waves take issue priority over the apply waves they share
   // compute units with (measured on MI355X: 628 -> 674 GPix/s in the
   // pipelined frame-set loop).
   __builtin_amdgcn_s_setprio(3);
-  __shared__ uint64_t sums[3][9];            // (n, S1, S2) per channel of the units taken
-  __shared__ uint64_t kept[REMOVAL ? 3 : 1][9];   // the same over their kept pixels
-  __shared__ double ab[3][kCS][2];           // their maps after the fit
-  // QFIT: the quantile sums of the facing pair (u0, u1) per channel, wave c
-  // taking channel c.
+  // QFIT: the quantile sums of the facing pair per channel, wave c taking
+  // channel c.
   __shared__ uint32_t qcum[QFIT ? kCS : 1][QFIT ? 2 * kNB : 1];
   __shared__ QSums qs[QFIT ? kCS : 1];
   const int nb = g.n_blocks;
   const int k = bid / nb, j = bid - (bid / nb) * nb;
   const int tid = threadIdx.x;
-  // WIDE: each half is whole waves, so its unit (camera, frame pointer) is
-  // uniform per wave and stays in scalar registers.
-  const int half = WIDE ? uniform((int32_t)(tid / kThreads)) : 0, ltid = tid - half * kThreads;
   if (b.whole_hist) zero_whole(g, b, bid * NT + tid, nblk * NT);
   if (!cam_active(g, k)) return;
-  const DevCam& cam = g.cams[k];
-  // Units taken, n of them: u0 the right band of camera k; u1 the band it
-  // faces, if any; then the left band of camera k if it faces nothing.
-  // Only u0 and u1 face each other.
-  const int fc = uniform(cam.face_cam[1]);
-  const int u0 = (k * 2 + 1) * nb + j;
-  const int uf = fc < 0 ? -1 : (fc * 2 + uniform(cam.face_side[1])) * nb + j;
-  const int ul = uniform(cam.face_cam[0]) < 0 ? k * 2 * nb + j : -1;
-  const int u1 = uf >= 0 ? uf : ul;
-  const int u2 = uf >= 0 ? ul : -1;
-  const int n = 1 + (u1 >= 0) + (u2 >= 0);
-  auto unit_at = [&](int i) { return i == 0 ? u0 : (i == 1 ? u1 : u2); };
-  auto band_pass = [&](int i, Lds& Li, int t) {
-    if constexpr (REMOVAL) band_unit_motion_dispatch(g, fp, pp, b, rm, unit_at(i), Li, sums[i], kept[i], t);
-    else band_unit_dispatch(g, fp, b, unit_at(i), Li, sums[i], t);
-  };
-  constexpr int kBarriers = REMOVAL ? kMotionBarriers : kBandBarriers;
+  const DevCam cam = uniform_cam(g, k);
+  const Seam m = seam_of(g, cam, k, j);
   // Thread 64 t + c fits channel c of unit t: its state is read now, ahead
   // of the band passes.
   const int t = tid / kWave, c = tid % kWave;
-  const bool fitter = t < n && c < kCS;
-  const int64_t u = fitter ? (int64_t)unit_at(t) * kCS + c : 0;
+  const bool fitter = t < m.n && c < kCS;
+  const int ut = t == 0 ? m.u[0] : (t == 1 ? m.u[1] : m.u[2]);
+  const int64_t u = fitter ? (int64_t)ut * kCS + c : 0;
   double p0 = 0.0, p1 = 0.0;
   uint8_t v = 0;
   if (fitter) {
@@ -129,90 +118,84 @@ __device__ __attribute__((always_inline)) void band_estimate_body(const Geo& g, 
     p1 = b.params[u * 2 + 1];
     v = b.valid[u];
   }
-  if (WIDE) {
-    // Units 2p and 2p + 1 in pass p, one per half; a half without a unit
-    // passes the same barriers.
-    for (int p = 0; 2 * p < n; ++p) {
-      if (p) __syncthreads();
-      const int i = 2 * p + half;
-      if (i < n) {
-        band_pass(i, L[WIDE ? half : 0], ltid);
-      } else {
-        for (int w = 0; w < kBarriers; ++w) __syncthreads();
-      }
-    }
-  } else {
-    for (int i = 0; i < n; ++i) {
-      if (i) __syncthreads();
-      band_pass(i, L[0], tid);
-    }
-  }
-  if (j == 0)
-    for (int col = tid; col < g.w_max; col += NT)
-      b.weights[(int64_t)k * g.w_max + col] = (uint16_t)blend_weight(cam.width, col);
-  __syncthreads();
+  seam_bands<NT, WHAT>(g, fp, b, a, m, L.band, L.sums, L.extra);
   if constexpr (QFIT) {
-    // Only u0 and u1 face each other; the band histograms were written by
-    // this workgroup's band passes.
+    // The band histograms were written by this workgroup's band passes.
     const int wv = uniform((int32_t)(tid / kWave));
-    if (uf >= 0 && wv < uniform(cam.channels)) {
+    if (m.faces && wv < cam.channels) {
       const int shift = cam.bit_depth > 8 ? cam.bit_depth - 8 : 0;
-      const QSums q = wave_quantile_sums(b.band_hist + ((int64_t)u0 * kCS + wv) * kNB,
-                                         b.band_hist + ((int64_t)uf * kCS + wv) * kNB, shift, qcum[wv], tid % kWave);
+      const QSums q = wave_quantile_sums(b.band_hist + ((int64_t)m.u[0] * kCS + wv) * kNB,
+                                         b.band_hist + ((int64_t)m.u[1] * kCS + wv) * kNB, shift, qcum[wv], tid % kWave);
       if (tid % kWave == 0) qs[wv] = q;
     }
     __syncthreads();
   }
   if (fitter) {
-    const int other = (uf >= 0 && t < 2) ? 1 - t : -1;
-    const uint64_t* fac = other >= 0 ? &sums[other][c * 3] : nullptr;
-    const int channels = uniform(g.cams[unit_at(t) / (2 * nb)].channels);
-    if constexpr (REMOVAL) {
-      const uint64_t* kfac = other >= 0 ? &kept[other][c * 3] : nullptr;
-      const int m = removal_method(&sums[t][0], other >= 0 ? &sums[other][0] : nullptr, &kept[t][0],
-                                   other >= 0 ? &kept[other][0] : nullptr, rm.min_kept);
-      removal_step(g, m, channels, c, &sums[t][c * 3], fac, &kept[t][c * 3], kfac, p0, p1, v);
-      if (c == 0 && rm.method) rm.method[unit_at(t)] = (uint8_t)m;
+    const int other = m.faces && t < 2 ? 1 - t : -1;
+    const uint64_t* own = &L.sums[t][c * 3];
+    const uint64_t* fac = other >= 0 ? &L.sums[other][c * 3] : nullptr;
+    // (The cameras of a ring have the same channels.)
+    if constexpr (kMotion) {
+      const int method = removal_method(&L.sums[t][0], other >= 0 ? &L.sums[other][0] : nullptr, &L.extra[t][0],
+                                        other >= 0 ? &L.extra[other][0] : nullptr, a.rm->min_kept);
+      removal_step(g, method, cam.channels, c, own, fac, &L.extra[t][c * 3],
+                   other >= 0 ? &L.extra[other][c * 3] : nullptr, p0, p1, v);
+      if (c == 0 && a.rm->method) a.rm->method[ut] = (uint8_t)method;
     } else {
-      double a, bb;
+      double fa, fb;
       int st;
       if (QFIT && fac)
-        st = fit_quantile(g, channels, c, true, sums[t][c * 3], sums[other][c * 3], qs[QFIT ? c : 0], t == 0, a,
-                          bb);
+        st = fit_quantile(g, cam.channels, c, true, own[0], fac[0], qs[QFIT ? c : 0], t == 0, fa, fb);
       else
-        st = fit_sums(g, channels, c, &sums[t][c * 3], fac, a, bb);
-      temporal_step(g, st, a, bb, p0, p1, v);
+        st = fit_sums(g, cam.channels, c, own, fac, fa, fb);
+      temporal_step(g, st, fa, fb, p0, p1, v);
     }
     b.params[u * 2] = p0;
     b.params[u * 2 + 1] = p1;
     b.valid[u] = v;
-    ab[t][c][0] = p0;
-    ab[t][c][1] = p1;
+    const int64_t A = q16_of(p0), B = q16_of(p1);
+    b.q16[u * 2] = A;
+    b.q16[u * 2 + 1] = B;
+    L.q[t][c][0] = A;
+    L.q[t][c][1] = B;
   }
+  // The camera's blend weights, shared by its seam blocks.
+  {
+    const int w1 = (int)((int64_t)(j + 1) * g.w_max / nb);
+    for (int col = (int)((int64_t)j * g.w_max / nb) + tid; col < w1; col += NT)
+      b.weights[(int64_t)k * g.w_max + col] = (uint16_t)blend_weight(cam.width, col);
+  }
+  if (cam.bps != 1) return;
   __syncthreads();
-  for (int w = half; w < n; w += (WIDE ? 2 : 1)) lut_entry_ab(g, b, unit_at(w), ltid, ab[w]);
+  // Four entries of a unit's channel table per thread.
+  constexpr int kQuads = kCS * kNB / 4;
+  for (int i = tid; i < m.n * kQuads; i += NT) {
+    const int w = i / kQuads, r = i - w * kQuads;
+    const int ch = r / (kNB / 4), x = 4 * (r % (kNB / 4));
+    const int unit = w == 0 ? m.u[0] : (w == 1 ? m.u[1] : m.u[2]);
+    reinterpret_cast<uint32_t*>(b.lut8 + (int64_t)unit * kCS * kNB)[r] = table_quad(L.q[w][ch][0], L.q[w][ch][1], x);
+  }
 }
 
-template <bool WIDE, bool QFIT>
-__global__ __launch_bounds__(WIDE ? 2 * kThreads : kThreads) void k_band_estimate(Geo g, FramePtrs fp, Bufs b) {
-  __shared__ StatsLds L[WIDE ? 2 : 1];
-  PrevPtrs pp;
-  Removal rm;
-  band_estimate_body<WIDE, false, QFIT>(g, fp, pp, b, rm, L, (int)blockIdx.x, (int)gridDim.x);
+template <int NT, bool QFIT>
+__global__ __launch_bounds__(NT) void k_band_estimate(Geo g, FramePtrs fp, Bufs b) {
+  __shared__ SeamLds L;
+  band_estimate_body<NT, kBandPlain, QFIT>(g, fp, BandArgs{}, b, L, (int)blockIdx.x, (int)gridDim.x);
 }
 
-template <bool WIDE>
-__global__ __launch_bounds__(WIDE ? 2 * kThreads : kThreads) void k_band_estimate_removal(Geo g, FramePtrs fp,
-                                                                                          PrevPtrs pp, Bufs b,
-                                                                                          Removal rm) {
-  __shared__ MotionLds L[WIDE ? 2 : 1];
-  band_estimate_body<WIDE, true, false>(g, fp, pp, b, rm, L, (int)blockIdx.x, (int)gridDim.x);
+template <int NT>
+__global__ __launch_bounds__(NT) void k_band_estimate_removal(Geo g, FramePtrs fp, PrevPtrs pp, Bufs b, Removal rm) {
+  __shared__ SeamLds L;
+  band_estimate_body<NT, kBandMotion, false>(g, fp, BandArgs{&pp, &rm, nullptr}, b, L, (int)blockIdx.x,
+                                             (int)gridDim.x);
 }
 
 // Band statistics with the kept sums, one workgroup per (camera, side, block).
 __global__ __launch_bounds__(kThreads) void k_motion_stats(Geo g, FramePtrs fp, PrevPtrs pp, Bufs b, Removal rm) {
-  __shared__ MotionLds L;
-  band_unit_motion_dispatch(g, fp, pp, b, rm, blockIdx.x, L, nullptr, nullptr, threadIdx.x);
+  __shared__ BandLds L;
+  const int unit = (int)blockIdx.x;
+  if (!cam_active(g, unit / (2 * g.n_blocks))) return;
+  band_unit<kThreads, kBandMotion>(g, fp, b, BandArgs{&pp, &rm, nullptr}, unit, L, nullptr, nullptr, (int)threadIdx.x);
 }
 
 // Removal fit or fallback of every (camera, side, block, channel) unit from
@@ -252,18 +235,15 @@ __global__ __launch_bounds__(kThreads) void k_estimate_removal(Geo g, Bufs b, Re
 // chain the estimates in order.
 union AheadLds {
   ApplyLds a;
-  StatsLds s[2];
+  SeamLds s;
 };
-static_assert(kApplyThreads == 2 * kThreads, "the seam part takes the wide form");
 template <bool VBLEND, bool QFIT>
 __global__ __launch_bounds__(kApplyThreads) void k_frameset_ahead(Geo g, FramePtrs fa, Bufs ba, FramePtrs fe, Bufs be,
                                                              int n_est) {
   __shared__ AheadLds U;
   const int bid = (int)blockIdx.x;
   if (bid < n_est) {
-    PrevPtrs pp;
-    Removal rm;
-    band_estimate_body<true, false, QFIT>(g, fe, pp, be, rm, U.s, bid, n_est);
+    band_estimate_body<kApplyThreads, kBandPlain, QFIT>(g, fe, BandArgs{}, be, U.s, bid, n_est);
     return;
   }
   apply_run<true, true, VBLEND, false>(g, fa, ba, nullptr, bid - n_est, U.a);
@@ -285,35 +265,36 @@ hipError_t launch_frameset_ahead(const Geo& g, const FramePtrs* fa, const Bufs& 
   return hipGetLastError();
 }
 
-// Seam blocks up to which the wide form is launched.
-constexpr int kWideSeamBlocks = 64;
+// Threads of the seam kernel.  Rigs of few seam blocks leave most of the chip
+// idle, so the wide form's shorter passes count there; beside the applies of a
+// pipeline the narrow one fits more easily on busy compute units.
+#ifndef RC_WIDE_BLOCKS
+#define RC_WIDE_BLOCKS 64
+#endif
+constexpr int kWideSeamBlocks = RC_WIDE_BLOCKS, kNarrow = 256, kWide = 512;
 
 hipError_t launch_band_estimate(const Geo& g, const FramePtrs& fp, const Bufs& b, hipStream_t st) {
   const int blocks = g.n_cams * g.n_blocks;
   const bool wide = blocks <= kWideSeamBlocks, q = g.fit == RT_FIT_QUANTILE;
-  const dim3 grid(blocks), block(wide ? 2 * kThreads : kThreads);
-  if (wide && q) hipLaunchKernelGGL((k_band_estimate<true, true>), grid, block, 0, st, g, fp, b);
-  else if (wide) hipLaunchKernelGGL((k_band_estimate<true, false>), grid, block, 0, st, g, fp, b);
-  else if (q) hipLaunchKernelGGL((k_band_estimate<false, true>), grid, block, 0, st, g, fp, b);
-  else hipLaunchKernelGGL((k_band_estimate<false, false>), grid, block, 0, st, g, fp, b);
+  const dim3 grid(blocks), block(wide ? kWide : kNarrow);
+  if (wide && q) hipLaunchKernelGGL((k_band_estimate<kWide, true>), grid, block, 0, st, g, fp, b);
+  else if (wide) hipLaunchKernelGGL((k_band_estimate<kWide, false>), grid, block, 0, st, g, fp, b);
+  else if (q) hipLaunchKernelGGL((k_band_estimate<kNarrow, true>), grid, block, 0, st, g, fp, b);
+  else hipLaunchKernelGGL((k_band_estimate<kNarrow, false>), grid, block, 0, st, g, fp, b);
   return hipGetLastError();
 }
 
 const void* band_estimate_kernel(const Geo& g) {
   const bool wide = g.n_cams * g.n_blocks <= kWideSeamBlocks, q = g.fit == RT_FIT_QUANTILE;
-  if (wide && q) return reinterpret_cast<const void*>(&k_band_estimate<true, true>);
-  if (wide) return reinterpret_cast<const void*>(&k_band_estimate<true, false>);
-  if (q) return reinterpret_cast<const void*>(&k_band_estimate<false, true>);
-  return reinterpret_cast<const void*>(&k_band_estimate<false, false>);
+  if (wide && q) return reinterpret_cast<const void*>(&k_band_estimate<kWide, true>);
+  if (wide) return reinterpret_cast<const void*>(&k_band_estimate<kWide, false>);
+  if (q) return reinterpret_cast<const void*>(&k_band_estimate<kNarrow, true>);
+  return reinterpret_cast<const void*>(&k_band_estimate<kNarrow, false>);
 }
 
 hipError_t launch_band_estimate_removal(const Geo& g, const FramePtrs& fp, const PrevPtrs& pp, const Bufs& b,
                                         const Removal& rm, hipStream_t st) {
-  const int blocks = g.n_cams * g.n_blocks;
-  if (blocks <= kWideSeamBlocks)
-    hipLaunchKernelGGL(k_band_estimate_removal<true>, dim3(blocks), dim3(2 * kThreads), 0, st, g, fp, pp, b, rm);
-  else
-    hipLaunchKernelGGL(k_band_estimate_removal<false>, dim3(blocks), dim3(kThreads), 0, st, g, fp, pp, b, rm);
+  hipLaunchKernelGGL(k_band_estimate_removal<kWide>, dim3(g.n_cams * g.n_blocks), dim3(kWide), 0, st, g, fp, pp, b, rm);
   return hipGetLastError();
 }
 

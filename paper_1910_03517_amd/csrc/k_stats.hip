@@ -5,8 +5,10 @@
 namespace rc {
 
 __global__ __launch_bounds__(kThreads) void k_band_stats(Geo g, FramePtrs fp, Bufs b) {
-  __shared__ StatsLds L;
-  band_unit_dispatch(g, fp, b, blockIdx.x, L);
+  __shared__ BandLds L;
+  const int unit = (int)blockIdx.x;
+  if (!cam_active(g, unit / (2 * g.n_blocks))) return;
+  band_unit<kThreads, kBandPlain>(g, fp, b, BandArgs{}, unit, L, nullptr, nullptr, (int)threadIdx.x);
 }
 
 __global__ __launch_bounds__(kThreads) void k_zero_whole(Geo g, Bufs b) {

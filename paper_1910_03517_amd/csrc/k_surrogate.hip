@@ -178,7 +178,7 @@ __global__ __launch_bounds__(kThreads) void k_select_lut(Geo g, const float* __r
     }
   }
   __syncthreads();
-  lut_entry(g, b, u3, tid);
+  unit_tables(g, b, u3, tid);
   if (u3 % (2 * nb) == 0)
     for (int col = tid; col < g.w_max; col += kThreads)
       b.weights[(int64_t)k * g.w_max + col] = (uint16_t)blend_weight(g.cams[k].width, col);

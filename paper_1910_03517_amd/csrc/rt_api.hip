@@ -12,7 +12,7 @@
 #include <string>
 #include <vector>
 
-#include "dev_motion.h"
+#include "dev_stats.h"
 #include "rt_ahead_internal.h"
 #include "rt_internal.h"
 #include "rt_surrogate_internal.h"
