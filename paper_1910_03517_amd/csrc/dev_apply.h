@@ -19,14 +19,25 @@
 // statistics with global atomics (the whole-frame buffers must be zero before
 // the first run).
 //
+// The runs of a camera interleave: run i of m takes every m-th step of
+// ap_lanes rows, so that all of a camera's workgroups read and write side by
+// side in its frame at any time, a handful of streams for the memory in place
+// of hundreds.
+//
 // What bounds it: memory requests in flight and, next to them, the vector ALU
 // and the LDS atomics, each busy about half of the time.  Long runs pay the
 // set-up and the flush of the histogram once per half compute unit, and rows
-// side by side keep narrow images' workgroups full.  Measured on MI355X
-// against one 256-thread workgroup per 22-row tile (us, statistics fused):
-// 14x1920x1080 RGB8 50.6 -> 44.7 (174 MB: 3.4 -> 3.9 TB/s), 1x640x480 18.0 ->
-// 10.6, 5x1031x517 RGB8 + 3x333x251 u16 + 2x719x405 gray8 57 -> 17, which was
-// the ragged row ends, read byte by byte and row by row.
+// side by side keep narrow images' workgroups full.  Measured on MI355X (us,
+// statistics fused; one 256-thread workgroup per 22-row tile, runs of
+// neighbouring rows, interleaved runs): 14x1920x1080 RGB8, 174 MB, 50.6, 44.7,
+// 43.0; with rt_frameset's estimate 66, 57.5, 55.7; the uneven rig of 4K, 1080p
+// and 16-bit cameras 110, 101, 96.  1x640x480 18.0 -> 10.6, and 5x1031x517 RGB8
+// + 3x333x251 u16 + 2x719x405 gray8 57 -> 16, which was the ragged row ends,
+// read byte by byte and row by row.
+//
+// Registers: at most 96 (RC_APPLY_WAVES 5), so that beside the four waves per
+// SIMD of two workgroups a seam-estimate wave finds room; at 108 the pipeline
+// of the 14x1920x1080 rig took 258.8 us per six frame-sets, at 96 250.5.
 #pragma once
 
 #include <type_traits>
@@ -209,10 +220,11 @@ __device__ inline bool cross_small(const Geo& g, const int64_t* q3, int k, int j
 }
 
 // Stages the maps of a piece of the run: entry e is block j0 + e, or with VB
-// row p0 + e (its two blocks' maps blended).
+// the run's row p0 + (e / lanes) stride + e % lanes (its two blocks' maps
+// blended).
 template <int C, int BPS, int KIND, bool VB>
 __device__ inline void stage_maps(const Geo& g, const Bufs& b, const int64_t* q3, const DevCam& cam, int k, int p0,
-                                  int j0, int n, ApplyLds& L) {
+                                  int stride, int j0, int n, ApplyLds& L) {
   const int nb = g.n_blocks, H = cam.height, tid = threadIdx.x;
   constexpr int kPer = KIND == kMapTable ? 2 * C * kNB / 4 : KIND >= kMapCross ? 2 * kX3 : 2 * C;
   if (!VB && tid < n) L.end[tid] = block_row(j0 + tid + 1, H, nb);
@@ -234,7 +246,7 @@ __device__ inline void stage_maps(const Geo& g, const Bufs& b, const int64_t* q3
       int64_t A, B;
       if (VB) {
         int ja, jb, v;
-        vblend_row(H, nb, p0 + e, ja, jb, v);
+        vblend_row(H, nb, min(H - 1, p0 + (e / cam.ap_lanes) * stride + e % cam.ap_lanes), ja, jb, v);
         const int64_t ua = unit_index(k, s, ja, c, nb), ub = unit_index(k, s, jb, c, nb);
         A = blend_q16(b.q16[ua * 2], b.q16[ub * 2], v);
         B = blend_q16(b.q16[ua * 2 + 1], b.q16[ub * 2 + 1], v);
@@ -364,100 +376,112 @@ __device__ inline void one_group(const uint32_t (&d)[C * BPS], uint32_t (&o)[C *
   }
 }
 
-// Rows [p0, p1) of the run, whose maps are staged.
+// The run's rows in [p0, p1), whose maps are staged: R0 + ln + i stride for
+// each of the workgroup's rows ln.  First the groups of four whole pixels on
+// one side of the centre, each thread down its columns; then the group across
+// the centre and the one at the row's ragged end, if any, a thread per row.
 template <int C, int BPS, int KIND, bool WRITE, bool STATS, bool VB>
 __device__ inline void piece_rows(const Geo& g, const Bufs& b, const DevCam& cam, int k, __amdgpu_buffer_rsrc_t rin,
-                                  __amdgpu_buffer_rsrc_t rout, int p0, int p1, ApplyLds& L, Sums16& sums) {
+                                  __amdgpu_buffer_rsrc_t rout, int R0, int step, int p0, int p1, int j0,
+                                  ApplyLds& L, Sums16& sums) {
   constexpr int NW = C * BPS;
+  constexpr int kU = KIND == kMapDirect || KIND == kMapCross ? kUnroll : 2;   // (rare maps: fewer registers)
   const int tid = threadIdx.x;
-  const int cols = cam.ap_cols, step = cam.ap_lanes;
-  const int ln = tid / cols, gc = tid - ln * cols;
-  if (ln >= step || p0 + ln >= p1) return;      // rows below are in [p0, p1), so inside a staged entry
+  const int cols = cam.ap_cols, lanes = cam.ap_lanes;
   const int W = cam.width, half = cam.half, pitch = (int)cam.pitch;
   const int ngroups = (W + 3) >> 2;
   const int hrep = tid & (kRep - 1);
   const int shift = cam.bit_depth - 8;
   const uint32_t maxv = (1u << cam.bit_depth) - 1u;
   const uint16_t* wrow = b.weights + (int64_t)k * g.w_max;
-  for (int grp = gc; grp < ngroups; grp += cols) {
-    const int col0 = grp * 4, npx = min(4, W - col0);
-    const int cbyte = col0 * NW;
-    uint32_t wp[4];
+  auto weights_of = [&](int col0, int npx, uint32_t (&wp)[4]) {
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
       const uint32_t w = WRITE && p < npx ? (uint32_t)wrow[col0 + p] : 0u;
       wp[p] = (256u - w) | (w << 16);
     }
-    int e = 0;     // staged entry of the row
-    auto entry_of = [&](int row) {
-      if (VB) {
-        e = row - p0;
-        return true;
-      }
-      if (row < L.end[e]) return false;
-      do ++e; while (row >= L.end[e]);     // blocks without rows are stepped over
-      return true;
-    };
-    const int side = col0 >= half ? 1 : 0;
-    if (npx == 4 && side == (col0 + 3 >= half ? 1 : 0)) {
+  };
+  const int ln = tid / cols;
+  int first = R0 + ln;                    // this thread's first row of the piece
+  if (first < p0) first += (p0 - first + step - 1) / step * step;
+  if (ln < lanes && first < p1) {         // so rows are in [p0, p1), inside a staged entry
+    // A step takes at least `skip` blocks on.
+    const int skip = (int)((uint32_t)step * (uint32_t)g.n_blocks / (uint32_t)cam.height);
+    for (int grp = tid - ln * cols; grp < ngroups; grp += cols) {
+      const int col0 = grp * 4;
+      const int side = col0 >= half ? 1 : 0;
+      if (col0 + 4 > W || (col0 < half && col0 + 3 >= half)) continue;
+      const int cbyte = col0 * NW;
+      uint32_t wp[4];
+      weights_of(col0, 4, wp);
+      // Staged entry of the row, rows taken in turn (every step-th): whether it
+      // is another one than before.
+      int e = VB ? (first - p0) / step * lanes + ln - lanes : -1;
+      auto next_entry = [&](int row) {
+        if (VB) {
+          e += lanes;
+          return true;
+        }
+        const int was = e;
+        e = e < 0 ? row_block(row, cam.height, g.n_blocks) - j0 : e + skip;
+        while (row >= L.end[e]) ++e;      // at most the block after, and blocks without rows
+        return e != was;
+      };
       SideMap<C, KIND> m;
-      if (WRITE && !VB) {
-        (void)entry_of(p0 + ln);
-        m.read(L, e, side);
-      }
-      for (int row = p0 + ln; row < p1; row += kUnroll * step) {
-        uint32_t d[kUnroll][NW];
+      for (int row = first; row < p1; row += kU * step) {
+        uint32_t d[kU][NW];
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u)
+        for (int u = 0; u < kU; ++u)
           if (row + u * step < p1) load_group<NW>(rin, (row + u * step) * pitch + cbyte, d[u]);
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
+        for (int u = 0; u < kU; ++u) {
           if (row + u * step < p1) {
-            if (WRITE && entry_of(row + u * step)) m.read(L, e, side);
+            if (WRITE && next_entry(row + u * step)) m.read(L, e, side);
             uint32_t o[NW];
             one_group<C, BPS, WRITE, STATS>(d[u], o, 4, m, wp, L, hrep, shift, maxv, sums);
             if (WRITE) store_group<NW>(rout, (row + u * step) * pitch + cbyte, o);
           }
         }
       }
-    } else {
-      // The group across the image centre or at the ragged end of the row:
-      // its pixels' maps are read per row and side.
-      constexpr int kU = 4;
-      for (int row = p0 + ln; row < p1; row += kU * step) {
-        uint32_t d[kU][NW];
-#pragma unroll
-        for (int u = 0; u < kU; ++u)
-          if (row + u * step < p1) load_part<NW>(rin, (row + u * step) * pitch + cbyte, npx * NW, d[u]);
+    }
+  }
+  const bool across = (half & 3) != 0, ragged = (W & 3) != 0;
+  if (!across && !ragged) return;
+  const int gc = half >> 2, gr = ngroups - 1;
+  const int per = across && ragged && gc != gr ? 2 : 1;      // such groups of a row
+  const int t0 = (p0 - R0) / step;                           // turns of the workgroup's rows in the piece
+  const int turns = (p1 - R0 + step - 1) / step - t0;
 #pragma unroll 1
-        for (int u = 0; u < kU; ++u) {
-          if (row + u * step < p1) {
-            uint32_t du[NW], o[NW];
+  for (int i = tid; i < turns * lanes * per; i += kApplyThreads) {
+    const int ri = i / per, turn = ri / lanes, l = ri - turn * lanes;
+    const int row = R0 + (t0 + turn) * step + l;
+    if (row < p0 || row >= p1) continue;
+    const int grp = i - ri * per == 0 && across ? gc : gr;
+    const int col0 = grp * 4, npx = min(4, W - col0);
+    const int side = col0 >= half ? 1 : 0;
+    const int off = row * pitch + col0 * NW;
+    uint32_t d[NW], o[NW], wp[4];
+    load_part<NW>(rin, off, npx * NW, d);
+    weights_of(col0, npx, wp);
+    SideMap<C, KIND> m;
+    const int e = VB ? ri : row_block(row, cam.height, g.n_blocks) - j0;
+    if (WRITE) m.read(L, e, side);
+    one_group<C, BPS, WRITE, STATS>(d, o, npx, m, wp, L, hrep, shift, maxv, sums);
+    if (WRITE) {
+      if (col0 < half && col0 + 3 >= half) {
+        // The pixels from half on, again with the right side's maps.
+        uint32_t q[NW];
+        m.read(L, e, 1);
+        one_group<C, BPS, WRITE, false>(d, q, npx, m, wp, L, hrep, shift, maxv, sums);
+        const int keep = (half - col0) * NW;                 // bytes of the left side's pixels
 #pragma unroll
-            for (int q = 0; q < NW; ++q) du[q] = u == 0 ? d[0][q] : u == 1 ? d[1][q] : u == 2 ? d[2][q] : d[3][q];
-            SideMap<C, KIND> m;
-            if (WRITE) {
-              (void)entry_of(row + u * step);
-              m.read(L, e, side);
-            }
-            one_group<C, BPS, WRITE, STATS>(du, o, npx, m, wp, L, hrep, shift, maxv, sums);
-            if (WRITE && col0 < half && col0 + 3 >= half) {
-              // The pixels from half on, again with the right side's maps.
-              uint32_t q[NW];
-              m.read(L, e, 1);
-              one_group<C, BPS, WRITE, false>(du, q, npx, m, wp, L, hrep, shift, maxv, sums);
-              const int keep = (half - col0) * NW;      // bytes of the left side's pixels
-#pragma unroll
-              for (int i = 0; i < NW; ++i) {
-                const int n = min(max(keep - 4 * i, 0), 4);
-                const uint32_t mask = n == 4 ? ~0u : (1u << (8 * n)) - 1u;
-                o[i] = (o[i] & mask) | (q[i] & ~mask);
-              }
-            }
-            if (WRITE) store_part<NW>(rout, (row + u * step) * pitch + cbyte, npx * NW, o);
-          }
+        for (int n = 0; n < NW; ++n) {
+          const int kept = min(max(keep - 4 * n, 0), 4);
+          const uint32_t mask = kept == 4 ? ~0u : (1u << (8 * kept)) - 1u;
+          o[n] = (o[n] & mask) | (q[n] & ~mask);
         }
       }
+      store_part<NW>(rout, off, npx * NW, o);
     }
   }
 }
@@ -499,12 +523,12 @@ __device__ inline void flush_whole(const Bufs& b, int k, ApplyLds& L, const Sums
   if (tid < 3 * C && L.sums[tid]) atomicAdd((unsigned long long*)&b.whole_sums[(int64_t)k * 9 + tid], L.sums[tid]);
 }
 
-// Rows [R0, R1) of camera k, of C channels of BPS bytes.  CROSS: the 3x3 maps
-// q3 in place of the affine ones.
+// The run's rows R0 + ln + i stride (ln < ap_lanes) below R1 of camera k, of C
+// channels of BPS bytes.  CROSS: the 3x3 maps q3 in place of the affine ones.
 template <int C, int BPS, bool WRITE, bool STATS, bool VB, bool CROSS, class FP>
 __device__ __attribute__((always_inline)) inline void apply_rows(const Geo& g, const FP& fp, const Bufs& b,
                                                                  const int64_t* q3, const DevCam& cam, int k, int R0,
-                                                                 int R1, ApplyLds& L) {
+                                                                 int R1, int stride, ApplyLds& L) {
   const int tid = threadIdx.x, H = cam.height, nb = g.n_blocks;
   if (STATS) {
     const u32x4 zero = {0, 0, 0, 0};
@@ -520,19 +544,20 @@ __device__ __attribute__((always_inline)) inline void apply_rows(const Geo& g, c
     constexpr int KIND = decltype(kind)::value;
     constexpr int kCap = MapEntry<KIND, C>::kCap;
     while (p0 < pe) {
-      const int j0 = row_block(p0, H, nb);
-      int p1 = pe, n;
+      int j0 = 0, p1, n;
       if (VB) {
-        p1 = min(pe, p0 + kCap);
-        n = p1 - p0;
+        const int turns = max(1, kCap / cam.ap_lanes);      // of the workgroup's rows
+        p1 = min(pe, p0 + turns * stride);
+        n = min(turns, (p1 - p0 + stride - 1) / stride) * cam.ap_lanes;
       } else {
+        j0 = row_block(p0, H, nb);
         n = min(kCap, row_block(pe - 1, H, nb) - j0 + 1);
         p1 = min(pe, block_row(j0 + n, H, nb));
       }
       if (p0 != R0) __syncthreads();    // the previous piece's rows are done with the maps
-      if (WRITE) stage_maps<C, BPS, KIND, VB>(g, b, q3, cam, k, p0, j0, n, L);
+      if (WRITE) stage_maps<C, BPS, KIND, VB>(g, b, q3, cam, k, p0, stride, j0, n, L);
       __syncthreads();
-      piece_rows<C, BPS, KIND, WRITE, STATS, VB>(g, b, cam, k, rin, rout, p0, p1, L, sums);
+      piece_rows<C, BPS, KIND, WRITE, STATS, VB>(g, b, cam, k, rin, rout, R0, stride, p0, p1, j0, L, sums);
       p0 = p1;
     }
   };
@@ -570,15 +595,16 @@ __device__ __attribute__((always_inline)) inline void apply_run(const Geo& g, co
     if (!cam_active(g, k)) continue;              // uniform over the workgroup
     const DevCam cam = uniform_cam(g, k);
     const int r0 = k == run.cam0 ? run.row0 : 0, r1 = k == run.cam1 ? run.row1 : cam.height;
+    const int stride = max(run.stride, cam.ap_lanes);
     if (r0 >= r1) continue;
     if constexpr (CROSS) {
-      apply_rows<3, 1, WRITE, STATS, VB, true>(g, fp, b, q3, cam, k, r0, r1, L);
+      apply_rows<3, 1, WRITE, STATS, VB, true>(g, fp, b, q3, cam, k, r0, r1, stride, L);
     } else if (cam.bps == 2) {
-      apply_rows<1, 2, WRITE, STATS, VB, false>(g, fp, b, q3, cam, k, r0, r1, L);
+      apply_rows<1, 2, WRITE, STATS, VB, false>(g, fp, b, q3, cam, k, r0, r1, stride, L);
     } else if (cam.channels == 3) {
-      apply_rows<3, 1, WRITE, STATS, VB, false>(g, fp, b, q3, cam, k, r0, r1, L);
+      apply_rows<3, 1, WRITE, STATS, VB, false>(g, fp, b, q3, cam, k, r0, r1, stride, L);
     } else {
-      apply_rows<1, 1, WRITE, STATS, VB, false>(g, fp, b, q3, cam, k, r0, r1, L);
+      apply_rows<1, 1, WRITE, STATS, VB, false>(g, fp, b, q3, cam, k, r0, r1, stride, L);
     }
     if (k < run.cam1) __syncthreads();
   }

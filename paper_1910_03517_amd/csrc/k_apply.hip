@@ -8,7 +8,7 @@
 namespace rc {
 
 #ifndef RC_APPLY_WAVES
-#define RC_APPLY_WAVES 4
+#define RC_APPLY_WAVES 5
 #endif
 // Workgroup w takes its run of rows (apply_run); no workgroup waits for
 // another.  VBLEND: the maps of adjacent blocks blended row by row (a kernel

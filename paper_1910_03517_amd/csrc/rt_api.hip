@@ -85,6 +85,7 @@ rt_status hip_fail(hipError_t e, const char* what) {
 constexpr int kMaxDim = 32768;
 constexpr int kDefaultTileRows = 32;
 constexpr int kMaxApplyGrid = 1 << 16;
+constexpr int kVblendLanes = 32;   // rows whose blended maps fit the staging area in every form
 // Apply workgroups of the default split, two per compute unit.  Measured on
 // the 14x1920x1080 rig (us per frame-set, both kernels): 512 of 512 threads
 // 60.6, 768 69.9, 256 of 1024 threads 75.2, 1024 of 256 threads 59.7 (but 45.1
@@ -155,13 +156,13 @@ rt_status check_active(const rt_ctx* ctx, uint64_t active) {
 // How an apply workgroup lies over the rows of camera d: ap_cols groups of 4
 // pixels by ap_lanes rows, the split of the row into equal column chunks (at
 // most 8) that keeps most of its threads busy.
-static void lay_apply(DevCam& d) {
+static void lay_apply(DevCam& d, int max_lanes) {
   const int groups = (d.width + 3) / 4;
   int64_t best = -1;
   for (int chunks = 1; chunks <= 8 || best < 0; ++chunks) {
     const int cols = (groups + chunks - 1) / chunks;
     if (cols > kApplyThreads) continue;
-    const int lanes = kApplyThreads / cols;
+    const int lanes = std::min(kApplyThreads / cols, max_lanes);
     // Groups taken per pass of the workgroup over a chunk, of equal worth at
     // equal use: the fewest chunks win.
     const int64_t use = (int64_t)groups * lanes * 1024 / chunks;
@@ -200,7 +201,7 @@ static rt_status build_tables(rt_ctx* ctx, int tile_rows, int grid) {
       const int parts = (rows + tile_rows - 1) / tile_rows;
       segments += parts;
       for (int p = 0; one_run_each && p < parts; ++p)
-        runs.push_back(WgRun{k, b0 + (int)((int64_t)p * rows / parts), k, b0 + (int)((int64_t)(p + 1) * rows / parts)});
+        runs.push_back(WgRun{k, b0 + (int)((int64_t)p * rows / parts), k, b0 + (int)((int64_t)(p + 1) * rows / parts), 0});
     }
   };
   int64_t total = 0;
@@ -226,13 +227,17 @@ static rt_status build_tables(rt_ctx* ctx, int tile_rows, int grid) {
     for (int i = 0; given < G; ++i, ++given) ++n[-rem[i].second];
     for (int k = 0; k < n_cams; ++k) {
       const int H = ctx->cams[k].height;
+      if (own) tiles(k, 0, H, false);
       const int step = own ? ctx->hcams[k].ap_lanes : 1;
       const int steps = (H + step - 1) / step;
       const int m = own ? std::min(n[k], steps) : n[k];
       for (int i = 0; i < m; ++i) {
-        const int a = std::min(H, (int)((int64_t)i * steps / m) * step);
-        const int e = std::min(H, (int)((int64_t)(i + 1) * steps / m) * step);
-        runs.push_back(WgRun{k, a, k, e});
+        if (own) {      // every m-th step
+          runs.push_back(WgRun{k, i * step, k, H, m * step});
+          continue;
+        }
+        const int a = (int)((int64_t)i * H / m), e = (int)((int64_t)(i + 1) * H / m);
+        runs.push_back(WgRun{k, a, k, e, 0});
         tiles(k, a, e, false);
       }
     }
@@ -258,7 +263,7 @@ static rt_status build_tables(rt_ctx* ctx, int tile_rows, int grid) {
       share_start(w + 1, c1, r1s);
       // A share that ends at a camera's first row ends with the camera before.
       const bool back = r1s == 0 && c1 > c0;
-      runs.push_back(WgRun{c0, r0s, back ? c1 - 1 : std::min(c1, n_cams - 1), back ? ctx->cams[c1 - 1].height : r1s});
+      runs.push_back(WgRun{c0, r0s, back ? c1 - 1 : std::min(c1, n_cams - 1), back ? ctx->cams[c1 - 1].height : r1s, 0});
       for (int k = c0; k <= c1 && k < n_cams; ++k)
         tiles(k, k == c0 ? r0s : 0, k == c1 ? r1s : ctx->cams[k].height, false);
       c0 = c1;
@@ -389,7 +394,7 @@ rt_status rt_ctx_create(const rt_camera_desc* cams, int32_t n_cams, const rt_opt
     d.band = std::min(o.band_width, d.half);
     d.row_bytes = c.width * c.channels * d.bps;
     d.pitch = c.pitch_bytes;
-    lay_apply(d);
+    lay_apply(d, o.vblend ? kVblendLanes : kApplyThreads);
     // Ring neighbours: right side of position p meets the left side of p + 1.
     int m = 0;
     for (int i = 0; i < n_cams; ++i) m += cams[i].ring == c.ring;

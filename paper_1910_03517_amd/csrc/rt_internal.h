@@ -32,10 +32,12 @@ struct DevCam {
   int64_t pitch;         // bytes between rows
 };
 
-// The run of an apply workgroup: from row row0 of camera cam0 up to row row1
-// (exclusive) of camera cam1, whole cameras between them.
+// The run of an apply workgroup: rows from row row0 of camera cam0 up to row
+// row1 (exclusive) of camera cam1, whole cameras between them.  It takes a
+// camera's ap_lanes rows at a time; stride 0: one such step after the other, so
+// every row; else the steps start `stride` rows apart.
 struct WgRun {
-  int32_t cam0, row0, cam1, row1;
+  int32_t cam0, row0, cam1, row1, stride;
 };
 
 // Frame pointers of one launch, passed by value as a kernel argument.
