@@ -138,6 +138,25 @@ __device__ inline bool fit_cross(const Geo& g, const uint64_t* os, const uint64_
   return true;
 }
 
+// The state p (12 parameters; had: it holds an estimate) of a unit after its
+// fit m (fresh) or without one; returns its new valid flag.
+__device__ inline uint8_t cross_step(const Geo& g, bool faces, bool fresh, bool had, const double (&m)[kX3],
+                                     double (&p)[kX3]) {
+  if (!fresh) {
+    if (faces && had) return 1;                 // no estimate: keep the state
+    for (int i = 0; i < kX3; ++i) p[i] = (i < 9 && i % 4 == 0) ? 1.0 : 0.0;
+    return faces ? 0 : 1;                       // identity without a facing band
+  }
+  const bool blend = g.mode == RT_MODE_SMOOTHING && had;
+  const double keep = 1.0 - g.alpha;
+  for (int i = 0; i < kX3; ++i) {
+    const double tp = keep * p[i];
+    const double tn = g.alpha * m[i];
+    p[i] = blend ? tp + tn : m[i];
+  }
+  return 1;
+}
+
 // One thread per (camera, side, block): fit, then the temporal step.
 __global__ __launch_bounds__(kThreads) void k_estimate_cross(Geo g, Bufs b, CrossBufs x) {
   const int nb = g.n_blocks;
@@ -146,29 +165,57 @@ __global__ __launch_bounds__(kThreads) void k_estimate_cross(Geo g, Bufs b, Cros
   const int k = u / (2 * nb), s = (u / nb) & 1, j = u % nb;
   if (!cam_active(g, k)) return;
   const DevCam& cam = g.cams[k];
-  double* p = x.params3 + (int64_t)u * kX3;
-  const bool had = x.valid3[u] != 0;
-  double m[kX3];
+  double p[kX3], m[kX3];
+  for (int i = 0; i < kX3; ++i) p[i] = x.params3[(int64_t)u * kX3 + i];
   const int fc = cam.face_cam[s];
   const int64_t uf = fc < 0 ? -1 : ((int64_t)fc * 2 + cam.face_side[s]) * nb + j;
   const bool fresh = uf >= 0 && fit_cross(g, b.band_sums + (int64_t)u * kCS * 3, x.cross + (int64_t)u * 3,
                                           b.band_sums + uf * kCS * 3, x.cross + uf * 3, m);
-  if (!fresh) {
-    if (uf >= 0 && had) return;                 // no estimate: keep the state
-    for (int i = 0; i < kX3; ++i) p[i] = (i < 9 && i % 4 == 0) ? 1.0 : 0.0;
-    x.valid3[u] = uf < 0 ? 1 : 0;               // identity without a facing band
-    return;
+  x.valid3[u] = cross_step(g, uf >= 0, fresh, x.valid3[u] != 0, m, p);
+  for (int i = 0; i < kX3; ++i) x.params3[(int64_t)u * kX3 + i] = p[i];
+}
+
+// Band statistics, cross sums, fit and fixed-point maps of a frame-set in one
+// launch, one workgroup of NT threads per seam block (see Seam; the whole-frame
+// statistics that the apply accumulates are cleared here too): the same
+// results as k_band_stats, k_cross_stats, k_estimate_cross, k_build_cross and
+// k_weights in sequence, which took 35 us of launches and dependent reads
+// beside the 62 us apply of the 14x1920x1080 rig; this takes 16 us.
+template <int NT>
+__global__ __launch_bounds__(NT) void k_seam_cross(Geo g, FramePtrs fp, Bufs b, CrossBufs x) {
+  __shared__ BandLds bands[2];
+  __shared__ uint64_t sums[3][9], cross[3][9];
+  const int nb = g.n_blocks, tid = threadIdx.x;
+  const int k = (int)blockIdx.x / nb, j = (int)blockIdx.x - k * nb;
+  zero_whole(g, b, blockIdx.x * NT + tid, gridDim.x * NT);
+  if (!cam_active(g, k)) return;
+  const DevCam cam = uniform_cam(g, k);
+  const Seam sm = seam_of(g, cam, k, j);
+  // Thread 64 t fits unit t; its state is read ahead of the band passes.
+  const int t = tid / kWave;
+  const bool fitter = tid % kWave == 0 && t < sm.n;
+  const int u = t == 0 ? sm.u[0] : (t == 1 ? sm.u[1] : sm.u[2]);
+  double p[kX3], m[kX3];
+  bool had = false;
+  if (fitter) {
+    for (int i = 0; i < kX3; ++i) p[i] = x.params3[(int64_t)u * kX3 + i];
+    had = x.valid3[u] != 0;
   }
-  if (g.mode == RT_MODE_SMOOTHING && had) {
-    const double keep = 1.0 - g.alpha;
+  seam_bands<NT, kBandCross>(g, fp, b, BandArgs{nullptr, nullptr, x.cross}, sm, bands, sums, cross);
+  if (fitter) {
+    const bool faces = sm.faces && t < 2;
+    const int o = t == 0 ? 1 : 0;
+    const bool fresh = faces && fit_cross(g, sums[t], cross[t], sums[o], cross[o], m);
+    x.valid3[u] = cross_step(g, faces, fresh, had, m, p);
     for (int i = 0; i < kX3; ++i) {
-      const double tp = keep * p[i];
-      const double tn = g.alpha * m[i];
-      m[i] = tp + tn;
+      x.params3[(int64_t)u * kX3 + i] = p[i];
+      x.q3[(int64_t)u * kX3 + i] = q16_of(p[i]);
     }
   }
-  for (int i = 0; i < kX3; ++i) p[i] = m[i];
-  x.valid3[u] = 1;
+  // The camera's blend weights, shared by its seam blocks.
+  const int w1 = (int)((int64_t)(j + 1) * g.w_max / nb);
+  for (int col = (int)((int64_t)j * g.w_max / nb) + tid; col < w1; col += NT)
+    x.weights[(int64_t)k * g.w_max + col] = (uint16_t)blend_weight(cam.width, col);
 }
 
 // q3 = round_half_even(params3 * 65536), one thread per parameter.
@@ -176,7 +223,7 @@ __global__ __launch_bounds__(kThreads) void k_build_cross(Geo g, CrossBufs x) {
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (i >= (int64_t)g.n_cams * 2 * g.n_blocks * kX3) return;
   if (!cam_active(g, (int)(i / ((int64_t)2 * g.n_blocks * kX3)))) return;
-  x.q3[i] = (int64_t)__builtin_rint(x.params3[i] * 65536.0);
+  x.q3[i] = q16_of(x.params3[i]);
 }
 
 // ----------------------------------------------------------------- apply
@@ -192,6 +239,12 @@ __global__ __launch_bounds__(kApplyThreads) void k_apply_cross(Geo g, FramePtrs 
 
 hipError_t launch_cross_stats(const Geo& g, const FramePtrs& fp, const CrossBufs& x, hipStream_t st) {
   hipLaunchKernelGGL(k_cross_stats, dim3(g.n_cams * 2 * g.n_blocks), dim3(kThreads), 0, st, g, fp, x);
+  return hipGetLastError();
+}
+
+hipError_t launch_seam_cross(const Geo& g, const FramePtrs& fp, const Bufs& b, const CrossBufs& x, hipStream_t st) {
+  constexpr int kNT = 256;
+  hipLaunchKernelGGL(k_seam_cross<kNT>, dim3(g.n_cams * g.n_blocks), dim3(kNT), 0, st, g, fp, b, x);
   return hipGetLastError();
 }
 

@@ -1736,11 +1736,7 @@ rt_status rt_frameset_cross(rt_ctx* ctx, const void* const* frames, void* const*
   const FramePtrs fp = make_ptrs(ctx, frames, out_frames);
   const Bufs b = make_bufs(stats, nullptr, nullptr);
   const CrossBufs xb = make_cross(x);
-  hipError_t e = launch_band_stats(g, fp, b, st);
-  if (e == hipSuccess) e = launch_cross_stats(g, fp, xb, st);
-  if (e == hipSuccess) e = launch_estimate_cross(g, b, xb, st);
-  if (e == hipSuccess) e = launch_build_cross(g, xb, st);
-  if (e == hipSuccess) e = launch_zero_whole(g, b, st);
+  hipError_t e = launch_seam_cross(g, fp, b, xb, st);
   if (e == hipSuccess) e = launch_apply_cross(g, fp, b, xb, true, st);
   return e == hipSuccess ? RT_OK : hip_fail(e, "cross-channel frame-set");
 }

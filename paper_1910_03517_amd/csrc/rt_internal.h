@@ -176,6 +176,7 @@ hipError_t launch_apply_sets(const Geo& g, const SetPtrs& sp, hipStream_t st, hi
 hipError_t launch_zero_whole(const Geo& g, const Bufs& b, hipStream_t st);
 hipError_t launch_weights(const Geo& g, const Bufs& b, hipStream_t st);
 hipError_t launch_cross_stats(const Geo& g, const FramePtrs& fp, const CrossBufs& x, hipStream_t st);
+hipError_t launch_seam_cross(const Geo& g, const FramePtrs& fp, const Bufs& b, const CrossBufs& x, hipStream_t st);
 hipError_t launch_estimate_cross(const Geo& g, const Bufs& b, const CrossBufs& x, hipStream_t st);
 hipError_t launch_build_cross(const Geo& g, const CrossBufs& x, hipStream_t st);
 hipError_t launch_apply_cross(const Geo& g, const FramePtrs& fp, const Bufs& b, const CrossBufs& x, bool stats,
