@@ -180,10 +180,10 @@ __global__ __launch_bounds__(kThreads) void k_estimate_cross(Geo g, Bufs b, Cros
 // statistics that the apply accumulates are cleared here too): the same
 // results as k_band_stats, k_cross_stats, k_estimate_cross, k_build_cross and
 // k_weights in sequence, which took 35 us of launches and dependent reads
-// beside the 62 us apply of the 14x1920x1080 rig; this takes 16 us.
+// beside the 62 us apply of the 14x1920x1080 rig; this takes 9 us.
 template <int NT>
 __global__ __launch_bounds__(NT) void k_seam_cross(Geo g, FramePtrs fp, Bufs b, CrossBufs x) {
-  __shared__ BandLds bands[2];
+  __shared__ BandLds<kBandRep> bands[2];
   __shared__ uint64_t sums[3][9], cross[3][9];
   const int nb = g.n_blocks, tid = threadIdx.x;
   const int k = (int)blockIdx.x / nb, j = (int)blockIdx.x - k * nb;
@@ -243,7 +243,7 @@ hipError_t launch_cross_stats(const Geo& g, const FramePtrs& fp, const CrossBufs
 }
 
 hipError_t launch_seam_cross(const Geo& g, const FramePtrs& fp, const Bufs& b, const CrossBufs& x, hipStream_t st) {
-  constexpr int kNT = 256;
+  constexpr int kNT = 512;
   hipLaunchKernelGGL(k_seam_cross<kNT>, dim3(g.n_cams * g.n_blocks), dim3(kNT), 0, st, g, fp, b, x);
   return hipGetLastError();
 }

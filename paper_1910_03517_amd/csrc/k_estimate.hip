@@ -56,6 +56,8 @@ __global__ __launch_bounds__(kThreads) void k_weights(Geo g, Bufs b) {
   if (cam_active(g, k)) b.weights[i] = (uint16_t)blend_weight(g.cams[k].width, col);
 }
 
+constexpr int kBesideRep = 4;   // histogram replicas beside applies
+
 // Band statistics, estimate and tables of a frame-set in one launch, one
 // workgroup of NT threads per seam block (see Seam).  A unit's estimate needs
 // only its own band and the one it faces, so after the statistics of its
@@ -73,19 +75,20 @@ __global__ __launch_bounds__(kThreads) void k_weights(Geo g, Bufs b) {
 // half of the workgroup with all of its loads in flight at once, one wave per
 // channel sums a histogram, the fixed-point maps pass through LDS and the
 // tables are built four entries per thread.  Measured on MI355X against the
-// bands one after the other (us): 17.6 -> 13.6 on that rig, 10.5 -> 8.4 on
-// 1x640x480; with object removal, whose groups were loaded one at a time, 38.4
-// -> 15.5.
+// bands one after the other (us): 17.6 -> 13.6 on that rig, and 7.6 with the
+// histogram in replicas (see BandLds); with object removal, whose groups were
+// loaded one at a time, 38.4 -> 15.5 -> 11.0.
+template <int REP>
 struct SeamLds {
-  BandLds band[2];
+  BandLds<REP> band[2];
   uint64_t sums[3][9];     // (n, S1, S2) per channel of the units taken
   uint64_t extra[3][9];    // the same over their kept pixels
   int64_t q[3][kCS][2];    // their Q16 maps after the fit
 };
 
-template <int NT, int WHAT, bool QFIT>
+template <int NT, int WHAT, bool QFIT, class Lds>
 __device__ __attribute__((always_inline)) inline void band_estimate_body(const Geo& g, const FramePtrs& fp,
-                                                                         const BandArgs& a, const Bufs& b, SeamLds& L,
+                                                                         const BandArgs& a, const Bufs& b, Lds& L,
                                                                          int bid, int nblk) {
   constexpr bool kMotion = WHAT == kBandMotion;
   static_assert(!(kMotion && QFIT), "object removal keeps only the moments of the kept pixels");
@@ -177,22 +180,22 @@ __device__ __attribute__((always_inline)) inline void band_estimate_body(const G
   }
 }
 
-template <int NT, bool QFIT>
+template <int NT, int REP, bool QFIT>
 __global__ __launch_bounds__(NT) void k_band_estimate(Geo g, FramePtrs fp, Bufs b) {
-  __shared__ SeamLds L;
+  __shared__ SeamLds<REP> L;
   band_estimate_body<NT, kBandPlain, QFIT>(g, fp, BandArgs{}, b, L, (int)blockIdx.x, (int)gridDim.x);
 }
 
 template <int NT>
 __global__ __launch_bounds__(NT) void k_band_estimate_removal(Geo g, FramePtrs fp, PrevPtrs pp, Bufs b, Removal rm) {
-  __shared__ SeamLds L;
+  __shared__ SeamLds<kBandRep> L;
   band_estimate_body<NT, kBandMotion, false>(g, fp, BandArgs{&pp, &rm, nullptr}, b, L, (int)blockIdx.x,
                                              (int)gridDim.x);
 }
 
 // Band statistics with the kept sums, one workgroup per (camera, side, block).
 __global__ __launch_bounds__(kThreads) void k_motion_stats(Geo g, FramePtrs fp, PrevPtrs pp, Bufs b, Removal rm) {
-  __shared__ BandLds L;
+  __shared__ BandLds<kBandRep> L;
   const int unit = (int)blockIdx.x;
   if (!cam_active(g, unit / (2 * g.n_blocks))) return;
   band_unit<kThreads, kBandMotion>(g, fp, b, BandArgs{&pp, &rm, nullptr}, unit, L, nullptr, nullptr, (int)threadIdx.x);
@@ -235,7 +238,7 @@ __global__ __launch_bounds__(kThreads) void k_estimate_removal(Geo g, Bufs b, Re
 // chain the estimates in order.
 union AheadLds {
   ApplyLds a;
-  SeamLds s;
+  SeamLds<kBesideRep> s;
 };
 template <bool VBLEND, bool QFIT>
 __global__ __launch_bounds__(kApplyThreads) void k_frameset_ahead(Geo g, FramePtrs fa, Bufs ba, FramePtrs fe, Bufs be,
@@ -265,31 +268,26 @@ hipError_t launch_frameset_ahead(const Geo& g, const FramePtrs* fa, const Bufs& 
   return hipGetLastError();
 }
 
-// Threads of the seam kernel.  Rigs of few seam blocks leave most of the chip
-// idle, so the wide form's shorter passes count there; beside the applies of a
-// pipeline the narrow one fits more easily on busy compute units.
-#ifndef RC_WIDE_BLOCKS
-#define RC_WIDE_BLOCKS 64
-#endif
-constexpr int kWideSeamBlocks = RC_WIDE_BLOCKS, kNarrow = 256, kWide = 512;
+// Alone on the chip the seam kernel takes the wide form, whose passes are
+// shorter; beside the applies of a pipeline fewer threads and less LDS find
+// room on busy compute units sooner.  14x1920x1080 rig: rt_frameset 48.8 us
+// wide, 49.1 narrow with 8 replicas, 49.9 with 4; six frame-sets through the
+// pipeline 240.4, 241.3 and 234.0 us.
+constexpr int kNarrow = 256, kWide = 512;
 
-hipError_t launch_band_estimate(const Geo& g, const FramePtrs& fp, const Bufs& b, hipStream_t st) {
-  const int blocks = g.n_cams * g.n_blocks;
-  const bool wide = blocks <= kWideSeamBlocks, q = g.fit == RT_FIT_QUANTILE;
-  const dim3 grid(blocks), block(wide ? kWide : kNarrow);
-  if (wide && q) hipLaunchKernelGGL((k_band_estimate<kWide, true>), grid, block, 0, st, g, fp, b);
-  else if (wide) hipLaunchKernelGGL((k_band_estimate<kWide, false>), grid, block, 0, st, g, fp, b);
-  else if (q) hipLaunchKernelGGL((k_band_estimate<kNarrow, true>), grid, block, 0, st, g, fp, b);
-  else hipLaunchKernelGGL((k_band_estimate<kNarrow, false>), grid, block, 0, st, g, fp, b);
+hipError_t launch_band_estimate(const Geo& g, const FramePtrs& fp, const Bufs& b, hipStream_t st, bool beside) {
+  const bool q = g.fit == RT_FIT_QUANTILE;
+  const dim3 grid(g.n_cams * g.n_blocks), block(beside ? kNarrow : kWide);
+  if (beside && q) hipLaunchKernelGGL((k_band_estimate<kNarrow, kBesideRep, true>), grid, block, 0, st, g, fp, b);
+  else if (beside) hipLaunchKernelGGL((k_band_estimate<kNarrow, kBesideRep, false>), grid, block, 0, st, g, fp, b);
+  else if (q) hipLaunchKernelGGL((k_band_estimate<kWide, kBandRep, true>), grid, block, 0, st, g, fp, b);
+  else hipLaunchKernelGGL((k_band_estimate<kWide, kBandRep, false>), grid, block, 0, st, g, fp, b);
   return hipGetLastError();
 }
 
 const void* band_estimate_kernel(const Geo& g) {
-  const bool wide = g.n_cams * g.n_blocks <= kWideSeamBlocks, q = g.fit == RT_FIT_QUANTILE;
-  if (wide && q) return reinterpret_cast<const void*>(&k_band_estimate<kWide, true>);
-  if (wide) return reinterpret_cast<const void*>(&k_band_estimate<kWide, false>);
-  if (q) return reinterpret_cast<const void*>(&k_band_estimate<kNarrow, true>);
-  return reinterpret_cast<const void*>(&k_band_estimate<kNarrow, false>);
+  if (g.fit == RT_FIT_QUANTILE) return reinterpret_cast<const void*>(&k_band_estimate<kWide, kBandRep, true>);
+  return reinterpret_cast<const void*>(&k_band_estimate<kWide, kBandRep, false>);
 }
 
 hipError_t launch_band_estimate_removal(const Geo& g, const FramePtrs& fp, const PrevPtrs& pp, const Bufs& b,

@@ -5,7 +5,7 @@
 namespace rc {
 
 __global__ __launch_bounds__(kThreads) void k_band_stats(Geo g, FramePtrs fp, Bufs b) {
-  __shared__ BandLds L;
+  __shared__ BandLds<kBandRep> L;
   const int unit = (int)blockIdx.x;
   if (!cam_active(g, unit / (2 * g.n_blocks))) return;
   band_unit<kThreads, kBandPlain>(g, fp, b, BandArgs{}, unit, L, nullptr, nullptr, (int)threadIdx.x);

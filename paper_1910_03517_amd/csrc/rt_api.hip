@@ -1206,7 +1206,7 @@ static rt_status pipe_submit(rt_pipe* p, uint64_t active, const void* const* fra
       for (int k = 0; k < ctx->n_cams; ++k)
         if ((active >> k) & 1ull) p->prev_in[k] = fp.in[k];
   } else if (e == hipSuccess) {
-    e = launch_band_estimate(g, fp, be, p->s_est);
+    e = launch_band_estimate(g, fp, be, p->s_est, true);
   }
   if (e == hipSuccess) {
     p->pending.push_back({fp, active, (hipEvent_t)done_event, slot, (int)(p->submitted % p->lanes)});
