@@ -1585,15 +1585,8 @@ rt_status rt_mlp_train(const rt_mlp* w, const rt_mlp* grad, const rt_mlp* m, con
   hipError_t e = hipSuccess;
   for (int s = 0; e == hipSuccess && s < n_steps; ++s) {
     const int32_t* ix = idx + (int64_t)s * batch;
-    // The per-step calls' sequence with the two gathers in one launch and the
-    // loss gradient computed by the output layer (the same arithmetic).
-    e = gather_rows2(X, kMlpIn, work->xb, T, kMlpOut, work->tb, ix, batch, st);
-    if (e == hipSuccess) e = mlp_forward(wp, work->xb, batch, work->h1, work->h2, work->y, st, work->tb, work->dy);
-    if (e == hipSuccess)
-      e = mlp_backward(wp, work->xb, work->h1, work->h2, work->y, work->tb, batch, gp, work->dy, work->dz1,
-                       work->dz2, st, true);
-    if (e == hipSuccess) e = mlp_adam(wp, gp, mp, vp, step0 + s, lr, beta1, beta2, eps, st);
-    if (e == hipSuccess) e = mlp_mse(work->y, work->tb, batch, losses + s, st);
+    e = mlp_train_step(wp, gp, mp, vp, X, T, ix, batch, step0 + s, lr, beta1, beta2, eps, work->xb, work->tb, work->h1,
+                       work->h2, work->y, work->dy, work->dz1, work->dz2, losses + s, st);
   }
   return e == hipSuccess ? RT_OK : hip_fail(e, "mlp train");
 }
