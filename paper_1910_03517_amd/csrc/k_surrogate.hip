@@ -13,17 +13,16 @@ namespace rc {
 // as given, own band, facing band), channels, 64 bins = 64 * (sum of 4
 // adjacent 256-bins) / the region-channel's count, computed in binary64 and
 // rounded once to float32.  Rows of non-RGB cameras are zero.
-// Features of unit u3 (one workgroup): wave w takes the region-channel pairs
+// kThreads threads (tid: the thread's index among them): wave w takes the region-channel pairs
 // rc = w, w + 4, w + 8 (rc = 3 r + c, features rc * 64 .. rc * 64 + 63); lane
 // l holds bin l's four 256-bins, and the pair's count is the wave's sum.
-__device__ __forceinline__ void features_unit(const Geo& g, const uint32_t* __restrict__ band_hist,
+__device__ __forceinline__ void features_unit(const Geo& g, const uint32_t* band_hist,
                                               const uint32_t* __restrict__ whole_hist, float* __restrict__ X,
-                                              int u3) {
+                                              int u3, int tid) {
   const int nb = g.n_blocks;
   const int k = u3 / (2 * nb);
   const int s = (u3 / nb) & 1;
   const int j = u3 % nb;
-  const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   const DevCam& cam = g.cams[k];
   float* out = X + (int64_t)u3 * kMlpIn;
@@ -50,7 +49,7 @@ __global__ __launch_bounds__(kThreads) void k_features(Geo g, const uint32_t* __
                                                        const uint32_t* __restrict__ whole_hist, float* __restrict__ X) {
   const int u3 = blockIdx.x;
   if (!cam_active(g, u3 / (2 * g.n_blocks))) return;
-  features_unit(g, band_hist, whole_hist, X, u3);
+  features_unit(g, band_hist, whole_hist, X, u3, (int)threadIdx.x);
 }
 
 // The plain estimate of every (camera, side, block, channel) before the temporal step.
@@ -132,56 +131,111 @@ __global__ __launch_bounds__(kThreads) void k_select(Geo g, const float* __restr
   select_unit(g, Y, p_new, status, tol, params, valid, used, residual, u3);
 }
 
-// Surrogate frame-set, step 1 (one workgroup per unit u3): the unit's
-// features, and its three channels' plain estimate (three lanes of the last wave).
-__global__ __launch_bounds__(kThreads) void k_features_new(Geo g, const uint32_t* __restrict__ band_hist,
-                                                           const uint64_t* __restrict__ band_sums,
-                                                           const uint32_t* __restrict__ whole_hist,
-                                                           float* __restrict__ X, double* __restrict__ p_new,
-                                                           int32_t* __restrict__ status) {
-  const int u3 = blockIdx.x;
-  if (!cam_active(g, u3 / (2 * g.n_blocks))) return;
-  const int tid = threadIdx.x - (kThreads - kWave);   // the last wave, which has the fewest feature pairs
-  if (tid >= 0 && tid < kCS) {
-    const int u = u3 * kCS + tid;
-    double a, b;
-    status[u] = fit_new(g, band_sums, u, a, b);
-    p_new[(int64_t)u * 2] = a;
-    p_new[(int64_t)u * 2 + 1] = b;
+// Surrogate frame-set, step 1, one workgroup of 2 kThreads threads per seam
+// block (see Seam): the band statistics of its units, then, each half taking
+// units in turn, their features from the histograms just written, and their
+// plain estimate from the sums in LDS.  One launch less than band statistics and
+// features one after the other (10 us with the gap on the 14x1920x1080 rig; this
+// 7.6).
+__global__ __launch_bounds__(2 * kThreads) void k_seam_features(Geo g, FramePtrs fp, Bufs b,
+                                                                const uint32_t* __restrict__ whole_hist,
+                                                                float* __restrict__ X, double* __restrict__ p_new,
+                                                                int32_t* __restrict__ status) {
+  __shared__ BandLds<kBandRep> bands[2];
+  __shared__ uint64_t sums[3][9], extra[3][9];
+  const int nb = g.n_blocks, tid = threadIdx.x;
+  const int k = (int)blockIdx.x / nb, j = (int)blockIdx.x - k * nb;
+  if (!cam_active(g, k)) return;
+  const DevCam cam = uniform_cam(g, k);
+  const Seam m = seam_of(g, cam, k, j);
+  seam_bands<2 * kThreads, kBandPlain>(g, fp, b, BandArgs{}, m, bands, sums, extra);
+  // Thread 64 t + c takes channel c of unit t.
+  const int t = tid / kWave, c = tid % kWave;
+  if (t < m.n && c < kCS) {
+    const int u = (t == 0 ? m.u[0] : (t == 1 ? m.u[1] : m.u[2])) * kCS + c;
+    const int other = m.faces && t < 2 ? 1 - t : -1;
+    double pa, pb;
+    status[u] = fit_sums(g, cam.channels, c, &sums[t][c * 3], other >= 0 ? &sums[other][c * 3] : nullptr, pa, pb);
+    p_new[(int64_t)u * 2] = pa;
+    p_new[(int64_t)u * 2 + 1] = pb;
   }
-  features_unit(g, band_hist, whole_hist, X, u3);
+  const int half = uniform((int32_t)(tid / kThreads));
+  for (int i = half; i < m.n; i += 2)
+    features_unit(g, b.band_hist, whole_hist, X, i == 0 ? m.u[0] : (i == 1 ? m.u[1] : m.u[2]), tid - half * kThreads);
 }
 
-// Surrogate frame-set, step 3 (one workgroup per unit u3): the network's
-// output row (wave 0, the routine of the forward pass's output layer), the
-// choice and state update (thread 0, which stored that row), the unit's
-// tables, the camera's weights (first unit), and clearing the whole-frame
-// statistics the apply accumulates.
+// Surrogate frame-set, step 3 (one workgroup per unit u3): wave 0 forms the
+// network's output row (the routine of the forward pass's output layer) and
+// takes select_unit's choice and state update, a lane per channel with the
+// state read ahead; the unit's tables follow from the maps left in LDS.  Also
+// the camera's weights, shared by its units, and the clearing of the
+// whole-frame statistics that the apply accumulates.
 __global__ __launch_bounds__(kThreads) void k_select_lut(Geo g, const float* __restrict__ H2,
                                                          const float* __restrict__ W3, const float* __restrict__ b3,
                                                          float* __restrict__ Y, const double* __restrict__ p_new,
                                                          const int32_t* __restrict__ status, float tol, Bufs b,
                                                          uint8_t* __restrict__ used, float* __restrict__ residual) {
+  __shared__ int64_t q[kCS][2];
   const int u3 = blockIdx.x;
   const int tid = threadIdx.x;
   const int nb = g.n_blocks;
   const int k = u3 / (2 * nb);
   if (b.whole_hist) zero_whole(g, b, blockIdx.x * kThreads + tid, gridDim.x * kThreads);
   if (!cam_active(g, k)) return;
+  const DevCam cam = uniform_cam(g, k);
   if (tid < kWave) {
-    float acc[kMlpOut];
-    wave_row_dot<kMlpOut>(H2 + (int64_t)u3 * kMlpHid, W3, b3, kMlpHid, kMlpOut, acc);
-    if (tid == 0) {
+    const int c = tid < kCS ? tid : 0;
+    const int u = u3 * kCS + c;
+    const int st = status[u];
+    double pa = p_new[(int64_t)u * 2], pb = p_new[(int64_t)u * 2 + 1];
+    double p0 = b.params[(int64_t)u * 2], p1 = b.params[(int64_t)u * 2 + 1];
+    uint8_t v = b.valid[u];
+    float y[kMlpOut];
+    wave_row_dot<kMlpOut>(H2 + (int64_t)u3 * kMlpHid, W3, b3, kMlpHid, kMlpOut, y);
+    bool finite = true;
 #pragma unroll
-      for (int o = 0; o < kMlpOut; ++o) Y[(int64_t)u3 * kMlpOut + o] = acc[o];
-      select_unit(g, Y, p_new, status, tol, b.params, b.valid, used, residual, u3);
+    for (int o = 0; o < kMlpOut; ++o) {
+      finite = finite && __builtin_isfinite(y[o]);
+      if (tid == 0) Y[(int64_t)u3 * kMlpOut + o] = y[o];
+    }
+    const float ya = c == 0 ? y[0] : (c == 1 ? y[1] : y[2]), yb = c == 0 ? y[3] : (c == 1 ? y[4] : y[5]);
+    const bool eligible = cam.channels == 3 && (__builtin_amdgcn_ballot_w64(st != kStNew) & 7ull) == 0;
+    double r = __builtin_inf();
+    if (eligible && finite) {
+      const double da = __builtin_fabs((double)ya - pa), db = __builtin_fabs((double)yb - pb / 255.0);
+      r = da > db ? da : db;
+#pragma unroll
+      for (int o = 0; o < kCS; ++o) {
+        const double t = __shfl(r, o, kWave);
+        r = t > r ? t : r;
+      }
+    }
+    const bool use = eligible && finite && r <= (double)tol;
+    if (use) {
+      pa = (double)ya;
+      pb = 255.0 * (double)yb;
+    }
+    temporal_step(g, st, pa, pb, p0, p1, v);
+    if (tid < kCS) {
+      b.params[(int64_t)u * 2] = p0;
+      b.params[(int64_t)u * 2 + 1] = p1;
+      b.valid[u] = v;
+      q[c][0] = b.q16[(int64_t)u * 2] = q16_of(p0);
+      q[c][1] = b.q16[(int64_t)u * 2 + 1] = q16_of(p1);
+    }
+    if (tid == 0) {
+      used[u3] = use ? 1 : 0;
+      residual[u3] = (float)r;
     }
   }
+  const int i = u3 - k * 2 * nb, w1 = (int)((int64_t)(i + 1) * g.w_max / (2 * nb));
+  for (int col = (int)((int64_t)i * g.w_max / (2 * nb)) + tid; col < w1; col += kThreads)
+    b.weights[(int64_t)k * g.w_max + col] = (uint16_t)blend_weight(cam.width, col);
+  if (cam.bps != 1) return;
   __syncthreads();
-  unit_tables(g, b, u3, tid);
-  if (u3 % (2 * nb) == 0)
-    for (int col = tid; col < g.w_max; col += kThreads)
-      b.weights[(int64_t)k * g.w_max + col] = (uint16_t)blend_weight(g.cams[k].width, col);
+  const int c = tid / (kNB / 4), x = 4 * (tid % (kNB / 4));
+  if (c < kCS)
+    reinterpret_cast<uint32_t*>(b.lut8 + ((int64_t)u3 * kCS + c) * kNB)[x / 4] = table_quad(q[c][0], q[c][1], x);
 }
 
 hipError_t launch_features(const Geo& g, const uint32_t* band_hist, const uint32_t* whole_hist, float* X,
@@ -205,10 +259,10 @@ hipError_t launch_targets(const Geo& g, const double* p_new, const int32_t* stat
   return hipGetLastError();
 }
 
-hipError_t launch_features_new(const Geo& g, const uint32_t* band_hist, const uint64_t* band_sums,
-                               const uint32_t* whole_hist, float* X, double* p_new, int32_t* status, hipStream_t st) {
-  hipLaunchKernelGGL(k_features_new, dim3(g.n_cams * 2 * g.n_blocks), dim3(kThreads), 0, st, g, band_hist, band_sums,
-                     whole_hist, X, p_new, status);
+hipError_t launch_seam_features(const Geo& g, const FramePtrs& fp, const Bufs& b, const uint32_t* whole_hist, float* X,
+                                double* p_new, int32_t* status, hipStream_t st) {
+  hipLaunchKernelGGL(k_seam_features, dim3(g.n_cams * g.n_blocks), dim3(2 * kThreads), 0, st, g, fp, b, whole_hist, X,
+                     p_new, status);
   return hipGetLastError();
 }
 

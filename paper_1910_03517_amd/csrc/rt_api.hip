@@ -1357,10 +1357,8 @@ static rt_status surrogate_frameset_run(rt_ctx* ctx, const rt_mlp* w, float tol,
   const Geo& g = ctx->geo;
   const FramePtrs fp = make_ptrs_masked(ctx, frames, out_frames, g.active);
   const Bufs b = make_bufs(stats, state, lut);
-  hipError_t e = launch_band_stats(g, fp, b, st);
-  if (e != hipSuccess) return hip_fail(e, "band statistics");
-  e = launch_features_new(g, b.band_hist, b.band_sums, whole_hist_prev, work->X, work->p_new, work->status, st);
-  if (e != hipSuccess) return hip_fail(e, "surrogate features and plain estimate");
+  hipError_t e = launch_seam_features(g, fp, b, whole_hist_prev, work->X, work->p_new, work->status, st);
+  if (e != hipSuccess) return hip_fail(e, "band statistics, surrogate features and plain estimate");
   float* wp[6];
   mlp_ptrs(w, wp);
   e = mlp_hidden(wp, work->X, g.n_cams * 2 * g.n_blocks, work->H1, work->H2, st);
