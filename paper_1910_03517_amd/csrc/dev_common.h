@@ -16,6 +16,11 @@ __device__ inline unsigned long long dpp_u64(unsigned long long v) {
   return ((unsigned long long)hi << 32) | lo;
 }
 
+template <int CTRL, int ROW_MASK = 0xf>
+__device__ inline uint32_t dpp_u32(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xf, false);
+}
+
 // Sum of v over the 64 lanes of the wave (all lanes active), returned to every
 // lane.  Inclusive prefix sums within each row of 16 lanes (row_shr 1, 2, 4,
 // 8), then the last lane of row 0 added to rows 1 and 3 (row_bcast:15) and the

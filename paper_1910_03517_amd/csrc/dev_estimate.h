@@ -67,34 +67,39 @@ struct QSums {
   int64_t sx, sf, sxx, sff, sxf;   // sums of 2x, 2f, (2x)^2, (2f)^2, (2x)(2f)
 };
 
-// Inclusive prefix sums of a 256-bin histogram (global memory) into cum (LDS),
-// lane l taking bins 4l .. 4l + 3.
-__device__ inline void wave_cum(const uint32_t* h, uint32_t* cum, int lane) {
-  const uint32_t c0 = h[4 * lane], c1 = c0 + h[4 * lane + 1], c2 = c1 + h[4 * lane + 2], c3 = c2 + h[4 * lane + 3];
+// Inclusive prefix sums of a 256-bin histogram into cum (LDS), lane l taking
+// bins 4l .. 4l + 3, c[i] its bin 4l + i; over the lanes by the row moves of
+// wave_sum_u64, whose partial results are the prefixes.
+__device__ inline void wave_cum(const uint32_t (&c)[4], uint32_t* cum, int lane) {
+  const uint32_t c1 = c[0] + c[1], c2 = c1 + c[2], c3 = c2 + c[3];
   uint32_t incl = c3;
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    const uint32_t t = __shfl_up(incl, d, kWave);
-    if (lane >= d) incl += t;
-  }
+  incl += dpp_u32<0x111>(incl);          // row_shr:1
+  incl += dpp_u32<0x112>(incl);          // row_shr:2
+  incl += dpp_u32<0x114>(incl);          // row_shr:4
+  incl += dpp_u32<0x118>(incl);          // row_shr:8
+  incl += dpp_u32<0x142, 0xa>(incl);     // row_bcast:15 into rows 1 and 3
+  incl += dpp_u32<0x143, 0xc>(incl);     // row_bcast:31 into rows 2 and 3
   const uint32_t base = incl - c3;
-  cum[4 * lane] = base + c0;
+  cum[4 * lane] = base + c[0];
   cum[4 * lane + 1] = base + c1;
   cum[4 * lane + 2] = base + c2;
   cum[4 * lane + 3] = base + c3;
 }
 
-// Smallest bin v with 2 M cum(v) >= (2 level + 1) n (binary search).
-__device__ inline int quantile_bin(const uint32_t* cum, int level) {
-  const uint64_t n = cum[kNB - 1];
-  const uint64_t need = (uint64_t)(2 * level + 1) * n;
-  int lo = 0, hi = kNB - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if ((uint64_t)(2 * kQLevels) * cum[mid] >= need) hi = mid;
-    else lo = mid + 1;
+// Smallest bins v with 2 M cum(v) >= (2 level + 1) n of two bands: eight
+// halvings, both bands' LDS reads in flight together.  It is a chain of
+// latencies; one band after the other with lane shuffles for the prefixes took
+// 0.8 us more of a frame-set (26.7 against 25.9 us on a ragged three-ring rig).
+__device__ inline void quantile_bins(const uint32_t* cx, const uint32_t* cf, int level, int& x, int& f) {
+  static_assert(kNB == 256, "eight halvings");
+  const uint64_t nx = (uint64_t)(2 * level + 1) * cx[kNB - 1], nf = (uint64_t)(2 * level + 1) * cf[kNB - 1];
+  x = f = 0;
+#pragma unroll
+  for (int step = kNB / 2; step; step >>= 1) {
+    const uint32_t a = cx[x + step - 1], b = cf[f + step - 1];
+    x += (uint64_t)(2 * kQLevels) * a < nx ? step : 0;
+    f += (uint64_t)(2 * kQLevels) * b < nf ? step : 0;
   }
-  return lo;
 }
 
 // Twice the centre of bin v in sample units: bins of 2^shift samples.
@@ -107,14 +112,21 @@ __device__ inline int64_t bin_centre2(int v, int shift) {
 // of LDS owned by the wave.  Every lane returns the totals.
 __device__ inline QSums wave_quantile_sums(const uint32_t* ho, const uint32_t* hf, int shift, uint32_t* cum,
                                            int lane) {
-  wave_cum(ho, cum, lane);
-  wave_cum(hf, cum + kNB, lane);
+  uint32_t co[4], cf[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    co[i] = ho[4 * lane + i];
+    cf[i] = hf[4 * lane + i];
+  }
+  wave_cum(co, cum, lane);
+  wave_cum(cf, cum + kNB, lane);
   // Lanes read what other lanes of the wave wrote.
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  const int64_t x = bin_centre2(quantile_bin(cum, lane), shift);
-  const int64_t f = bin_centre2(quantile_bin(cum + kNB, lane), shift);
+  int bx, bf;
+  quantile_bins(cum, cum + kNB, lane, bx, bf);
+  const int64_t x = bin_centre2(bx, shift), f = bin_centre2(bf, shift);
   QSums q;
   q.sx = (int64_t)wave_sum_u64((unsigned long long)x);
   q.sf = (int64_t)wave_sum_u64((unsigned long long)f);
