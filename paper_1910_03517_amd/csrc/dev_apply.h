@@ -19,10 +19,12 @@
 // statistics with global atomics (the whole-frame buffers must be zero before
 // the first run).
 //
-// The runs of a camera interleave: run i of m takes every m-th step of
-// ap_lanes rows, so that all of a camera's workgroups read and write side by
-// side in its frame at any time, a handful of streams for the memory in place
-// of hundreds.
+// The runs of a camera interleave (run i of m takes every m-th step of ap_lanes
+// rows) where they hold enough rows for it, and are contiguous elsewhere (see
+// runs_interleave).  The form that stages whole 256-entry tables, two blocks of
+// RGB at a time, is always contiguous: rt_apply without statistics took, us
+// interleaved and contiguous, 14x1920x1080 of 16 blocks 42.5 and 36.8, of 64
+// blocks 75.6 and 37.2, 3x200x150 8.2 and 4.2.
 //
 // What bounds it: memory requests in flight and, next to them, the vector ALU
 // and the LDS atomics, each busy about half of the time.  Long runs pay the
@@ -524,12 +526,13 @@ __device__ inline void flush_whole(const Bufs& b, int k, ApplyLds& L, const Sums
 }
 
 // The run's rows R0 + ln + i stride (ln < ap_lanes) below R1 of camera k, of C
-// channels of BPS bytes.  CROSS: the 3x3 maps q3 in place of the affine ones.
+// channels of BPS bytes (see RowRun).  CROSS: the 3x3 maps q3 in place of the affine ones.
 template <int C, int BPS, bool WRITE, bool STATS, bool VB, bool CROSS, class FP>
 __device__ __attribute__((always_inline)) inline void apply_rows(const Geo& g, const FP& fp, const Bufs& b,
-                                                                 const int64_t* q3, const DevCam& cam, int k, int R0,
-                                                                 int R1, int stride, ApplyLds& L) {
+                                                                 const int64_t* q3, const DevCam& cam, int k,
+                                                                 const RowRun& run, ApplyLds& L) {
   const int tid = threadIdx.x, H = cam.height, nb = g.n_blocks;
+  const int R0 = run.row0, R1 = run.row1, stride = run.stride;
   if (STATS) {
     const u32x4 zero = {0, 0, 0, 0};
     for (int i = tid; i < C * kNB * kRep / 4; i += kApplyThreads) reinterpret_cast<u32x4*>(L.hist)[i] = zero;
@@ -594,17 +597,21 @@ __device__ __attribute__((always_inline)) inline void apply_run(const Geo& g, co
   for (int k = run.cam0; k <= run.cam1; ++k) {
     if (!cam_active(g, k)) continue;              // uniform over the workgroup
     const DevCam cam = uniform_cam(g, k);
-    const int r0 = k == run.cam0 ? run.row0 : 0, r1 = k == run.cam1 ? run.row1 : cam.height;
-    const int stride = max(run.stride, cam.ap_lanes);
-    if (r0 >= r1) continue;
+    RowRun r = {k == run.cam0 ? run.row0 : 0, k == run.cam1 ? run.row1 : cam.height, cam.ap_lanes};
+    if (run.of) {
+      const int steps = (cam.height + cam.ap_lanes - 1) / cam.ap_lanes;
+      const bool tables = WRITE && !STATS && !VB && !CROSS && cam.bps == 1;
+      r = row_run(cam.height, cam.ap_lanes, run.row0, run.of, !tables && runs_interleave(steps, run.of, g.n_blocks));
+    }
+    if (r.row0 >= r.row1) continue;
     if constexpr (CROSS) {
-      apply_rows<3, 1, WRITE, STATS, VB, true>(g, fp, b, q3, cam, k, r0, r1, stride, L);
+      apply_rows<3, 1, WRITE, STATS, VB, true>(g, fp, b, q3, cam, k, r, L);
     } else if (cam.bps == 2) {
-      apply_rows<1, 2, WRITE, STATS, VB, false>(g, fp, b, q3, cam, k, r0, r1, stride, L);
+      apply_rows<1, 2, WRITE, STATS, VB, false>(g, fp, b, q3, cam, k, r, L);
     } else if (cam.channels == 3) {
-      apply_rows<3, 1, WRITE, STATS, VB, false>(g, fp, b, q3, cam, k, r0, r1, stride, L);
+      apply_rows<3, 1, WRITE, STATS, VB, false>(g, fp, b, q3, cam, k, r, L);
     } else {
-      apply_rows<1, 1, WRITE, STATS, VB, false>(g, fp, b, q3, cam, k, r0, r1, stride, L);
+      apply_rows<1, 1, WRITE, STATS, VB, false>(g, fp, b, q3, cam, k, r, L);
     }
     if (k < run.cam1) __syncthreads();
   }

@@ -232,8 +232,8 @@ static rt_status build_tables(rt_ctx* ctx, int tile_rows, int grid) {
       const int steps = (H + step - 1) / step;
       const int m = own ? std::min(n[k], steps) : n[k];
       for (int i = 0; i < m; ++i) {
-        if (own) {      // every m-th step
-          runs.push_back(WgRun{k, i * step, k, H, m * step});
+        if (own) {
+          runs.push_back(WgRun{k, i, k, 0, m});
           continue;
         }
         const int a = (int)((int64_t)i * H / m), e = (int)((int64_t)(i + 1) * H / m);

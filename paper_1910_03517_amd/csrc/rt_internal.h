@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "../../include/ringcorr.h"
+#include "apply_split.h"
 
 namespace rc {
 
@@ -32,12 +33,12 @@ struct DevCam {
   int64_t pitch;         // bytes between rows
 };
 
-// The run of an apply workgroup: rows from row row0 of camera cam0 up to row
-// row1 (exclusive) of camera cam1, whole cameras between them.  It takes a
-// camera's ap_lanes rows at a time; stride 0: one such step after the other, so
-// every row; else the steps start `stride` rows apart.
+// The run of an apply workgroup.  of == 0: rows from row row0 of camera cam0 up
+// to row row1 (exclusive) of camera cam1, whole cameras between them.  of > 0
+// (the default split): run row0 of the `of` runs of camera cam0 == cam1 (see
+// row_run).
 struct WgRun {
-  int32_t cam0, row0, cam1, row1, stride;
+  int32_t cam0, row0, cam1, row1, of;
 };
 
 // Frame pointers of one launch, passed by value as a kernel argument.

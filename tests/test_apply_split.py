@@ -1,0 +1,61 @@
+"""The apply pass's default split of a camera's rows into runs (CPU): every row
+in exactly one run, a run that ends at its own last row, and no run whose rows
+span many more blocks than it has steps (a workgroup looks at and stages the
+maps of all blocks between its first and its last row)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+GXX = shutil.which("g++")
+pytestmark = pytest.mark.skipif(GXX is None, reason="no g++")
+
+
+def compile_host(tmp, name):
+    """A program of tests/split, with the headers' device attributes defined away."""
+    exe = os.path.join(tmp, name)
+    subprocess.run([GXX, "-std=c++17", "-Wall", "-D__host__=", "-D__device__=",
+                    os.path.join(HERE, "split", name + ".cpp"), "-o", exe], check=True)
+    return exe
+
+
+@pytest.fixture(scope="module")
+def row_runs(tmp_path_factory):
+    exe = compile_host(str(tmp_path_factory.mktemp("split")), "row_runs")
+
+    def get(H, lanes, m, nb):
+        out = subprocess.run([exe, str(H), str(lanes), str(m), str(nb)], check=True, capture_output=True, text=True)
+        runs = [tuple(int(v) for v in ln.split()) for ln in out.stdout.splitlines()]
+        assert len(runs) == 2 * m
+        return runs[:m], runs[m:]
+
+    return get
+
+
+# (height, rows at a time, runs, blocks)
+CASES = [(1, 1, 1, 1), (1, 512, 1, 16), (7, 3, 3, 16), (40, 2, 20, 64), (480, 16, 30, 16), (480, 3, 160, 16),
+         (517, 11, 47, 7), (720, 8, 85, 64), (1080, 1, 36, 16), (1080, 1, 37, 64), (1080, 1, 256, 256),
+         (1080, 1, 512, 1024), (2160, 2, 79, 16), (2160, 1, 79, 1024), (32768, 1, 512, 16), (32768, 256, 128, 1000),
+         (32767, 5, 8, 3)]
+
+
+@pytest.mark.parametrize("H,lanes,m,nb", CASES)
+def test_runs_cover_rows_and_span_few_blocks(row_runs, H, lanes, m, nb):
+    for runs, table_form in zip(row_runs(H, lanes, m, nb), (False, True)):
+        rows = [0] * H
+        for row0, row1, stride in runs:
+            assert 0 <= row0 < row1 <= H and stride >= lanes
+            own = [r for s in range(row0, row1, stride) for r in range(s, min(s + lanes, row1))]
+            for r in own:
+                rows[r] += 1
+            assert own[-1] == row1 - 1
+            block = lambda r: ((r + 1) * nb - 1) // H
+            spanned = block(row1 - 1) - block(row0) + 1
+            steps = -(-(row1 - row0) // stride)
+            if table_form:
+                assert stride == lanes
+            # The blocks of its own rows if they were contiguous, or one a step.
+            assert spanned <= max(len(own) * nb // H + 2, steps)
+        assert rows == [1] * H
