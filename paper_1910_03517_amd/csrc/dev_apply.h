@@ -598,10 +598,9 @@ __device__ __attribute__((always_inline)) inline void apply_run(const Geo& g, co
     if (!cam_active(g, k)) continue;              // uniform over the workgroup
     const DevCam cam = uniform_cam(g, k);
     RowRun r = {k == run.cam0 ? run.row0 : 0, k == run.cam1 ? run.row1 : cam.height, cam.ap_lanes};
-    if (run.of) {
-      const int steps = (cam.height + cam.ap_lanes - 1) / cam.ap_lanes;
-      const bool tables = WRITE && !STATS && !VB && !CROSS && cam.bps == 1;
-      r = row_run(cam.height, cam.ap_lanes, run.row0, run.of, !tables && runs_interleave(steps, run.of, g.n_blocks));
+    if (run.stride) {
+      if (WRITE && !STATS && !VB && !CROSS && cam.bps == 1) r = RowRun{run.trow0, run.trow1, cam.ap_lanes};
+      else r.stride = run.stride;
     }
     if (r.row0 >= r.row1) continue;
     if constexpr (CROSS) {

@@ -201,7 +201,7 @@ static rt_status build_tables(rt_ctx* ctx, int tile_rows, int grid) {
       const int parts = (rows + tile_rows - 1) / tile_rows;
       segments += parts;
       for (int p = 0; one_run_each && p < parts; ++p)
-        runs.push_back(WgRun{k, b0 + (int)((int64_t)p * rows / parts), k, b0 + (int)((int64_t)(p + 1) * rows / parts), 0});
+        runs.push_back(WgRun{k, b0 + (int)((int64_t)p * rows / parts), k, b0 + (int)((int64_t)(p + 1) * rows / parts), 0, 0, 0});
     }
   };
   int64_t total = 0;
@@ -233,11 +233,12 @@ static rt_status build_tables(rt_ctx* ctx, int tile_rows, int grid) {
       const int m = own ? std::min(n[k], steps) : n[k];
       for (int i = 0; i < m; ++i) {
         if (own) {
-          runs.push_back(WgRun{k, i, k, 0, m});
+          const RowRun r = row_run(H, step, i, m, runs_interleave(steps, m, nb)), t = row_run(H, step, i, m, false);
+          runs.push_back(WgRun{k, r.row0, k, r.row1, r.stride, t.row0, t.row1});
           continue;
         }
         const int a = (int)((int64_t)i * H / m), e = (int)((int64_t)(i + 1) * H / m);
-        runs.push_back(WgRun{k, a, k, e, 0});
+        runs.push_back(WgRun{k, a, k, e, 0, 0, 0});
         tiles(k, a, e, false);
       }
     }
@@ -263,7 +264,7 @@ static rt_status build_tables(rt_ctx* ctx, int tile_rows, int grid) {
       share_start(w + 1, c1, r1s);
       // A share that ends at a camera's first row ends with the camera before.
       const bool back = r1s == 0 && c1 > c0;
-      runs.push_back(WgRun{c0, r0s, back ? c1 - 1 : std::min(c1, n_cams - 1), back ? ctx->cams[c1 - 1].height : r1s, 0});
+      runs.push_back(WgRun{c0, r0s, back ? c1 - 1 : std::min(c1, n_cams - 1), back ? ctx->cams[c1 - 1].height : r1s, 0, 0, 0});
       for (int k = c0; k <= c1 && k < n_cams; ++k)
         tiles(k, k == c0 ? r0s : 0, k == c1 ? r1s : ctx->cams[k].height, false);
       c0 = c1;

@@ -33,12 +33,12 @@ struct DevCam {
   int64_t pitch;         // bytes between rows
 };
 
-// The run of an apply workgroup.  of == 0: rows from row row0 of camera cam0 up
-// to row row1 (exclusive) of camera cam1, whole cameras between them.  of > 0
-// (the default split): run row0 of the `of` runs of camera cam0 == cam1 (see
-// row_run).
+// The run of an apply workgroup: rows from row row0 of camera cam0 up to row
+// row1 (exclusive) of camera cam1, whole cameras between them.  stride > 0: the
+// rows of one camera as RowRun has them; then trow0 and trow1 bound the
+// contiguous rows that the form that stages whole tables takes instead.
 struct WgRun {
-  int32_t cam0, row0, cam1, row1, of;
+  int32_t cam0, row0, cam1, row1, stride, trow0, trow1;
 };
 
 // Frame pointers of one launch, passed by value as a kernel argument.
