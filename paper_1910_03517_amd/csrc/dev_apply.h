@@ -75,6 +75,7 @@ struct ApplyLds {
   alignas(16) uint8_t map[kMapBytes];          // [block or row][side][channel] maps, see stage_maps
   alignas(16) uint32_t hist[kCS * kNB * kRep]; // [channel][bin][replica]
   int32_t end[kMapEntries];                    // first row after each staged block
+  alignas(16) int32_t good[kApplyThreads / kWave];   // per wave, see stage_maps
   unsigned long long sums[9];                  // [channel] (n, S1, S2) of the run
 };
 
@@ -154,11 +155,10 @@ struct MapEntry {   // bytes of one block's (or row's) staged maps, both sides
 
 // An 8-bit map may be evaluated directly, bit for bit equal to its table, when
 // A fits a 24-bit multiply and A x + Bq + 2^15 stays inside int32 for x in [0,
-// 255].  |A| <= 2^22 (a gain of 64) and |Bq + 2^15| <= 2^30 give that, and hold
-// for every convex combination of maps that pass.
+// 255].
 __device__ inline bool small_map(int64_t A, int64_t Bq) {
-  const int64_t c = Bq + 32768;
-  return A <= (1 << 22) && A >= -(1 << 22) && c <= (1 << 30) && c >= -(1 << 30);
+  const int64_t c = Bq + 32768, e = 255 * A + c;
+  return A < (1 << 23) && A >= -(1 << 23) && c <= INT32_MAX && c >= INT32_MIN && e <= INT32_MAX && e >= INT32_MIN;
 }
 
 // Row-wise blend of adjacent blocks' maps (section 5's convex combinations of
@@ -194,41 +194,34 @@ __device__ inline int64_t blend_q16(int64_t pa, int64_t pb, int v) {
   return ((256 - v) * pa + v * pb + 128) >> 8;
 }
 
-// Whether the maps of blocks [ja, jb] of camera k pass small_map.  Each wave
-// looks at all of them, so that every wave has the answer without a barrier.
-template <int C>
-__device__ inline bool maps_small(const Geo& g, const Bufs& b, int k, int ja, int jb) {
-  const int n = (jb - ja + 1) * 2 * C;
-  bool ok = true;
-  for (int i = threadIdx.x % kWave; i < n; i += kWave) {
-    const int c = i % C, s = (i / C) & 1, j = ja + i / (2 * C);
-    const int64_t u = unit_index(k, s, j, c, g.n_blocks);
-    ok = ok && small_map(b.q16[u * 2], b.q16[u * 2 + 1]);
+// Row r of a 3x3 map q: coefficients that fit 24-bit multiplies, and A_r . x +
+// B_r + 2^15 inside int32 for every x in [0, 255]^3.
+__device__ inline bool small_cross(const int64_t* q, int r) {
+  int64_t lo = q[9 + r] + 32768, hi = lo;
+  bool ok = lo <= INT32_MAX && lo >= INT32_MIN;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const int64_t a = q[r * 3 + c];
+    const bool fits = a < (1 << 23) && a > -(1 << 23);
+    ok = ok && fits;
+    lo += fits && a < 0 ? 255 * a : 0;
+    hi += fits && a > 0 ? 255 * a : 0;
   }
-  return __builtin_amdgcn_ballot_w64(!ok) == 0;
-}
-
-// 3x3 maps: |A| <= 2^20 (a coefficient of 16) and |B + 2^15| <= 2^30 keep
-// A_r . x + B_r + 2^15 inside int32 for every x in [0, 255]^3.
-__device__ inline bool cross_small(const Geo& g, const int64_t* q3, int k, int ja, int jb) {
-  const int n = (jb - ja + 1) * 2 * kX3;
-  bool ok = true;
-  for (int i = threadIdx.x % kWave; i < n; i += kWave) {
-    const int e = i % kX3, s = (i / kX3) & 1, j = ja + i / (2 * kX3);
-    const int64_t v = q3[(((int64_t)k * 2 + s) * g.n_blocks + j) * kX3 + e];
-    ok = ok && (e < 9 ? v <= (1 << 20) && v >= -(1 << 20) : v + 32768 <= (1 << 30) && v + 32768 >= -(1 << 30));
-  }
-  return __builtin_amdgcn_ballot_w64(!ok) == 0;
+  return ok && lo >= INT32_MIN && hi <= INT32_MAX;
 }
 
 // Stages the maps of a piece of the run: entry e is block j0 + e, or with VB
 // the run's row p0 + (e / lanes) stride + e % lanes (its two blocks' maps
-// blended).
+// blended).  Ends with a barrier and returns the number of entries, from the
+// first on, that the form evaluates exactly: fewer than n only where 32-bit
+// arithmetic does not hold a map.  That is looked at on the values on their way
+// to LDS; a pass over them of its own took 0.4 us more of every workgroup.
 template <int C, int BPS, int KIND, bool VB>
-__device__ inline void stage_maps(const Geo& g, const Bufs& b, const int64_t* q3, const DevCam& cam, int k, int p0,
-                                  int stride, int j0, int n, ApplyLds& L) {
+__device__ inline int stage_maps(const Geo& g, const Bufs& b, const int64_t* q3, const DevCam& cam, int k, int p0,
+                                 int stride, int j0, int n, ApplyLds& L) {
   const int nb = g.n_blocks, H = cam.height, tid = threadIdx.x;
   constexpr int kPer = KIND == kMapTable ? 2 * C * kNB / 4 : KIND >= kMapCross ? 2 * kX3 : 2 * C;
+  int good = n;
   if (!VB && tid < n) L.end[tid] = block_row(j0 + tid + 1, H, nb);
   for (int i = tid; i < n * kPer; i += kApplyThreads) {
     const int e = i / kPer, rem = i - e * kPer;
@@ -258,6 +251,7 @@ __device__ inline void stage_maps(const Geo& g, const Bufs& b, const int64_t* q3
         B = b.q16[u * 2 + 1];
       }
       if (KIND == kMapDirect) {
+        if (!small_map(A, B)) good = min(good, e);
         reinterpret_cast<int32_t*>(L.map)[2 * i] = (int32_t)A;
         reinterpret_cast<int32_t*>(L.map)[2 * i + 1] = (int32_t)(B + 32768);
       } else {
@@ -266,6 +260,24 @@ __device__ inline void stage_maps(const Geo& g, const Bufs& b, const int64_t* q3
       }
     }
   }
+  if constexpr (KIND == kMapDirect || KIND == kMapCross) {
+    if (KIND == kMapCross)
+      for (int i = tid; i < n * 6; i += kApplyThreads) {
+        const int e = i / 6, s = i / 3 & 1;
+        if (!small_cross(q3 + (((int64_t)k * 2 + s) * nb + j0 + e) * kX3, i % 3)) good = min(good, e);
+      }
+    if (__builtin_amdgcn_ballot_w64(good < n) != 0) {
+#pragma unroll
+      for (int o = kWave / 2; o; o >>= 1) good = min(good, __shfl_xor(good, o, kWave));
+    }
+    if (tid % kWave == 0) L.good[tid / kWave] = good;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kApplyThreads / kWave; ++w) good = min(good, L.good[w]);
+    return uniform((int32_t)good);
+  }
+  __syncthreads();
+  return n;
 }
 
 // The maps of one side of one entry, in registers (the tables stay in LDS).
@@ -296,12 +308,14 @@ struct SideMap {
       // Staged coefficients fit 24 bits (small_map), so these are 24-bit
       // multiplies.  clamp(v >> 16, 0, 255) << 16 == clamp(v, 0, 2^24 - 1) &
       // 0xffff0000 for the arithmetic shift, so f lands in the high half.
-      auto m24 = [](int32_t a, uint32_t s) { return ((int32_t)((uint32_t)a << 8) >> 8) * (int32_t)s; };
+      // The whole sum is inside int32, its parts may not be.
+      auto m24 = [](int32_t a, uint32_t s) { return (uint32_t)(((int32_t)((uint32_t)a << 8) >> 8) * (int32_t)s); };
       int32_t y;
       if constexpr (KIND == kMapDirect) {
-        y = m24(v[2 * c], x) + v[2 * c + 1];
+        y = (int32_t)(m24(v[2 * c], x) + (uint32_t)v[2 * c + 1]);
       } else {
-        y = m24(v[c * 3], xs[0]) + m24(v[c * 3 + 1], xs[C > 1 ? 1 : 0]) + m24(v[c * 3 + 2], xs[C > 2 ? 2 : 0]) + v[9 + c];
+        y = (int32_t)(m24(v[c * 3], xs[0]) + m24(v[c * 3 + 1], xs[C > 1 ? 1 : 0]) +
+                      m24(v[c * 3 + 2], xs[C > 2 ? 2 : 0]) + (uint32_t)v[9 + c]);
       }
       y = y < 0 ? 0 : (y > 0xffffff ? 0xffffff : y);
       return ((uint32_t)y & 0xffff0000u) | x;
@@ -542,49 +556,38 @@ __device__ __attribute__((always_inline)) inline void apply_rows(const Geo& g, c
   __amdgpu_buffer_rsrc_t rout = rin;
   if (WRITE) rout = frame_rsrc(fp.out[k], cam);
   Sums16 sums = {0, 0};
-  // The run in pieces whose maps fit the staging area.
-  auto pieces = [&](auto kind, int p0, int pe) {
-    constexpr int KIND = decltype(kind)::value;
-    constexpr int kCap = MapEntry<KIND, C>::kCap;
-    while (p0 < pe) {
-      int j0 = 0, p1, n;
-      if (VB) {
-        const int turns = max(1, kCap / cam.ap_lanes);      // of the workgroup's rows
-        p1 = min(pe, p0 + turns * stride);
-        n = min(turns, (p1 - p0 + stride - 1) / stride) * cam.ap_lanes;
-      } else {
-        j0 = row_block(p0, H, nb);
-        n = min(kCap, row_block(pe - 1, H, nb) - j0 + 1);
-        p1 = min(pe, block_row(j0 + n, H, nb));
-      }
-      if (p0 != R0) __syncthreads();    // the previous piece's rows are done with the maps
-      if (WRITE) stage_maps<C, BPS, KIND, VB>(g, b, q3, cam, k, p0, stride, j0, n, L);
-      __syncthreads();
-      piece_rows<C, BPS, KIND, WRITE, STATS, VB>(g, b, cam, k, rin, rout, R0, stride, p0, p1, j0, L, sums);
-      p0 = p1;
-    }
-  };
   if constexpr (!WRITE) {
-    pieces(std::integral_constant<int, kMapDirect>{}, R0, R1);
-  } else if constexpr (CROSS) {
-    if (cross_small(g, q3, k, row_block(R0, H, nb), row_block(R1 - 1, H, nb)))
-      pieces(std::integral_constant<int, kMapCross>{}, R0, R1);
-    else
-      pieces(std::integral_constant<int, kMapCrossWide>{}, R0, R1);
-  } else if constexpr (BPS == 2) {
-    pieces(std::integral_constant<int, kMapWide>{}, R0, R1);
-  } else if constexpr (VB) {
-    if (maps_small<C>(g, b, k, max(0, row_block(R0, H, nb) - 1), min(nb - 1, row_block(R1 - 1, H, nb) + 1)))
-      pieces(std::integral_constant<int, kMapDirect>{}, R0, R1);
-    else
-      pieces(std::integral_constant<int, kMapWide>{}, R0, R1);
-  } else if constexpr (STATS) {
-    if (maps_small<C>(g, b, k, row_block(R0, H, nb), row_block(R1 - 1, H, nb)))
-      pieces(std::integral_constant<int, kMapDirect>{}, R0, R1);
-    else
-      pieces(std::integral_constant<int, kMapTable>{}, R0, R1);
+    __syncthreads();
+    piece_rows<C, BPS, kMapDirect, WRITE, STATS, false>(g, b, cam, k, rin, rout, R0, stride, R0, R1, 0, L, sums);
   } else {
-    pieces(std::integral_constant<int, kMapTable>{}, R0, R1);
+    // The run in pieces whose maps fit the staging area.  Where a map is too
+    // large for the fast form, the entries before it are taken first, then
+    // its own block (or, blended, its turn of the workgroup's rows) in the exact
+    // form.
+    constexpr int kFast = CROSS ? kMapCross : BPS == 2 ? kMapWide : VB || STATS ? kMapDirect : kMapTable;
+    constexpr int kExact = CROSS ? kMapCrossWide : VB ? kMapWide : kMapTable;
+    constexpr bool kChecked = kFast == kMapDirect || kFast == kMapCross;
+    constexpr int kCap = MapEntry<kFast, C>::kCap;
+    const int per = VB ? cam.ap_lanes : 1;                // entries of a block or turn
+    const int je = VB ? 0 : row_block(R1 - 1, H, nb);
+#pragma unroll 1
+    for (int p0 = R0, p1; p0 < R1; p0 = p1) {
+      const int j0 = VB ? 0 : row_block(p0, H, nb);
+      // Blocks (VB: turns) at hand, and the end of the rows of the first n of them.
+      int n = VB ? min(max(1, kCap / per), (R1 - p0 + stride - 1) / stride) : min(kCap, je - j0 + 1);
+      auto end = [&](int m) { return min(R1, VB ? p0 + m * stride : block_row(j0 + m, H, nb)); };
+      if (p0 != R0) __syncthreads();      // the previous piece's rows are done with the maps
+      const int good = stage_maps<C, BPS, kFast, VB>(g, b, q3, cam, k, p0, stride, j0, n * per, L) / per;
+      if (!kChecked || good > 0) {
+        p1 = end(kChecked ? good : n);
+        piece_rows<C, BPS, kFast, WRITE, STATS, VB>(g, b, cam, k, rin, rout, R0, stride, p0, p1, j0, L, sums);
+      } else if constexpr (kChecked) {
+        __syncthreads();
+        (void)stage_maps<C, BPS, kExact, VB>(g, b, q3, cam, k, p0, stride, j0, per, L);
+        p1 = end(1);
+        piece_rows<C, BPS, kExact, WRITE, STATS, VB>(g, b, cam, k, rin, rout, R0, stride, p0, p1, j0, L, sums);
+      }
+    }
   }
   if (STATS) flush_whole<C, BPS>(b, k, L, sums);
 }
