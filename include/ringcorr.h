@@ -592,8 +592,9 @@ rt_status rt_graph_set_frames(rt_graph* g, const void* const* frames, void* cons
 rt_status rt_ctx_check(rt_ctx* ctx);
 
 /* Performance knobs that never change results.  The default (tile_rows 32, grid
- * 0): about two apply workgroups per compute unit, shared among the cameras
- * by their bytes, each on an even share of its camera's rows.  grid == 0 with
+ * 0): about two apply workgroups per compute unit, shared among the active
+ * cameras of the launch by their bytes, each on an even share of its
+ * camera's rows.  grid == 0 with
  * another tile_rows (1..4096): each vertical block of each camera is cut into
  * tiles of equal height of at most tile_rows rows, one apply workgroup per
  * tile.  grid > 0

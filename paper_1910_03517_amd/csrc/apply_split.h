@@ -42,4 +42,28 @@ __host__ __device__ inline RowRun row_run(int height, int lanes, int i, int m, b
   return r;
 }
 
+// The workgroups of the default split shared among the cameras of the bit mask
+// `active`, by their bytes, at least one each and at most one a step: camera
+// k's runs are workgroups first[k] .. first[k + 1] - 1 (`first` holds n + 1
+// entries).  Returns their number, at most max(total, active cameras).
+inline int split_shares(int n, const int64_t* bytes, const int32_t* steps, uint64_t active, int total,
+                        uint16_t* first) {
+  int64_t all = 0, before = 0;
+  int cams = 0;
+  for (int k = 0; k < n; ++k)
+    if ((active >> k) & 1u) all += bytes[k], ++cams;
+  const int64_t more = total > cams ? total - cams : 0;      // beyond one each
+  int w = 0;
+  for (int k = 0; k < n; ++k) {
+    first[k] = (uint16_t)w;
+    if (!((active >> k) & 1u)) continue;
+    const int64_t a = more * before / all, e = more * (before + bytes[k]) / all;
+    before += bytes[k];
+    const int m = 1 + (int)(e - a);
+    w += m < steps[k] ? m : steps[k];
+  }
+  first[n] = (uint16_t)w;
+  return w;
+}
+
 }  // namespace rc

@@ -592,11 +592,29 @@ __device__ __attribute__((always_inline)) inline void apply_rows(const Geo& g, c
   if (STATS) flush_whole<C, BPS>(b, k, L, sums);
 }
 
+// Run w of the default split over the active cameras of a larger rig, worked out
+// here: the context's table shares the workgroups among all cameras and would
+// leave a few of them with a few.  rt_frameset_batch, apply us, table and this:
+// one 1920x1080 camera of 32 45.9 and 18.4 (28.5 with one workgroup per
+// tile), one 1280x720 of 60 38.4 and 13.1 (26.4), seven 1920x1080 of 14 36.7 and
+// 27.1 (37.9).
+__device__ inline WgRun subset_run(const Geo& g, int w) {
+  static_assert(RT_MAX_CAMS <= kWave, "a lane per camera");
+  const int lane = threadIdx.x % kWave;
+  const int k = __popcll(__builtin_amdgcn_ballot_w64(lane < g.n_cams && g.first[lane + 1] <= w));
+  const DevCam cam = uniform_cam(g, k);
+  const int i = w - g.first[k], m = g.first[k + 1] - g.first[k];
+  const int steps = (cam.height + cam.ap_lanes - 1) / cam.ap_lanes;
+  const RowRun r = row_run(cam.height, cam.ap_lanes, i, m, runs_interleave(steps, m, g.n_blocks));
+  const RowRun t = row_run(cam.height, cam.ap_lanes, i, m, false);
+  return WgRun{k, r.row0, k, r.row1, r.stride, t.row0, t.row1};
+}
+
 // Workgroup w's run: its rows of every camera it takes.
 template <bool WRITE, bool STATS, bool VB, bool CROSS, class FP>
 __device__ __attribute__((always_inline)) inline void apply_run(const Geo& g, const FP& fp, const Bufs& b,
                                                                 const int64_t* q3, int w, ApplyLds& L) {
-  const WgRun run = uniform_run(g, w);
+  const WgRun run = g.subset ? subset_run(g, w) : uniform_run(g, w);
   for (int k = run.cam0; k <= run.cam1; ++k) {
     if (!cam_active(g, k)) continue;              // uniform over the workgroup
     const DevCam cam = uniform_cam(g, k);

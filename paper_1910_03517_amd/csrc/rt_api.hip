@@ -29,7 +29,8 @@ struct rt_ctx {
   int tile_rows = 0;
   int grid = 0;             // apply workgroups (0: see build_tables)
   DevCam* dcams = nullptr;
-  WgRun* druns = nullptr;   // [n_wg] rows of each apply workgroup
+  WgRun* druns = nullptr;   // [n_runs] rows of each apply workgroup over all cameras
+  int n_runs = 0;
   double* seam_rows = nullptr;   // row values of rt_seam_cost when the caller passes none
   size_t seam_rows_n = 0;
 
@@ -174,6 +175,30 @@ static void lay_apply(DevCam& d, int max_lanes) {
   }
 }
 
+static bool default_split(const rt_ctx* ctx) { return ctx->grid == 0 && ctx->tile_rows == kDefaultTileRows; }
+
+// The default split's workgroups among the cameras in `active` (split_shares).
+static int share_runs(const rt_ctx* ctx, uint64_t active, uint16_t* first) {
+  int64_t bytes[RT_MAX_CAMS];
+  int32_t steps[RT_MAX_CAMS];
+  for (int k = 0; k < ctx->n_cams; ++k) {
+    const DevCam& d = ctx->hcams[k];
+    bytes[k] = (int64_t)d.height * d.row_bytes;
+    steps[k] = (d.height + d.ap_lanes - 1) / d.ap_lanes;
+  }
+  return split_shares(ctx->n_cams, bytes, steps, active, kAutoRuns, first);
+}
+
+// The context's constants for a launch over the cameras in `active`.
+static Geo geo_for(const rt_ctx* ctx, uint64_t active) {
+  Geo g = ctx->geo;
+  if (g.active == active && g.n_wg) return g;
+  g.active = active;
+  g.subset = default_split(ctx) && active != all_cams(ctx->n_cams);
+  g.n_wg = g.subset ? share_runs(ctx, active, g.first) : ctx->n_runs;
+  return g;
+}
+
 // Device tables: the rows that each apply workgroup takes.  By default
 // (tile_rows kDefaultTileRows, grid 0) every camera gets a whole number of
 // workgroups, about kAutoRuns of them over the rig in proportion to its bytes,
@@ -204,52 +229,55 @@ static rt_status build_tables(rt_ctx* ctx, int tile_rows, int grid) {
         runs.push_back(WgRun{k, b0 + (int)((int64_t)p * rows / parts), k, b0 + (int)((int64_t)(p + 1) * rows / parts), 0, 0, 0});
     }
   };
-  int64_t total = 0;
-  for (int k = 0; k < n_cams; ++k) total += (int64_t)ctx->cams[k].height * ctx->hcams[k].row_bytes;
-  const bool own = grid == 0 && tile_rows == kDefaultTileRows;
-  const int G = own ? std::max(kAutoRuns, n_cams) : grid;
-  if (grid == 0 && !own) {
+  const bool own = default_split(ctx);
+  if (own) {
+    uint16_t first[RT_MAX_CAMS + 1];
+    share_runs(ctx, all_cams(n_cams), first);
+    for (int k = 0; k < n_cams; ++k) {
+      const int H = ctx->cams[k].height, lanes = ctx->hcams[k].ap_lanes;
+      const int m = first[k + 1] - first[k];
+      tiles(k, 0, H, false);
+      for (int i = 0; i < m; ++i) {
+        const RowRun r = row_run(H, lanes, i, m, runs_interleave((H + lanes - 1) / lanes, m, nb));
+        const RowRun t = row_run(H, lanes, i, m, false);
+        runs.push_back(WgRun{k, r.row0, k, r.row1, r.stride, t.row0, t.row1});
+      }
+    }
+  } else if (grid == 0) {
     for (int k = 0; k < n_cams; ++k) tiles(k, 0, ctx->cams[k].height, true);
-  } else if (G >= n_cams) {
+  } else if (grid >= n_cams) {
     // Every camera gets a whole number of shares, one plus its part of the
-    // other G - K by bytes (largest remainders), and its rows are split
+    // other grid - K by bytes (largest remainders), and its rows are split
     // evenly among them: no share spans two cameras.
+    int64_t total = 0;
+    for (int k = 0; k < n_cams; ++k) total += (int64_t)ctx->cams[k].height * ctx->hcams[k].row_bytes;
     std::vector<int> n(n_cams, 1);
     std::vector<std::pair<int64_t, int>> rem(n_cams);
     int given = n_cams;
     for (int k = 0; k < n_cams; ++k) {
-      const __int128 q = (__int128)(G - n_cams) * ((int64_t)ctx->cams[k].height * ctx->hcams[k].row_bytes);
+      const __int128 q = (__int128)(grid - n_cams) * ((int64_t)ctx->cams[k].height * ctx->hcams[k].row_bytes);
       n[k] += (int)(q / total);
       given += (int)(q / total);
       rem[k] = {(int64_t)(q % total), -k};
     }
     std::sort(rem.begin(), rem.end(), std::greater<std::pair<int64_t, int>>());
-    for (int i = 0; given < G; ++i, ++given) ++n[-rem[i].second];
+    for (int i = 0; given < grid; ++i, ++given) ++n[-rem[i].second];
     for (int k = 0; k < n_cams; ++k) {
       const int H = ctx->cams[k].height;
-      if (own) tiles(k, 0, H, false);
-      const int step = own ? ctx->hcams[k].ap_lanes : 1;
-      const int steps = (H + step - 1) / step;
-      const int m = own ? std::min(n[k], steps) : n[k];
-      for (int i = 0; i < m; ++i) {
-        if (own) {
-          const RowRun r = row_run(H, step, i, m, runs_interleave(steps, m, nb)), t = row_run(H, step, i, m, false);
-          runs.push_back(WgRun{k, r.row0, k, r.row1, r.stride, t.row0, t.row1});
-          continue;
-        }
-        const int a = (int)((int64_t)i * H / m), e = (int)((int64_t)(i + 1) * H / m);
+      for (int i = 0; i < n[k]; ++i) {
+        const int a = (int)((int64_t)i * H / n[k]), e = (int)((int64_t)(i + 1) * H / n[k]);
         runs.push_back(WgRun{k, a, k, e, 0, 0, 0});
         tiles(k, a, e, false);
       }
     }
   } else {
     // Fewer workgroups than cameras: share w starts at the first row whose
-    // byte offset reaches w / G of the total, so shares span cameras.
+    // byte offset reaches w / grid of the total, so shares span cameras.
     std::vector<int64_t> base(n_cams + 1, 0);
     for (int k = 0; k < n_cams; ++k)
       base[k + 1] = base[k] + (int64_t)ctx->cams[k].height * ctx->hcams[k].row_bytes;
     auto share_start = [&](int w, int& cam, int& row) {
-      const int64_t target = (int64_t)((__int128)w * base[n_cams] / G);
+      const int64_t target = (int64_t)((__int128)w * base[n_cams] / grid);
       cam = 0;
       while (cam < n_cams && base[cam + 1] <= target) ++cam;
       if (cam == n_cams) { row = 0; return; }
@@ -259,7 +287,7 @@ static rt_status build_tables(rt_ctx* ctx, int tile_rows, int grid) {
     };
     int c0, r0s;
     share_start(0, c0, r0s);
-    for (int w = 0; w < G; ++w) {
+    for (int w = 0; w < grid; ++w) {
       int c1, r1s;
       share_start(w + 1, c1, r1s);
       // A share that ends at a camera's first row ends with the camera before.
@@ -281,9 +309,10 @@ static rt_status build_tables(rt_ctx* ctx, int tile_rows, int grid) {
   if (e == hipSuccess) e = hipMemcpy(ctx->druns, runs.data(), sizeof(WgRun) * runs.size(), hipMemcpyHostToDevice);
   if (e != hipSuccess) return hip_fail(e, "uploading context tables");
   Geo& g = ctx->geo;
+  g.n_wg = 0;
   g.cams = ctx->dcams;
   g.runs = ctx->druns;
-  g.n_wg = (int32_t)runs.size();
+  ctx->n_runs = (int32_t)runs.size();
   g.n_cams = n_cams;
   g.n_blocks = nb;
   g.w_max = ctx->w_max;
@@ -294,7 +323,7 @@ static rt_status build_tables(rt_ctx* ctx, int tile_rows, int grid) {
   g.alpha = ctx->opts.ema_alpha;
   g.a_min = ctx->opts.a_min;
   g.a_max = ctx->opts.a_max;
-  if (g.active == 0) g.active = all_cams(n_cams);
+  g = geo_for(ctx, g.active ? g.active : all_cams(n_cams));
   return RT_OK;
 }
 
@@ -627,8 +656,7 @@ static rt_status frameset_masked(rt_ctx* ctx, uint64_t active, const void* const
   if (r == RT_OK) r = check_lut(lut);
   if (r != RT_OK) return r;
   hipStream_t st = (hipStream_t)stream;
-  Geo g = ctx->geo;
-  g.active = active;
+  const Geo g = geo_for(ctx, active);
   const FramePtrs fp = make_ptrs_masked(ctx, frames, out_frames, active);
   const Bufs b = make_bufs(stats, state, lut);
   const hipError_t e = launch_band_estimate(g, fp, b, st);
@@ -700,7 +728,7 @@ rt_status rt_frameset_ahead(rt_ctx* ctx, const void* const* frames, void* const*
 rt_status rt_ctx_set_active(rt_ctx* ctx, uint64_t active) {
   if (!ctx) return fail(RT_EINVAL, "ctx is NULL");
   rt_status r = check_active(ctx, active);
-  if (r == RT_OK) ctx->geo.active = active;
+  if (r == RT_OK) ctx->geo = geo_for(ctx, active);
   return r;
 }
 
@@ -1024,9 +1052,7 @@ static hipError_t pipe_flush_fused(rt_pipe* p) {
       sp.b[m] = SetBufs{p->wholes[q.slot].whole_hist, p->wholes[q.slot].whole_sums, p->luts[q.slot].lut8,
                         p->luts[q.slot].q16, p->luts[q.slot].weights};
     }
-    Geo gg = ctx->geo;
-    gg.active = p->pending[i].active;
-    e = timed_apply_sets(ctx, gg, sp, sl);
+    e = timed_apply_sets(ctx, geo_for(ctx, p->pending[i].active), sp, sl);
     for (size_t m = 0; m < n; ++m) {
       const auto& q = p->pending[i + m];
       if (e == hipSuccess && q.done) e = hipEventRecord(q.done, sl);
@@ -1059,9 +1085,7 @@ static hipError_t pipe_flush(rt_pipe* p) {
       const auto& q = p->pending[i];
       if (q.lane != l) continue;
       const Bufs ba = make_bufs(&p->wholes[q.slot], nullptr, &p->luts[q.slot]);
-      Geo g = ctx->geo;
-      g.active = q.active;
-      e = timed_apply(ctx, g, q.fp, ba, true, true, sl);
+      e = timed_apply(ctx, geo_for(ctx, q.active), q.fp, ba, true, true, sl);
       if (e == hipSuccess && q.done) e = hipEventRecord(q.done, sl);
       p->slot_group[q.slot] = p->groups;
       p->slot_lane[q.slot] = l;

@@ -103,6 +103,10 @@ struct Geo {
   uint64_t active;       // cameras processed by this launch (bit k = camera k)
   int32_t vblend;        // 1: the maps of adjacent blocks are blended row by row in the apply
   int32_t fit;           // RT_FIT_MOMENTS or RT_FIT_QUANTILE
+  // The default split over a part of the rig's cameras, in place of `runs`: see
+  // split_shares and subset_run.
+  int32_t subset;
+  uint16_t first[RT_MAX_CAMS + 1];
 };
 
 __host__ __device__ inline bool cam_active(const Geo& g, int k) { return (g.active >> k) & 1ull; }

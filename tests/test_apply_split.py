@@ -1,7 +1,9 @@
 """The apply pass's default split of a camera's rows into runs (CPU): every row
 in exactly one run, a run that ends at its own last row, and no run whose rows
 span many more blocks than it has steps (a workgroup looks at and stages the
-maps of all blocks between its first and its last row)."""
+maps of all blocks between its first and its last row).  And of the workgroups
+among the cameras of a launch: by their bytes over the active ones, whatever
+the rest of the rig is."""
 import os
 import shutil
 import subprocess
@@ -59,3 +61,40 @@ def test_runs_cover_rows_and_span_few_blocks(row_runs, H, lanes, m, nb):
             # The blocks of its own rows if they were contiguous, or one a step.
             assert spanned <= max(len(own) * nb // H + 2, steps)
         assert rows == [1] * H
+
+
+@pytest.fixture(scope="module")
+def shares(tmp_path_factory):
+    exe = compile_host(str(tmp_path_factory.mktemp("shares")), "shares")
+
+    def get(cams, active, total=512):
+        out = subprocess.run([exe, str(active), str(total)] + [f"{b}:{s}" for b, s in cams], check=True,
+                             capture_output=True, text=True)
+        first = [int(v) for v in out.stdout.split()]
+        assert len(first) == len(cams) + 1 and first[0] == 0
+        return [b - a for a, b in zip(first, first[1:])]
+
+    return get
+
+
+HD, VGA, UHD, TINY = (1080 * 5760, 1080), (480 * 1920, 160), (2160 * 12288, 2160), (100, 1)
+
+
+@pytest.mark.parametrize("cams,active", [
+    ([HD] * 14, (1 << 14) - 1), ([HD] * 14, 1), ([HD] * 14, 0x2a), ([HD] * 32, 1 << 31), ([VGA] * 60, 0xff),
+    ([VGA] * 64, (1 << 64) - 1), ([VGA] * 64, 1 << 63), ([UHD] * 4 + [HD] * 8 + [VGA] * 4, 0xffff),
+    ([UHD] + [VGA] * 12, 2), ([TINY] * 3, 7), ([TINY, UHD], 3), ([(2 ** 31 - 1, 32768)] * 64, (1 << 64) - 1)])
+def test_shares_follow_the_active_cameras(shares, cams, active):
+    got = shares(cams, active)
+    on = [k for k in range(len(cams)) if (active >> k) & 1]
+    total = sum(cams[k][0] for k in on)
+    for k, m in enumerate(got):
+        if k not in on:
+            assert m == 0
+            continue
+        fair = 1 + (max(512, len(on)) - len(on)) * cams[k][0] / total
+        assert 1 <= m <= cams[k][1]
+        assert m == cams[k][1] or abs(m - fair) < 1.0 + 1e-9
+    assert sum(got) <= max(512, len(on))
+    # A part of a rig is served as a rig of those cameras alone.
+    assert [got[k] for k in on] == shares([cams[k] for k in on], (1 << len(on)) - 1)
