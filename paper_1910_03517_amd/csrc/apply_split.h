@@ -42,6 +42,46 @@ __host__ __device__ inline RowRun row_run(int height, int lanes, int i, int m, b
   return r;
 }
 
+constexpr int kSplitMany = 512, kSplitFew = 256;   // apply workgroups: two per compute unit, one
+constexpr int kSplitRows = 6;                      // steps a thread has in flight
+
+// Apply workgroups of the default split for `steps` steps over all cameras.  A
+// workgroup beyond one per compute unit pays its set-up and the atomics of its
+// histogram's flush, all of a camera's on the same 768 words, and is worth it
+// only for work that one per compute unit has not in flight after two rounds.
+// MI355X, apply with statistics, us with 256 and 512 workgroups: one 1920x1080
+// image (1080 steps) 11.9 and 14.4, three 640x480 (480) 10.2 and 13.4, two
+// 1920x1080 (2160) 16.2 and 17.3, five 1031x517 (2585) 16.3 and 16.4, six
+// 1280x720 (4320) 17.7 and 17.9, eight 1920x1080 of 16 bits (8640) 27.1 and 22.8,
+// fourteen 1920x1080 (15120) 47.3 and 42.9 (768 workgroups: 51.7).
+inline int split_total(int64_t steps) { return steps <= 2 * kSplitRows * kSplitFew ? kSplitFew : kSplitMany; }
+
+// How a workgroup of `threads` threads lies over the rows of a camera of `height`
+// rows of `groups` groups of 4 pixels, when `share` workgroups take the camera:
+// `cols` groups of `lanes` rows (at most max_lanes), a row in equal column
+// chunks.  The split whose serial trips to memory are fewest: a thread walks
+// the chunks one after the other and in each its run's steps, kSplitRows of
+// them in flight.  By busy threads alone 640x480 lay 32 x 16 in five chunks (512
+// threads, 30 workgroups) in place of 160 x 3 in one (480 threads, 160): apply
+// with statistics 12.8 us against 10.2, without 7.1 against 4.2; 6x1280x720 of
+// 64 blocks 64 x 8 in five chunks 23.0 against 17.9 for 320 x 1.
+inline void lay_rows(int groups, int height, int share, int max_lanes, int threads, int32_t* cols, int32_t* lanes) {
+  int64_t best = -1;
+  for (int chunks = 1; chunks <= 8 || best < 0; ++chunks) {
+    const int c = (groups + chunks - 1) / chunks;
+    if (c > threads) continue;
+    const int l = threads / c < max_lanes ? threads / c : max_lanes;
+    const int steps = (height + l - 1) / l, m = share < steps ? share : steps;
+    const int run = (steps + m - 1) / m;                // steps of a run
+    const int64_t trips = (int64_t)chunks * ((run + kSplitRows - 1) / kSplitRows);
+    if (best < 0 || trips < best) {
+      best = trips;
+      *cols = c;
+      *lanes = l;
+    }
+  }
+}
+
 // The workgroups of the default split shared among the cameras of the bit mask
 // `active`, by their bytes, at least one each and at most one a step: camera
 // k's runs are workgroups first[k] .. first[k + 1] - 1 (`first` holds n + 1

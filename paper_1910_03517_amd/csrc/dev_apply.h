@@ -10,7 +10,7 @@
 // and walks down the run ap_lanes rows at a time, kUnroll rows in flight, so
 // its pixels' weights and its side's map constants stay in registers.  Images
 // whose groups do not fit the workgroup in one row, or fill it badly, are
-// taken in ap_chunks column chunks (chosen per camera on the host).  The maps
+// taken in column chunks (see lay_rows).  The maps
 // of the run's blocks (or, blended between blocks, of its rows) are staged in
 // LDS, kMapBytes at a time.  The histogram is kept in LDS in kRep replicas
 // interleaved bin by bin, lane l updating replica l % kRep, so that lanes of
@@ -54,9 +54,6 @@ typedef unsigned int u32x3 __attribute__((ext_vector_type(3)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
-#ifndef RC_APPLY_UNROLL
-#define RC_APPLY_UNROLL 6
-#endif
 #ifndef RC_LOAD_POLICY
 #define RC_LOAD_POLICY 2      // non-temporal: every frame byte is touched exactly once
 #endif
@@ -64,7 +61,7 @@ typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 #define RC_STORE_POLICY 2
 #endif
 constexpr int kRep = 8;                        // histogram replicas
-constexpr int kUnroll = RC_APPLY_UNROLL;       // rows in flight per thread
+constexpr int kUnroll = kSplitRows;            // rows in flight per thread
 constexpr int kLoadPolicy = RC_LOAD_POLICY;    // cache-policy bits of frame loads
 constexpr int kStorePolicy = RC_STORE_POLICY;  // cache-policy bits of frame stores
 

@@ -87,15 +87,6 @@ constexpr int kMaxDim = 32768;
 constexpr int kDefaultTileRows = 32;
 constexpr int kMaxApplyGrid = 1 << 16;
 constexpr int kVblendLanes = 32;   // rows whose blended maps fit the staging area in every form
-// Apply workgroups of the default split, two per compute unit.  Measured on
-// the 14x1920x1080 rig (us per frame-set, both kernels): 512 of 512 threads
-// 60.6, 768 69.9, 256 of 1024 threads 75.2, 1024 of 256 threads 59.7 (but 45.1
-// against 42.4 on a rig of small ragged cameras).
-#ifndef RC_APPLY_RUNS
-#define RC_APPLY_RUNS 512
-#endif
-constexpr int kAutoRuns = RC_APPLY_RUNS;
-
 bool aligned(const void* p, uintptr_t a) { return ((uintptr_t)p % a) == 0; }
 
 // Frames of the cameras in `active` only (the others may be NULL).
@@ -154,39 +145,19 @@ rt_status check_active(const rt_ctx* ctx, uint64_t active) {
 
 }  // namespace
 
-// How an apply workgroup lies over the rows of camera d: ap_cols groups of 4
-// pixels by ap_lanes rows, the split of the row into equal column chunks (at
-// most 8) that keeps most of its threads busy.
-static void lay_apply(DevCam& d, int max_lanes) {
-  const int groups = (d.width + 3) / 4;
-  int64_t best = -1;
-  for (int chunks = 1; chunks <= 8 || best < 0; ++chunks) {
-    const int cols = (groups + chunks - 1) / chunks;
-    if (cols > kApplyThreads) continue;
-    const int lanes = std::min(kApplyThreads / cols, max_lanes);
-    // Groups taken per pass of the workgroup over a chunk, of equal worth at
-    // equal use: the fewest chunks win.
-    const int64_t use = (int64_t)groups * lanes * 1024 / chunks;
-    if (use > best + best / 32) {
-      best = use;
-      d.ap_cols = cols;
-      d.ap_lanes = lanes;
-    }
-  }
-}
-
 static bool default_split(const rt_ctx* ctx) { return ctx->grid == 0 && ctx->tile_rows == kDefaultTileRows; }
 
 // The default split's workgroups among the cameras in `active` (split_shares).
 static int share_runs(const rt_ctx* ctx, uint64_t active, uint16_t* first) {
-  int64_t bytes[RT_MAX_CAMS];
+  int64_t bytes[RT_MAX_CAMS], all = 0;
   int32_t steps[RT_MAX_CAMS];
   for (int k = 0; k < ctx->n_cams; ++k) {
     const DevCam& d = ctx->hcams[k];
     bytes[k] = (int64_t)d.height * d.row_bytes;
     steps[k] = (d.height + d.ap_lanes - 1) / d.ap_lanes;
+    if ((active >> k) & 1ull) all += steps[k];
   }
-  return split_shares(ctx->n_cams, bytes, steps, active, kAutoRuns, first);
+  return split_shares(ctx->n_cams, bytes, steps, active, split_total(all), first);
 }
 
 // The context's constants for a launch over the cameras in `active`.
@@ -201,7 +172,7 @@ static Geo geo_for(const rt_ctx* ctx, uint64_t active) {
 
 // Device tables: the rows that each apply workgroup takes.  By default
 // (tile_rows kDefaultTileRows, grid 0) every camera gets a whole number of
-// workgroups, about kAutoRuns of them over the rig in proportion to its bytes,
+// workgroups, split_total of them over the rig in proportion to its bytes,
 // and its rows are split evenly among them, in steps of the rows a workgroup
 // takes at a time.  Any other tile_rows with grid 0: one workgroup per tile,
 // every vertical block cut into ceil(rows / tile_rows) tiles of equal height
@@ -424,7 +395,6 @@ rt_status rt_ctx_create(const rt_camera_desc* cams, int32_t n_cams, const rt_opt
     d.band = std::min(o.band_width, d.half);
     d.row_bytes = c.width * c.channels * d.bps;
     d.pitch = c.pitch_bytes;
-    lay_apply(d, o.vblend ? kVblendLanes : kApplyThreads);
     // Ring neighbours: right side of position p meets the left side of p + 1.
     int m = 0;
     for (int i = 0; i < n_cams; ++i) m += cams[i].ring == c.ring;
@@ -440,6 +410,13 @@ rt_status rt_ctx_create(const rt_camera_desc* cams, int32_t n_cams, const rt_opt
         if (cams[i].ring == c.ring && cams[i].pos == q) d.face_cam[s] = i;
     }
     ctx->w_max = std::max(ctx->w_max, c.width);
+  }
+  int64_t bytes = 0;
+  for (const DevCam& d : ctx->hcams) bytes += (int64_t)d.height * d.row_bytes;
+  for (DevCam& d : ctx->hcams) {
+    const int64_t share = 1 + (kSplitMany - n_cams) * ((int64_t)d.height * d.row_bytes) / bytes;
+    lay_rows((d.width + 3) / 4, d.height, (int)share, o.vblend ? kVblendLanes : kApplyThreads, kApplyThreads, &d.ap_cols,
+             &d.ap_lanes);
   }
   rt_status st = build_tables(ctx, kDefaultTileRows, 0);
   if (st != RT_OK) {

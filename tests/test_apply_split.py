@@ -3,7 +3,8 @@ in exactly one run, a run that ends at its own last row, and no run whose rows
 span many more blocks than it has steps (a workgroup looks at and stages the
 maps of all blocks between its first and its last row).  And of the workgroups
 among the cameras of a launch: by their bytes over the active ones, whatever
-the rest of the rig is."""
+the rest of the rig is.  And of a workgroup's threads over the rows: as few
+serial trips to memory as any split into column chunks needs."""
 import os
 import shutil
 import subprocess
@@ -98,3 +99,40 @@ def test_shares_follow_the_active_cameras(shares, cams, active):
     assert sum(got) <= max(512, len(on))
     # A part of a rig is served as a rig of those cameras alone.
     assert [got[k] for k in on] == shares([cams[k] for k in on], (1 << len(on)) - 1)
+
+
+@pytest.fixture(scope="module")
+def layout(tmp_path_factory):
+    exe = compile_host(str(tmp_path_factory.mktemp("layout")), "layout")
+
+    def get(width, height, share, max_lanes=512):
+        out = subprocess.run([exe, str(-(-width // 4)), str(height), str(share), str(max_lanes)], check=True,
+                             capture_output=True, text=True)
+        return tuple(int(v) for v in out.stdout.split())
+
+    return get
+
+
+def trips(groups, height, share, cols, lanes):
+    steps = -(-height // lanes)
+    return -(-groups // cols) * -(-(-(-steps // min(share, steps))) // 6)
+
+
+@pytest.mark.parametrize("width,height,share,max_lanes", [
+    (1, 1, 1, 512), (4, 32768, 512, 512), (4, 32768, 8, 32), (200, 150, 170, 512), (333, 251, 60, 512), (640, 480, 512, 512),
+    (640, 480, 170, 512), (640, 480, 8, 512), (640, 512, 12, 32), (719, 405, 200, 512), (1031, 517, 90, 512),
+    (1031, 517, 4, 512), (1280, 720, 85, 512), (1920, 1080, 36, 512), (1920, 1080, 512, 32), (2047, 9, 200, 512),
+    (2050, 7, 200, 512), (4096, 2160, 79, 512), (32768, 32768, 512, 512), (32767, 3, 1, 32)])
+def test_layout_takes_the_fewest_trips(layout, width, height, share, max_lanes):
+    cols, lanes, total = layout(width, height, share, max_lanes)
+    groups = -(-width // 4)
+    assert 1 <= cols and 1 <= lanes <= max_lanes and cols * lanes <= 512
+    options = [(c, min(512 // c, max_lanes)) for c in {-(-groups // n) for n in range(1, 9)} if c <= 512]
+    assert all(trips(groups, height, share, cols, lanes) <= trips(groups, height, share, c, l) for c, l in options)
+    assert total == (256 if -(-height // lanes) <= 12 * 256 else 512)
+
+
+def test_small_image_keeps_the_chip_busy(layout, shares):
+    cols, lanes, total = layout(640, 480, 512)
+    assert (cols, lanes) == (160, 3)
+    assert shares([(480 * 1920, -(-480 // lanes))], 1, total) == [160]
