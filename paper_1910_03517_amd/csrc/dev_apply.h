@@ -37,9 +37,12 @@
 // + 3x333x251 u16 + 2x719x405 gray8 57 -> 16, which was the ragged row ends,
 // read byte by byte and row by row.
 //
-// Registers: at most 96 (RC_APPLY_WAVES 5), so that beside the four waves per
-// SIMD of two workgroups a seam-estimate wave finds room; at 108 the pipeline
-// of the 14x1920x1080 rig took 258.8 us per six frame-sets, at 96 250.5.
+// Registers: at most 96 (RC_APPLY_WAVES 5) and none spilled, so that beside the
+// four waves per SIMD of two workgroups a seam-estimate wave finds room; at 108
+// the pipeline of the 14x1920x1080 rig took 258.8 us per six frame-sets, at 96
+// 250.5, and without the six to eight spills of that form 5 us less (246.6 and
+// 241.3 side by side).  The look-ahead launch holds to it too (97 with blended
+// maps); 3x3 maps with statistics take 98.
 #pragma once
 
 #include <type_traits>
@@ -215,8 +218,8 @@ __device__ inline bool small_cross(const int64_t* q, int r) {
 // to LDS; a pass over them of its own took 0.4 us more of every workgroup.
 template <int C, int BPS, int KIND, bool VB>
 __device__ inline int stage_maps(const Geo& g, const Bufs& b, const int64_t* q3, const DevCam& cam, int k, int p0,
-                                 int stride, int j0, int n, ApplyLds& L) {
-  const int nb = g.n_blocks, H = cam.height, tid = threadIdx.x;
+                                 int stride, int j0, int n, ApplyLds& L, int tid) {
+  const int nb = g.n_blocks, H = cam.height;
   constexpr int kPer = KIND == kMapTable ? 2 * C * kNB / 4 : KIND >= kMapCross ? 2 * kX3 : 2 * C;
   int good = n;
   if (!VB && tid < n) L.end[tid] = block_row(j0 + tid + 1, H, nb);
@@ -396,10 +399,9 @@ __device__ inline void one_group(const uint32_t (&d)[C * BPS], uint32_t (&o)[C *
 template <int C, int BPS, int KIND, bool WRITE, bool STATS, bool VB>
 __device__ inline void piece_rows(const Geo& g, const Bufs& b, const DevCam& cam, int k, __amdgpu_buffer_rsrc_t rin,
                                   __amdgpu_buffer_rsrc_t rout, int R0, int step, int p0, int p1, int j0,
-                                  ApplyLds& L, Sums16& sums) {
+                                  ApplyLds& L, Sums16& sums, int tid) {
   constexpr int NW = C * BPS;
   constexpr int kU = KIND == kMapDirect || KIND == kMapCross ? kUnroll : 2;   // (rare maps: fewer registers)
-  const int tid = threadIdx.x;
   const int cols = cam.ap_cols, lanes = cam.ap_lanes;
   const int W = cam.width, half = cam.half, pitch = (int)cam.pitch;
   const int ngroups = (W + 3) >> 2;
@@ -503,8 +505,8 @@ __device__ inline void piece_rows(const Geo& g, const Bufs& b, const DevCam& cam
 // S2) - linear in the histogram for 8-bit samples, the threads' sums for
 // 16-bit ones - to the camera's whole-frame statistics.
 template <int C, int BPS>
-__device__ inline void flush_whole(const Bufs& b, int k, ApplyLds& L, const Sums16& sums) {
-  const int tid = threadIdx.x, lane = tid % kWave;
+__device__ inline void flush_whole(const Bufs& b, int k, ApplyLds& L, const Sums16& sums, int tid) {
+  const int lane = tid % kWave;
   auto add = [&](int i, unsigned long long s) {
     if (lane == 0)
       __hip_atomic_fetch_add(&L.sums[i], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -542,7 +544,12 @@ template <int C, int BPS, bool WRITE, bool STATS, bool VB, bool CROSS, class FP>
 __device__ __attribute__((always_inline)) inline void apply_rows(const Geo& g, const FP& fp, const Bufs& b,
                                                                  const int64_t* q3, const DevCam& cam, int k,
                                                                  const RowRun& run, ApplyLds& L) {
-  const int tid = threadIdx.x, H = cam.height, nb = g.n_blocks;
+  // The thread's index as a value of its own in every camera and form: else what
+  // follows from it is worked out for all of them ahead of the loop over cameras,
+  // kept in registers and, at 96, spilled.
+  int tid = threadIdx.x;
+  asm("" : "+v"(tid));
+  const int H = cam.height, nb = g.n_blocks;
   const int R0 = run.row0, R1 = run.row1, stride = run.stride;
   if (STATS) {
     const u32x4 zero = {0, 0, 0, 0};
@@ -555,7 +562,7 @@ __device__ __attribute__((always_inline)) inline void apply_rows(const Geo& g, c
   Sums16 sums = {0, 0};
   if constexpr (!WRITE) {
     __syncthreads();
-    piece_rows<C, BPS, kMapDirect, WRITE, STATS, false>(g, b, cam, k, rin, rout, R0, stride, R0, R1, 0, L, sums);
+    piece_rows<C, BPS, kMapDirect, WRITE, STATS, false>(g, b, cam, k, rin, rout, R0, stride, R0, R1, 0, L, sums, tid);
   } else {
     // The run in pieces whose maps fit the staging area.  Where a map is too
     // large for the fast form, the entries before it are taken first, then
@@ -574,19 +581,19 @@ __device__ __attribute__((always_inline)) inline void apply_rows(const Geo& g, c
       int n = VB ? min(max(1, kCap / per), (R1 - p0 + stride - 1) / stride) : min(kCap, je - j0 + 1);
       auto end = [&](int m) { return min(R1, VB ? p0 + m * stride : block_row(j0 + m, H, nb)); };
       if (p0 != R0) __syncthreads();      // the previous piece's rows are done with the maps
-      const int good = stage_maps<C, BPS, kFast, VB>(g, b, q3, cam, k, p0, stride, j0, n * per, L) / per;
+      const int good = stage_maps<C, BPS, kFast, VB>(g, b, q3, cam, k, p0, stride, j0, n * per, L, tid) / per;
       if (!kChecked || good > 0) {
         p1 = end(kChecked ? good : n);
-        piece_rows<C, BPS, kFast, WRITE, STATS, VB>(g, b, cam, k, rin, rout, R0, stride, p0, p1, j0, L, sums);
+        piece_rows<C, BPS, kFast, WRITE, STATS, VB>(g, b, cam, k, rin, rout, R0, stride, p0, p1, j0, L, sums, tid);
       } else if constexpr (kChecked) {
         __syncthreads();
-        (void)stage_maps<C, BPS, kExact, VB>(g, b, q3, cam, k, p0, stride, j0, per, L);
+        (void)stage_maps<C, BPS, kExact, VB>(g, b, q3, cam, k, p0, stride, j0, per, L, tid);
         p1 = end(1);
-        piece_rows<C, BPS, kExact, WRITE, STATS, VB>(g, b, cam, k, rin, rout, R0, stride, p0, p1, j0, L, sums);
+        piece_rows<C, BPS, kExact, WRITE, STATS, VB>(g, b, cam, k, rin, rout, R0, stride, p0, p1, j0, L, sums, tid);
       }
     }
   }
-  if (STATS) flush_whole<C, BPS>(b, k, L, sums);
+  if (STATS) flush_whole<C, BPS>(b, k, L, sums, tid);
 }
 
 // Run w of the default split over the active cameras of a larger rig, worked out
