@@ -45,6 +45,21 @@ __host__ __device__ inline RowRun row_run(int height, int lanes, int i, int m, b
 constexpr int kSplitMany = 512, kSplitFew = 256;   // apply workgroups: two per compute unit, one
 constexpr int kSplitRows = 6;                      // steps a thread has in flight
 
+// The forms in which a thread evaluates a row's maps (see dev_apply.h), and the
+// rows of each it has in flight.  Whether a form is rare decides, not what it
+// costs in registers alone: every 16-bit camera takes kMapWide with one channel,
+// every 8-bit rt_apply without statistics kMapTable (55 registers with two
+// rows, 67 with six).  Two rows and six, us: eight 1920x1080 cameras of 16 bits
+// with statistics 23.6 and 22.3, without 17.8 and 16.5, blended maps 22.1 and
+// 20.2; eight of 8-bit gray without statistics 14.0 and 11.4, six 1280x720 of 64
+// blocks 12.3 and 10.6.  The exact forms of 8-bit maps keep two: their 64-bit
+// maps of three channels would not fit the registers beside six rows.
+enum { kMapDirect, kMapWide, kMapTable, kMapCross, kMapCrossWide };
+constexpr int rows_in_flight(int kind, int channels, bool stats) {
+  return kind == kMapDirect || kind == kMapCross || (kind == kMapWide && channels == 1) || (kind == kMapTable && !stats)
+             ? kSplitRows : 2;
+}
+
 // Apply workgroups of the default split for `steps` steps over all cameras.  A
 // workgroup beyond one per compute unit pays its set-up and the atomics of its
 // histogram's flush, all of a camera's on the same 768 words, and is worth it

@@ -7,7 +7,7 @@
 // A workgroup of kApplyThreads threads takes a run of rows.  Its threads lie
 // over the image as ap_lanes rows of ap_cols groups of 4 consecutive pixels
 // (12 bytes for RGB8, 4 for gray8, 8 for gray16); a thread keeps its columns
-// and walks down the run ap_lanes rows at a time, kUnroll rows in flight, so
+// and walks down the run ap_lanes rows at a time, rows_in_flight of them, so
 // its pixels' weights and its side's map constants stay in registers.  Images
 // whose groups do not fit the workgroup in one row, or fill it badly, are
 // taken in column chunks (see lay_rows).  The maps
@@ -64,7 +64,6 @@ typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 #define RC_STORE_POLICY 2
 #endif
 constexpr int kRep = 8;                        // histogram replicas
-constexpr int kUnroll = kSplitRows;            // rows in flight per thread
 constexpr int kLoadPolicy = RC_LOAD_POLICY;    // cache-policy bits of frame loads
 constexpr int kStorePolicy = RC_STORE_POLICY;  // cache-policy bits of frame stores
 
@@ -142,8 +141,6 @@ __device__ inline void store_part(__amdgpu_buffer_rsrc_t r, int off, int nb, con
 //   kMapCross / kMapCrossWide  3x3 maps across the channels, f_r(x) =
 //               clamp((A_r . x + B_r + 2^15) >> 16, 0, 255), in 32-bit integers
 //               (B_r + 2^15 staged) or 64-bit ones.
-enum { kMapDirect, kMapWide, kMapTable, kMapCross, kMapCrossWide };
-
 constexpr int kX3 = 12;   // parameters of one 3x3 map
 
 template <int KIND, int C>
@@ -401,7 +398,7 @@ __device__ inline void piece_rows(const Geo& g, const Bufs& b, const DevCam& cam
                                   __amdgpu_buffer_rsrc_t rout, int R0, int step, int p0, int p1, int j0,
                                   ApplyLds& L, Sums16& sums, int tid) {
   constexpr int NW = C * BPS;
-  constexpr int kU = KIND == kMapDirect || KIND == kMapCross ? kUnroll : 2;   // (rare maps: fewer registers)
+  constexpr int kU = rows_in_flight(KIND, C, STATS);
   const int cols = cam.ap_cols, lanes = cam.ap_lanes;
   const int W = cam.width, half = cam.half, pitch = (int)cam.pitch;
   const int ngroups = (W + 3) >> 2;

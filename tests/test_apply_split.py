@@ -136,3 +136,7 @@ def test_small_image_keeps_the_chip_busy(layout, shares):
     cols, lanes, total = layout(640, 480, 512)
     assert (cols, lanes) == (160, 3)
     assert shares([(480 * 1920, -(-480 // lanes))], 1, total) == [160]
+
+
+def test_ordinary_forms_keep_rows_in_flight(tmp_path):
+    compile_host(str(tmp_path), "rows_in_flight")
