@@ -69,7 +69,7 @@ constexpr int rows_in_flight(int kind, int channels, bool stats) {
 // 1920x1080 (2160) 16.2 and 17.3, five 1031x517 (2585) 16.3 and 16.4, six
 // 1280x720 (4320) 17.7 and 17.9, eight 1920x1080 of 16 bits (8640) 27.1 and 22.8,
 // fourteen 1920x1080 (15120) 47.3 and 42.9 (768 workgroups: 51.7).
-inline int split_total(int64_t steps) { return steps <= 2 * kSplitRows * kSplitFew ? kSplitFew : kSplitMany; }
+__host__ __device__ inline int split_total(int64_t steps) { return steps <= 2 * kSplitRows * kSplitFew ? kSplitFew : kSplitMany; }
 
 // How a workgroup of `threads` threads lies over the rows of a camera of `height`
 // rows of `groups` groups of 4 pixels, when `share` workgroups take the camera:
@@ -97,25 +97,33 @@ inline void lay_rows(int groups, int height, int share, int max_lanes, int threa
   }
 }
 
-// The workgroups of the default split shared among the cameras of the bit mask
-// `active`, by their bytes, at least one each and at most one a step: camera
-// k's runs are workgroups first[k] .. first[k + 1] - 1 (`first` holds n + 1
-// entries).  Returns their number, at most max(total, active cameras).
-inline int split_shares(int n, const int64_t* bytes, const int32_t* steps, uint64_t active, int total,
-                        uint16_t* first) {
-  int64_t all = 0, before = 0;
-  int cams = 0;
+// The workgroups of a camera of `bytes` bytes and `steps` steps, the `before` first
+// of the `all` bytes of a launch being those of the active cameras ahead of it:
+// one, its part by bytes of the `more` beyond one each, and at most one a step.
+// In binary64, whose division the kernels do faster than 64-bit integers': the
+// products stay below 2^47 and the quotients below 512, so each quotient's floor
+// is that of the exact one.
+__host__ __device__ inline int camera_share(int more, int64_t before, int64_t bytes, int64_t all, int steps) {
+  const double to = (double)more * (double)(before + bytes) / (double)all;
+  const double from = (double)more * (double)before / (double)all;
+  const int m = 1 + (int)to - (int)from;
+  return m < steps ? m : steps;
+}
+
+// The default split's workgroups over the cameras of the bit mask `active`:
+// camera k's runs are workgroups first[k] .. first[k + 1] - 1 (`first` holds n + 1
+// entries).  Returns their number.
+inline int split_shares(int n, const int64_t* bytes, const int32_t* steps, uint64_t active, uint16_t* first) {
+  int64_t all = 0, all_steps = 0, before = 0;
+  int cams = 0, w = 0;
   for (int k = 0; k < n; ++k)
-    if ((active >> k) & 1u) all += bytes[k], ++cams;
-  const int64_t more = total > cams ? total - cams : 0;      // beyond one each
-  int w = 0;
+    if ((active >> k) & 1u) all += bytes[k], all_steps += steps[k], ++cams;
+  const int more = split_total(all_steps) - cams;
   for (int k = 0; k < n; ++k) {
     first[k] = (uint16_t)w;
     if (!((active >> k) & 1u)) continue;
-    const int64_t a = more * before / all, e = more * (before + bytes[k]) / all;
+    w += camera_share(more, before, bytes[k], all, steps[k]);
     before += bytes[k];
-    const int m = 1 + (int)(e - a);
-    w += m < steps[k] ? m : steps[k];
   }
   first[n] = (uint16_t)w;
   return w;

@@ -593,21 +593,46 @@ __device__ __attribute__((always_inline)) inline void apply_rows(const Geo& g, c
   if (STATS) flush_whole<C, BPS>(b, k, L, sums, tid);
 }
 
+// Sums of v over the lanes up to and including the own one (all lanes active).
+__device__ inline unsigned long long wave_prefix_u64(unsigned long long v) {
+  v += dpp_u64<0x111>(v);          // row_shr:1
+  v += dpp_u64<0x112>(v);          // row_shr:2
+  v += dpp_u64<0x114>(v);          // row_shr:4
+  v += dpp_u64<0x118>(v);          // row_shr:8
+  v += dpp_u64<0x142, 0xa>(v);     // row_bcast:15 into rows 1 and 3
+  v += dpp_u64<0x143, 0xc>(v);     // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
 // Run w of the default split over the active cameras of a larger rig, worked out
-// here: the context's table shares the workgroups among all cameras and would
-// leave a few of them with a few.  rt_frameset_batch, apply us, table and this:
-// one 1920x1080 camera of 32 45.9 and 18.4 (28.5 with one workgroup per
-// tile), one 1280x720 of 60 38.4 and 13.1 (26.4), seven 1920x1080 of 14 36.7 and
-// 27.1 (37.9).
+// here, a lane per camera, as split_shares does: the context's table shares the
+// workgroups among all cameras and would leave a few of them with a few.  (The
+// shares as a kernel argument of 130 bytes cost every launch of the library 0.1
+// us.)  rt_frameset_batch, apply us, table and this: one 1920x1080 camera of 32
+// 45.9 and 15.5 (28.5 with one workgroup per tile), one 1280x720 of 60 38.4 and
+// 10.9 (26.4), seven 1920x1080 of 14 36.7 and 26.7 (37.9).
 __device__ inline WgRun subset_run(const Geo& g, int w) {
   static_assert(RT_MAX_CAMS <= kWave, "a lane per camera");
   const int lane = threadIdx.x % kWave;
-  const int k = __popcll(__builtin_amdgcn_ballot_w64(lane < g.n_cams && g.first[lane + 1] <= w));
-  const DevCam cam = uniform_cam(g, k);
-  const int i = w - g.first[k], m = g.first[k + 1] - g.first[k];
-  const int steps = (cam.height + cam.ap_lanes - 1) / cam.ap_lanes;
-  const RowRun r = row_run(cam.height, cam.ap_lanes, i, m, runs_interleave(steps, m, g.n_blocks));
-  const RowRun t = row_run(cam.height, cam.ap_lanes, i, m, false);
+  int64_t bytes = 0;
+  int32_t steps = 0, height = 0, lanes = 1;
+  if (lane < g.n_cams && cam_active(g, lane)) {
+    const DevCam& c = g.cams[lane];
+    height = c.height;
+    lanes = c.ap_lanes;
+    bytes = (int64_t)height * c.row_bytes;
+    steps = (height + lanes - 1) / lanes;
+  }
+  const int64_t upto = (int64_t)wave_prefix_u64(bytes);
+  const int64_t all = (int64_t)wave_sum_u64(bytes), all_steps = (int64_t)wave_sum_u64(steps);
+  const int share = steps ? camera_share(split_total(all_steps) - __popcll(g.active), upto - bytes, bytes, all, steps) : 0;
+  const int end = (int)wave_prefix_u64(share);
+  const int k = __popcll(__builtin_amdgcn_ballot_w64(end <= w));   // (the lanes beyond the last camera hold the total)
+  const int m = __builtin_amdgcn_readlane(share, k), i = w - (__builtin_amdgcn_readlane(end, k) - m);
+  height = __builtin_amdgcn_readlane(height, k);
+  lanes = __builtin_amdgcn_readlane(lanes, k);
+  const bool interleave = runs_interleave(__builtin_amdgcn_readlane(steps, k), m, g.n_blocks);
+  const RowRun r = row_run(height, lanes, i, m, interleave), t = row_run(height, lanes, i, m, false);
   return WgRun{k, r.row0, k, r.row1, r.stride, t.row0, t.row1};
 }
 
@@ -615,7 +640,7 @@ __device__ inline WgRun subset_run(const Geo& g, int w) {
 template <bool WRITE, bool STATS, bool VB, bool CROSS, class FP>
 __device__ __attribute__((always_inline)) inline void apply_run(const Geo& g, const FP& fp, const Bufs& b,
                                                                 const int64_t* q3, int w, ApplyLds& L) {
-  const WgRun run = g.subset ? subset_run(g, w) : uniform_run(g, w);
+  const WgRun run = g.runs ? uniform_run(g, w) : subset_run(g, w);
   for (int k = run.cam0; k <= run.cam1; ++k) {
     if (!cam_active(g, k)) continue;              // uniform over the workgroup
     const DevCam cam = uniform_cam(g, k);

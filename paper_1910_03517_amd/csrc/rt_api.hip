@@ -149,15 +149,14 @@ static bool default_split(const rt_ctx* ctx) { return ctx->grid == 0 && ctx->til
 
 // The default split's workgroups among the cameras in `active` (split_shares).
 static int share_runs(const rt_ctx* ctx, uint64_t active, uint16_t* first) {
-  int64_t bytes[RT_MAX_CAMS], all = 0;
+  int64_t bytes[RT_MAX_CAMS];
   int32_t steps[RT_MAX_CAMS];
   for (int k = 0; k < ctx->n_cams; ++k) {
     const DevCam& d = ctx->hcams[k];
     bytes[k] = (int64_t)d.height * d.row_bytes;
     steps[k] = (d.height + d.ap_lanes - 1) / d.ap_lanes;
-    if ((active >> k) & 1ull) all += steps[k];
   }
-  return split_shares(ctx->n_cams, bytes, steps, active, split_total(all), first);
+  return split_shares(ctx->n_cams, bytes, steps, active, first);
 }
 
 // The context's constants for a launch over the cameras in `active`.
@@ -165,8 +164,10 @@ static Geo geo_for(const rt_ctx* ctx, uint64_t active) {
   Geo g = ctx->geo;
   if (g.active == active && g.n_wg) return g;
   g.active = active;
-  g.subset = default_split(ctx) && active != all_cams(ctx->n_cams);
-  g.n_wg = g.subset ? share_runs(ctx, active, g.first) : ctx->n_runs;
+  const bool part = default_split(ctx) && active != all_cams(ctx->n_cams);
+  g.runs = part ? nullptr : ctx->druns;
+  uint16_t first[RT_MAX_CAMS + 1];
+  g.n_wg = part ? share_runs(ctx, active, first) : ctx->n_runs;
   return g;
 }
 
@@ -282,7 +283,6 @@ static rt_status build_tables(rt_ctx* ctx, int tile_rows, int grid) {
   Geo& g = ctx->geo;
   g.n_wg = 0;
   g.cams = ctx->dcams;
-  g.runs = ctx->druns;
   ctx->n_runs = (int32_t)runs.size();
   g.n_cams = n_cams;
   g.n_blocks = nb;

@@ -95,7 +95,7 @@ struct CrossBufs {
 // Context-wide constants passed to every kernel.
 struct Geo {
   const DevCam* cams;    // device array [K]
-  const WgRun* runs;     // device array [n_wg]
+  const WgRun* runs;     // device array [n_wg]; NULL: the default split over a part of the rig
   int32_t n_cams, n_blocks, w_max, n_tiles;
   int32_t mode;
   int32_t n_wg;          // apply workgroups
@@ -103,10 +103,6 @@ struct Geo {
   uint64_t active;       // cameras processed by this launch (bit k = camera k)
   int32_t vblend;        // 1: the maps of adjacent blocks are blended row by row in the apply
   int32_t fit;           // RT_FIT_MOMENTS or RT_FIT_QUANTILE
-  // The default split over a part of the rig's cameras, in place of `runs`: see
-  // split_shares and subset_run.
-  int32_t subset;
-  uint16_t first[RT_MAX_CAMS + 1];
 };
 
 __host__ __device__ inline bool cam_active(const Geo& g, int k) { return (g.active >> k) & 1ull; }
