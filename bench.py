@@ -1025,7 +1025,7 @@ def main() -> int:
                     help="serving leg: rigs of the benchmark ring spread over contexts (0: skip)")
     ap.add_argument("--tile-rows", type=int, default=0)
     ap.add_argument("--grid", type=int, default=None,
-                    help="apply workgroups (rt_ctx_tune; 0 = one per tile; default: the context's own choice)")
+                    help="apply workgroups (rt_ctx_tune; 0 = the default split, or one per tile with --tile-rows; default: the context's own choice)")
     ap.add_argument("--depth", type=int, default=8, help="slots of the pipe mode (>= lanes, >= group, divides --nbuf)")
     ap.add_argument("--copy-only", action="store_true", help="time the streaming copy of the frame bytes only")
     ap.add_argument("--timing-every", type=int, default=0,

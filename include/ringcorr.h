@@ -592,18 +592,15 @@ rt_status rt_graph_set_frames(rt_graph* g, const void* const* frames, void* cons
 rt_status rt_ctx_check(rt_ctx* ctx);
 
 /* Performance knobs that never change results.  The default (tile_rows 32, grid
- * 0): about two apply workgroups per compute unit, shared among the active
- * cameras of the launch by their bytes, each on an even share of its
- * camera's rows.  grid == 0 with
- * another tile_rows (1..4096): each vertical block of each camera is cut into
- * tiles of equal height of at most tile_rows rows, one apply workgroup per
- * tile.  grid > 0
- * (up to 65536): that many workgroups, each on a contiguous share of rows,
- * cut into segments at block boundaries and at most tile_rows rows; with at
- * least one workgroup per camera every camera gets a whole number of shares
+ * 0): one or two apply workgroups per compute unit by the size of the launch,
+ * shared among its active cameras by their bytes, each on an even share of its
+ * camera's rows.  grid == 0 with another tile_rows (1..4096): each vertical
+ * block of each camera is cut into tiles of equal height of at most tile_rows
+ * rows, one apply workgroup per tile.  grid > 0 (up to 65536): that many
+ * workgroups, each on a contiguous share of rows, whatever tile_rows is; with
+ * at least one workgroup per camera every camera gets a whole number of shares
  * (one plus its part of the rest by bytes) split evenly by rows, with fewer
- * the shares are equal in bytes and run across cameras.  This balances the
- * work per compute unit when the tile count does not divide evenly over them.
+ * the shares are equal in bytes and run across cameras.
  * Synchronizes the device; rebuilds the context's tables. */
 rt_status rt_ctx_tune(rt_ctx* ctx, int32_t tile_rows, int32_t grid);
 

@@ -5,8 +5,9 @@ and cached per (GPU architecture, rig signature, options, mode) in a JSON
 file.  The knobs never change results, only speed.
 
 * eager (one rt_frameset per frame-set on one stream, as the serving
-  backend issues its batches): the apply pass's work split, segment height
-  in rows and apply grid (rt_ctx_tune);
+  backend issues its batches): the apply pass's work split (rt_ctx_tune), the
+  default one, tiles of several heights, and contiguous shares of several
+  numbers of workgroups;
 * pipe (rt_pipe: statistics and estimates in order on one stream, applies
   round-robin over several streams): apply lanes and group size together
   with the work split.
@@ -26,6 +27,10 @@ from dataclasses import asdict, dataclass
 DEFAULT_CACHE = os.path.join(os.path.expanduser("~"), ".cache", "ringcorr", "autotune.json")
 TILE_ROWS = (8, 16, 32, 64)
 GRIDS = (0, 512, 768, 1024)
+DEFAULT_SPLIT = (32, 0)     # of a context that was not tuned
+# Raised when a change of the apply kernels or of their splits makes earlier
+# timings worthless; part of every cache key.
+SPLIT_VERSION = 2
 # Pipe mode: (lanes, group, fuse) forms and work splits worth timing.  Unfused,
 # more lanes than 4 or groups larger than the lane count were slower in
 # every measurement; one lane is the plain stream order.  Fused, a group is
@@ -45,9 +50,9 @@ class Choice:
 
 
 def signature(cams, opts, arch: str, mode: str = "eager") -> str:
-    """Stable key of a rig: architecture, every camera's geometry, the options
-    and the launch mode the knobs were timed in."""
-    parts = [arch, f"nb={opts.n_blocks}", f"bw={opts.band_width}", f"closed={int(opts.closed_ring)}"]
+    """Stable key of a rig: architecture, version of the splits, every camera's
+    geometry, the options and the launch mode the knobs were timed in."""
+    parts = [arch, f"v={SPLIT_VERSION}", f"nb={opts.n_blocks}", f"bw={opts.band_width}", f"closed={int(opts.closed_ring)}"]
     if mode != "eager":
         parts.append(f"mode={mode}")
     if getattr(opts, "vblend", False):
@@ -58,10 +63,12 @@ def signature(cams, opts, arch: str, mode: str = "eager") -> str:
 
 
 def candidates(cams, n_blocks: int) -> list[tuple[int, int]]:
-    """(tile_rows, grid) pairs worth timing: tile heights up to the tallest block."""
+    """(tile_rows, grid) pairs worth timing: tile heights up to the tallest block,
+    and each number of workgroups once (the height of a tile does not count
+    then)."""
     tallest = max(-(-c.height // n_blocks) for c in cams)
     rows = sorted({r for r in TILE_ROWS if r <= max(tallest, TILE_ROWS[0])} | {min(tallest, TILE_ROWS[-1])})
-    return [(r, g) for r in rows for g in GRIDS]
+    return [(r, 0) for r in rows] + [(min(tallest, DEFAULT_SPLIT[0]), g) for g in GRIDS if g]
 
 
 def load_cache(path: str = DEFAULT_CACHE) -> dict:
@@ -105,7 +112,8 @@ def time_frameset(rig, frames, outs, iters: int = 30, warmup: int = 5) -> float:
 
 def tune(rig, frames, outs, cache_path: str | None = DEFAULT_CACHE, iters: int = 30,
          cands: list[tuple[int, int]] | None = None) -> Choice:
-    """Time every candidate on this rig, apply the fastest, cache it.
+    """Time the default split and every candidate on this rig (or `cands` alone),
+    apply the fastest, cache it.
 
     frames / outs: lists of per-camera device frame lists (one or more
     frame-sets to rotate over).  The estimator state of the rig advances while
@@ -114,7 +122,9 @@ def tune(rig, frames, outs, cache_path: str | None = DEFAULT_CACHE, iters: int =
     arch = device_arch()
     key = signature(rig.cams, rig.opts, arch)
     best = None
-    for tile_rows, grid in (cands or candidates(rig.cams, rig.opts.n_blocks)):
+    if not cands:
+        cands = [DEFAULT_SPLIT] + [c for c in candidates(rig.cams, rig.opts.n_blocks) if c != DEFAULT_SPLIT]
+    for tile_rows, grid in cands:
         rig.tune(tile_rows, grid)
         us = time_frameset(rig, frames, outs, iters)
         if best is None or us < best.us_per_frameset:
