@@ -186,9 +186,9 @@ __global__ __launch_bounds__(NT) void k_band_estimate(Geo g, FramePtrs fp, Bufs 
   band_estimate_body<NT, kBandPlain, QFIT>(g, fp, BandArgs{}, b, L, (int)blockIdx.x, (int)gridDim.x);
 }
 
-template <int NT>
+template <int NT, int REP>
 __global__ __launch_bounds__(NT) void k_band_estimate_removal(Geo g, FramePtrs fp, PrevPtrs pp, Bufs b, Removal rm) {
-  __shared__ SeamLds<kBandRep> L;
+  __shared__ SeamLds<REP> L;
   band_estimate_body<NT, kBandMotion, false>(g, fp, BandArgs{&pp, &rm, nullptr}, b, L, (int)blockIdx.x,
                                              (int)gridDim.x);
 }
@@ -272,7 +272,9 @@ hipError_t launch_frameset_ahead(const Geo& g, const FramePtrs* fa, const Bufs& 
 // shorter; beside the applies of a pipeline fewer threads and less LDS find
 // room on busy compute units sooner.  14x1920x1080 rig: rt_frameset 48.8 us
 // wide, 49.1 narrow with 8 replicas, 49.9 with 4; six frame-sets through the
-// pipeline 240.4, 241.3 and 234.0 us.
+// pipeline 240.4, 241.3 and 234.0 us; with object removal 45.5 us per frame-set
+// wide and 41.0 narrow with 4, fused 44.0 and 40.5.  A two-branch graph, whose
+// launches run further apart, takes 74.5 us either way and keeps the wide form.
 constexpr int kNarrow = 256, kWide = 512;
 
 hipError_t launch_band_estimate(const Geo& g, const FramePtrs& fp, const Bufs& b, hipStream_t st, bool beside) {
@@ -291,8 +293,12 @@ const void* band_estimate_kernel(const Geo& g) {
 }
 
 hipError_t launch_band_estimate_removal(const Geo& g, const FramePtrs& fp, const PrevPtrs& pp, const Bufs& b,
-                                        const Removal& rm, hipStream_t st) {
-  hipLaunchKernelGGL(k_band_estimate_removal<kWide>, dim3(g.n_cams * g.n_blocks), dim3(kWide), 0, st, g, fp, pp, b, rm);
+                                        const Removal& rm, hipStream_t st, bool beside) {
+  const dim3 grid(g.n_cams * g.n_blocks);
+  if (beside)
+    hipLaunchKernelGGL((k_band_estimate_removal<kNarrow, kBesideRep>), grid, dim3(kNarrow), 0, st, g, fp, pp, b, rm);
+  else
+    hipLaunchKernelGGL((k_band_estimate_removal<kWide, kBandRep>), grid, dim3(kWide), 0, st, g, fp, pp, b, rm);
   return hipGetLastError();
 }
 

@@ -1203,7 +1203,7 @@ static rt_status pipe_submit(rt_pipe* p, uint64_t active, const void* const* fra
     if (!has_prev) memset(&pp, 0, sizeof pp);
     Removal rm = p->rm;
     rm.has_prev = has_prev ? 1 : 0;
-    e = launch_band_estimate_removal(g, fp, pp, be, rm, p->s_est);
+    e = launch_band_estimate_removal(g, fp, pp, be, rm, p->s_est, true);
     if (e == hipSuccess)
       for (int k = 0; k < ctx->n_cams; ++k)
         if ((active >> k) & 1ull) p->prev_in[k] = fp.in[k];

@@ -186,7 +186,7 @@ hipError_t launch_apply_cross(const Geo& g, const FramePtrs& fp, const Bufs& b, 
 struct PrevPtrs;
 struct Removal;
 hipError_t launch_band_estimate_removal(const Geo& g, const FramePtrs& fp, const PrevPtrs& pp, const Bufs& b,
-                                        const Removal& rm, hipStream_t st);
+                                        const Removal& rm, hipStream_t st, bool beside = false);
 hipError_t launch_motion_stats(const Geo& g, const FramePtrs& fp, const PrevPtrs& pp, const Bufs& b,
                                const Removal& rm, hipStream_t st);
 hipError_t launch_estimate_removal(const Geo& g, const Bufs& b, const Removal& rm, hipStream_t st);
