@@ -13,16 +13,22 @@ struct RowRun {
   int32_t row0, row1, stride;
 };
 
+constexpr int kSplitBlocks = 64;   // blocks whose maps a workgroup stages at a time (8-bit affine ones)
+
 // Whether the m runs of a camera of `steps` steps interleave (run i takes steps
 // i, i + m, ...) or lie one after the other (each a contiguous share).
 // Interleaved, all of a camera's workgroups read and write side by side in its
 // frame, a handful of streams for the memory; but a run then spans all blocks
-// and looks at and stages all of their maps, so it needs as many steps as there
-// are blocks.  Apply with statistics on MI355X, us interleaved and contiguous:
-// 14x1920x1080, 30 steps a run, 16 blocks 43.2 and 44.0; 4x4096x2160, 34 steps,
-// 50.2 and 52.1; one 1920x1080 image, 3 steps, 16.3 and 14.4; 14x1920x1080 of 256
-// blocks 59.7 and 45.0, of 64 blocks 44.7 and 44.4.
-__host__ __device__ inline bool runs_interleave(int steps, int m, int n_blocks) { return steps / m >= n_blocks; }
+// and stages all of their maps.  That is worth it from four steps a run on if
+// the maps are staged at once, and else from as many steps as blocks.  Apply with
+// statistics on MI355X, us interleaved and contiguous: 14x1920x1080, 30 steps a
+// run, 16 blocks 43.2 and 44.0; 4x4096x2160, 34 steps, 50.2 and 52.1; sixteen
+// 1280x720, 7 steps, 27.3 and 30.2; one 1280x720, 3 steps, 10.9 and 10.0;
+// 14x1920x1080 of 256 blocks 59.7 and 45.0.
+__host__ __device__ inline bool runs_interleave(int steps, int m, int n_blocks) {
+  const int run = steps / m;
+  return run >= n_blocks || (run >= 4 && n_blocks <= kSplitBlocks);
+}
 
 // Run i of the m runs (m <= steps) of a camera, in steps of `lanes` rows.
 __host__ __device__ inline RowRun row_run(int height, int lanes, int i, int m, bool interleave) {
@@ -74,12 +80,18 @@ __host__ __device__ inline int split_total(int64_t steps) { return steps <= 2 * 
 // How a workgroup of `threads` threads lies over the rows of a camera of `height`
 // rows of `groups` groups of 4 pixels, when `share` workgroups take the camera:
 // `cols` groups of `lanes` rows (at most max_lanes), a row in equal column
-// chunks.  The split whose serial trips to memory are fewest: a thread walks
-// the chunks one after the other and in each its run's steps, kSplitRows of
-// them in flight.  By busy threads alone 640x480 lay 32 x 16 in five chunks (512
-// threads, 30 workgroups) in place of 160 x 3 in one (480 threads, 160): apply
-// with statistics 12.8 us against 10.2, without 7.1 against 4.2; 6x1280x720 of
-// 64 blocks 64 x 8 in five chunks 23.0 against 17.9 for 320 x 1.
+// chunks.  A thread walks the chunks one after the other and in each its run's
+// steps, kSplitRows of them in flight.  The split of the least cost: the steps
+// of all chunks, two for each serial trip to memory, and two for a chunk (its
+// weights, and rows in pieces for the memory); of equal ones the fewest chunks.
+// Apply with statistics, us, laid by busy threads / by trips alone / so:
+// 640x480 32 x 16 in five chunks (512 threads busy, 30 workgroups) 12.4 and
+// otherwise 160 x 3 in one (480 threads, 160 workgroups) 8.8; six 1280x720 of 64
+// blocks 22.8 / 17.9 / 16.8, sixteen of 16 blocks 29.2 / 32.5 / 27.4 (64 x 8, 107 x
+// 4, 160 x 3), thirty-two 46.3 / 52.0 / 43.8; twenty 1600x900 53.2 / 55.6 / 45.7
+// (100 x 5, 80 x 6, 400 x 1); sixteen 1031x517 26.5 / 23.0 / 23.4; fourteen
+// 800x600 19.2 / 18.0 / 18.3; and the sum of steps and trips alone 52.3 on six
+// 2592x1944 (162 x 4), so 49.5 (216 x 2).
 inline void lay_rows(int groups, int height, int share, int max_lanes, int threads, int32_t* cols, int32_t* lanes) {
   int64_t best = -1;
   for (int chunks = 1; chunks <= 8 || best < 0; ++chunks) {
@@ -88,9 +100,9 @@ inline void lay_rows(int groups, int height, int share, int max_lanes, int threa
     const int l = threads / c < max_lanes ? threads / c : max_lanes;
     const int steps = (height + l - 1) / l, m = share < steps ? share : steps;
     const int run = (steps + m - 1) / m;                // steps of a run
-    const int64_t trips = (int64_t)chunks * ((run + kSplitRows - 1) / kSplitRows);
-    if (best < 0 || trips < best) {
-      best = trips;
+    const int64_t cost = (int64_t)chunks * (run + 2 * ((run + kSplitRows - 1) / kSplitRows) + 2);
+    if (best < 0 || cost < best) {
+      best = cost;
       *cols = c;
       *lanes = l;
     }

@@ -68,7 +68,7 @@ constexpr int kLoadPolicy = RC_LOAD_POLICY;    // cache-policy bits of frame loa
 constexpr int kStorePolicy = RC_STORE_POLICY;  // cache-policy bits of frame stores
 
 constexpr int kMapBytes = 3072;                // staged maps
-constexpr int kMapEntries = 64;                // most blocks (or rows) staged at a time
+constexpr int kMapEntries = kSplitBlocks;      // most blocks (or rows) staged at a time
 
 struct ApplyLds {
   alignas(16) uint8_t map[kMapBytes];          // [block or row][side][channel] maps, see stage_maps
