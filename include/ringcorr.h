@@ -605,7 +605,9 @@ rt_status rt_ctx_check(rt_ctx* ctx);
 rt_status rt_ctx_tune(rt_ctx* ctx, int32_t tile_rows, int32_t grid);
 
 /* Current knobs (grid as requested, 0 = the default) and the resulting
- * number of apply segments (any pointer may be NULL). */
+ * number of apply segments: the workgroups of the default split over all
+ * cameras; else the parts of the workgroups' rows inside one block, of at most
+ * tile_rows rows (any pointer may be NULL). */
 rt_status rt_ctx_tuning(const rt_ctx* ctx, int32_t* tile_rows, int32_t* grid, int32_t* n_tiles);
 
 /* Instrumentation: with slots > 0, every `every`-th later apply kernel launch

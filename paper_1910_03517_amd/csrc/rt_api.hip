@@ -186,8 +186,9 @@ static rt_status build_tables(rt_ctx* ctx, int tile_rows, int grid) {
   ctx->grid = grid;
   ++ctx->generation;
   std::vector<WgRun> runs;
-  // Segments (parts of runs inside one block, of at most tile_rows rows) of
-  // rows [a, e) of camera k: what rt_ctx_tuning reports.
+  // Segments of the splits other than the default one (parts of runs inside one
+  // block, of at most tile_rows rows) in rows [a, e) of camera k: what
+  // rt_ctx_tuning reports.
   int64_t segments = 0;
   auto tiles = [&](int k, int a, int e, bool one_run_each) {
     const int H = ctx->cams[k].height;
@@ -208,7 +209,6 @@ static rt_status build_tables(rt_ctx* ctx, int tile_rows, int grid) {
     for (int k = 0; k < n_cams; ++k) {
       const int H = ctx->cams[k].height, lanes = ctx->hcams[k].ap_lanes;
       const int m = first[k + 1] - first[k];
-      tiles(k, 0, H, false);
       for (int i = 0; i < m; ++i) {
         const RowRun r = row_run(H, lanes, i, m, runs_interleave((H + lanes - 1) / lanes, m, nb));
         const RowRun t = row_run(H, lanes, i, m, false);
@@ -287,7 +287,7 @@ static rt_status build_tables(rt_ctx* ctx, int tile_rows, int grid) {
   g.n_cams = n_cams;
   g.n_blocks = nb;
   g.w_max = ctx->w_max;
-  g.n_tiles = (int32_t)segments;
+  g.n_tiles = own ? ctx->n_runs : (int32_t)segments;
   g.mode = ctx->opts.mode;
   g.vblend = ctx->opts.vblend;
   g.fit = ctx->opts.fit;

@@ -11,7 +11,7 @@ namespace rc {
 
 constexpr int kCS = RT_CSLOTS;   // channel slots
 constexpr int kNB = RT_NBINS;    // histogram bins
-constexpr int kThreads = 256;    // threads of every workgroup
+constexpr int kThreads = 256;    // threads of a workgroup, where a kernel names no other number
 constexpr int kMlpIn = RT_MLP_IN, kMlpHid = RT_MLP_HID, kMlpOut = RT_MLP_OUT;
 
 #ifndef RC_APPLY_THREADS
