@@ -55,7 +55,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 METRIC = "corrected GPix/s and % HBM roofline; p50/p99 frame-set latency, plain vs surrogate"
-KERNEL_SOURCES = ["dev_common.h", "dev_apply.h", "dev_estimate.h", "k_apply.hip", "rt_internal.h"]
+KERNEL_SOURCES = ["dev_common.h", "apply_split.h", "dev_apply.h", "dev_estimate.h", "k_apply.hip", "rt_internal.h"]
 # Counter-derived HBM traffic of each form of the dominant kernel.
 TRAFFIC_FILES = {"k_apply_sets<false>": os.path.join(ROOT, "profiles", "k_apply_sets_rig14_traffic.txt"),
                  "k_apply<true,true,false>": os.path.join(ROOT, "profiles", "k_apply_rig14_traffic.txt")}
