@@ -57,9 +57,9 @@ constexpr int kSplitRows = 6;                      // steps a thread has in flig
 // every 8-bit rt_apply without statistics kMapTable (55 registers with two
 // rows, 67 with six).  Two rows and six, us: eight 1920x1080 cameras of 16 bits
 // with statistics 23.6 and 22.3, without 17.8 and 16.5, blended maps 22.1 and
-// 20.2; eight of 8-bit gray without statistics 14.0 and 11.4, six 1280x720 of 64
-// blocks 12.3 and 10.6.  The exact forms of 8-bit maps keep two: their 64-bit
-// maps of three channels would not fit the registers beside six rows.
+// 20.2; eight of 8-bit gray without statistics 14.0 and 11.4.  The exact forms of
+// 8-bit maps keep two: their 64-bit maps of three channels would not fit the
+// registers beside six rows.
 enum { kMapDirect, kMapWide, kMapTable, kMapCross, kMapCrossWide };
 constexpr int rows_in_flight(int kind, int channels, bool stats) {
   return kind == kMapDirect || kind == kMapCross || (kind == kMapWide && channels == 1) || (kind == kMapTable && !stats)
@@ -87,7 +87,8 @@ __host__ __device__ inline int split_total(int64_t steps) { return steps <= 2 * 
 // Apply with statistics, us, laid by busy threads / by trips alone / so:
 // 640x480 32 x 16 in five chunks (512 threads busy, 30 workgroups) 12.4 and
 // otherwise 160 x 3 in one (480 threads, 160 workgroups) 8.8; six 1280x720 of 64
-// blocks 22.8 / 17.9 / 16.8, sixteen of 16 blocks 29.2 / 32.5 / 27.4 (64 x 8, 107 x
+// blocks 22.8 / 17.9 / 16.8 (without statistics 19.7 / 10.5 / 13.4: the table form
+// stages its tables once a chunk), sixteen of 16 blocks 29.2 / 32.5 / 27.4 (64 x 8, 107 x
 // 4, 160 x 3), thirty-two 46.3 / 52.0 / 43.8; twenty 1600x900 53.2 / 55.6 / 45.7
 // (100 x 5, 80 x 6, 400 x 1); sixteen 1031x517 26.5 / 23.0 / 23.4; fourteen
 // 800x600 19.2 / 18.0 / 18.3; and the sum of steps and trips alone 52.3 on six

@@ -32,10 +32,9 @@
 // side by side keep narrow images' workgroups full.  Measured on MI355X (us,
 // statistics fused; one 256-thread workgroup per 22-row tile, runs of
 // neighbouring rows, interleaved runs): 14x1920x1080 RGB8, 174 MB, 50.6, 44.7,
-// 43.0; with rt_frameset's estimate 66, 57.5, 55.7; the uneven rig of 4K, 1080p
-// and 16-bit cameras 110, 101, 96.  1x640x480 18.0 -> 10.6, and 5x1031x517 RGB8
-// + 3x333x251 u16 + 2x719x405 gray8 57 -> 16, which was the ragged row ends,
-// read byte by byte and row by row.
+// 43.0, and 42.0 with the present layout and registers.  1x640x480 18.5 by tiles
+// and 9.3, 5x1031x517 RGB8 58.2 and 14.7, which was the ragged row ends, read
+// byte by byte and row by row.
 //
 // Registers: at most 96 (RC_APPLY_WAVES 5) and none spilled, so that beside the
 // four waves per SIMD of two workgroups a seam-estimate wave finds room; at 108

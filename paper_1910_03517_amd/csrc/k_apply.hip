@@ -1,5 +1,5 @@
 // Apply kernel of section 3.1, weights read from the caller's table.  With
-// statistics, each tile adds its input histogram and sums to the camera's
+// statistics, each run adds its input histogram and sums to the camera's
 // whole-frame statistics with atomics.
 #include <hip/hip_ext.h>
 
